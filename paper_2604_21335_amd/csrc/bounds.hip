@@ -1,46 +1,114 @@
 // Quest page summary: per-page, per-channel min and max of the cached keys
 // (token-level stage of the paper, Sec. 3.2; chunk size 16 from App. C.1).
-#include "build_helpers.hpp"
 #include "stc_common.hpp"
 #include "stc_kernels.hpp"
 
 namespace stc {
 
-// One thread owns 8 adjacent channels (one 128-bit load per token row) of one
-// page and walks the page's tokens.  D/8 neighbouring threads cover a row, so a
-// wavefront reads 64/(D/8) whole rows of 2*D bytes per load instruction.  The result goes
-// into the tiled layout the scoring kernel reads (two 16-byte units per thread); pages
-// past the last one of a stream's last tile are written as zeros.
+typedef __attribute__((ext_vector_type(2))) short i16x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t bounds_u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t bounds_u32x2;
+
+// Two bf16 patterns per dword <-> two signed 16-bit integers in the same order (-0 below +0);
+// the map is its own inverse.
+__device__ __forceinline__ i16x2 bf16_order2(i16x2 x) {
+  return x ^ ((x >> 15) & (i16x2){0x7fff, 0x7fff});
+}
+
+// Lanes that differ in lane bit 5 (SWAP 32) or bit 4 (SWAP 16) hold the same two quantities a
+// and b for different rows: the swap gives one half of the lanes both values of a, the other
+// half both values of b, so one min/max reduces both.
+template <int SWAP, class Op>
+__device__ __forceinline__ i16x2 fold_pair(i16x2 a, i16x2 b, Op op) {
+  const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+  const auto r = SWAP == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                            : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+  return op(__builtin_bit_cast(i16x2, (uint32_t)r[0]), __builtin_bit_cast(i16x2, (uint32_t)r[1]));
+}
+
+constexpr int kBoundsWavePages = 2;  // adjacent pages per wavefront, all requested at once
+
+// One wavefront takes 2 adjacent pages.  Every request is 1 KiB of adjacent addresses (4 token
+// rows at D = 128, 8 at D = 64): lane l receives channels 8*(l % LPR) .. +8 of row l / LPR, so
+// the lanes l + LPR*i hold the same channels of different rows.  Minima and maxima are taken
+// on packed 16-bit integers, first over a lane's own rows, then across lanes by swapping halves
+// of register pairs, which leaves every lane with the minimum and maximum of two channels.
+// Bound by memory (K is read once, 1/8 of it written).  K is larger than the caches wherever
+// the time matters, so it is read with streaming loads that leave them alone.  Measured on 64
+// streams of 32768 tokens (604 MB): 95.8 us (6.3 TB/s) against 106.5 with ordinary loads, 113
+// with 4 pages per wavefront, 124-137 with wavefronts that walk a run of pages, and 131 for
+// the form before, in which a thread walked the 16 rows of a page four loads at a time (a request
+// was four pieces of 256 bytes in four pages).
 template <int D>
-__global__ __launch_bounds__(256) void bounds_kernel(const uint4* __restrict__ K,
-                                                     uint4* __restrict__ bounds, int N, int NP,
+__global__ __launch_bounds__(256) void bounds_kernel(const bounds_u32x4* __restrict__ K,
+                                                     uint32_t* __restrict__ bounds, int N, int NP,
                                                      int Ncap) {
-  constexpr int LPP = D / 8;  // threads per page
+  constexpr int LPR = D / 8;            // lanes per token row
+  constexpr int RPL = 64 / LPR;         // rows per request
+  constexpr int NLD = kPage / RPL;      // requests per page
+  constexpr int PW = kBoundsWavePages;
   const int stream = blockIdx.y;
-  const int sub = threadIdx.x % LPP;
-  const int page = blockIdx.x * (256 / LPP) + threadIdx.x / LPP;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int p0 = (blockIdx.x * 4 + wave) * PW;
   const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
-  if (page >= ntiles * kBoundsTilePages) return;
-  const int t0 = page * kPage;
-  const int t1 = min(t0 + kPage, N);  // t1 <= t0 for a padding page: zeros
-  uint32_t w[8];  // per channel: minimum | maximum << 16
-  page_bounds_words<D>(K + ((size_t)stream * Ncap + t0) * LPP + sub, t1 - t0, w);
-  store_bounds_units<D>(
-      bounds + (size_t)stream * bounds_tiles(Ncap) * (bounds_tile_dwords(D) / 4), page, sub, w);
+  if (p0 >= ntiles * kBoundsTilePages) return;
+  const int piece = lane % LPR, row = lane / LPR;
+  const bounds_u32x4* Ks = K + (size_t)stream * Ncap * LPR + piece;
+  // rows past the last token repeat it, which changes neither minimum nor maximum
+  bounds_u32x4 v[PW][NLD];
+#pragma unroll
+  for (int p = 0; p < PW; ++p)
+#pragma unroll
+    for (int j = 0; j < NLD; ++j)
+      v[p][j] = __builtin_nontemporal_load(
+          Ks + (size_t)min((p0 + p) * kPage + j * RPL + row, N - 1) * LPR);
+  uint32_t* tiles = bounds + (size_t)stream * bounds_tiles(Ncap) * bounds_tile_dwords(D);
+  auto lo = [](i16x2 a, i16x2 b) { return __builtin_elementwise_min(a, b); };
+  auto hi = [](i16x2 a, i16x2 b) { return __builtin_elementwise_max(a, b); };
+#pragma unroll
+  for (int p = 0; p < PW; ++p) {
+    i16x2 mn[4], mx[4];  // channels 8*piece + 2*d, +1
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+#pragma unroll
+      for (int j = 0; j < NLD; ++j) {
+        const i16x2 k = bf16_order2(__builtin_bit_cast(i16x2, (uint32_t)v[p][j][d]));
+        mn[d] = j ? lo(mn[d], k) : k;
+        mx[d] = j ? hi(mx[d], k) : k;
+      }
+    }
+    // lane bit 5 chooses between dwords d and d + 2, lane bit 4 between d and d + 1
+    i16x2 a = fold_pair<16>(fold_pair<32>(mn[0], mn[2], lo), fold_pair<32>(mn[1], mn[3], lo), lo);
+    i16x2 b = fold_pair<16>(fold_pair<32>(mx[0], mx[2], hi), fold_pair<32>(mx[1], mx[3], hi), hi);
+    if constexpr (D == 64) {  // rows also differ in lane bit 3
+      a = lo(a, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, a))));
+      b = hi(b, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, b))));
+    }
+    uint32_t mnw = __builtin_bit_cast(uint32_t, bf16_order2(a));
+    uint32_t mxw = __builtin_bit_cast(uint32_t, bf16_order2(b));
+    const int page = p0 + p;
+    if (page >= NP) mnw = mxw = 0u;  // padding pages of the stream's last tile
+    // minimum in the low half, maximum in the high half of each channel's dword
+    const bounds_u32x2 w = {(mnw & 0xffffu) | (mxw << 16), (mnw >> 16) | (mxw & 0xffff0000u)};
+    const int c = 8 * piece + 2 * (lane >> 4);
+    if (D == 128 || (lane & 8) == 0)
+      *(bounds_u32x2*)(tiles + (size_t)(page / kBoundsTilePages) * bounds_tile_dwords(D) +
+                       bounds_tile_unit(D, page % kBoundsTilePages, c) * 4 + c % 4) = w;
+  }
 }
 
 int launch_bounds(const stc_shape_t& s, const void* K, void* bounds, hipStream_t st) {
   const int NP = (s.N + kPage - 1) / kPage;
   const int streams = s.B * s.Hkv;
-  const int pages_per_block = 256 / (s.D / 8);
+  const int pages_per_block = 4 * kBoundsWavePages;
   const int pages = (NP + kBoundsTilePages - 1) / kBoundsTilePages * kBoundsTilePages;
   dim3 grid((pages + pages_per_block - 1) / pages_per_block, streams);
   if (s.D == 128)
-    bounds_kernel<128><<<grid, 256, 0, st>>>((const uint4*)K, (uint4*)bounds, s.N, NP,
-                                          token_cap(s));
+    bounds_kernel<128><<<grid, 256, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N, NP,
+                                             token_cap(s));
   else
-    bounds_kernel<64><<<grid, 256, 0, st>>>((const uint4*)K, (uint4*)bounds, s.N, NP,
-                                         token_cap(s));
+    bounds_kernel<64><<<grid, 256, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N, NP,
+                                            token_cap(s));
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
