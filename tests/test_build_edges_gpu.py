@@ -1,0 +1,51 @@
+"""Cache construction at the edges of its kernels' tiles: page bounds (2 pages per wavefront,
+8 per tile), the packed copy (64 tokens per workgroup, chunks of 256), against the oracle, bit
+for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_21335_amd as stc
+from oracle import stc_oracle as O
+from tests import parity as PT
+from tests.helpers import randn_bf16
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("D,G,room", [(128, 8, 0), (128, 16, 37), (128, 1, 0), (64, 4, 5), (64, 8, 0)])
+@pytest.mark.parametrize("N", [1, 15, 17, 63, 64, 65, 129, 255, 256, 257, 321, 528])
+def test_bounds_and_packed_copy_at_tile_edges(N, D, G, room):
+    """Every array of the cache, with and without spare token capacity; slots behind the kept
+    groups stay untouched, and so do those behind a capacity that ends inside a workgroup's run."""
+    B, Hkv = 2, 3
+    rng = np.random.default_rng(1000 * D + 10 * G + N)
+    K, V = randn_bf16(rng, (B, Hkv, N, D)), randn_bf16(rng, (B, Hkv, N, D))
+    K[0, 0, ::3] = 0x8000                                  # -0 next to ordinary values
+    mask = rng.integers(0, 1 << G, size=(B, Hkv, N)).astype(np.uint16)
+    mask[1, 1] = 0                                         # a stream that keeps nothing
+    mask[1, 2] = (1 << G) - 1                              # and one that keeps everything
+    want = [[(m := mask[b, h], off := O.token_offsets(m, G), O.pack_values(V[b, h], m, off, G))
+             for h in range(Hkv)] for b in range(B)]
+    # one less than the kept groups of the second stream, so that its last slot is dropped
+    tight = max(1, int(want[0][1][1][-1]) - 1)
+    for cap in ((N + room) * G, tight):
+        c = stc.RoutedCache(B, Hkv, Hkv, D, N, G, 1, v_cap_groups=cap, device=DEV,
+                            n_cap=N + room if room else 0)
+        c.vpacked.view(torch.int16).fill_(0x7FC0)
+        c.build(PT.to_dev_bf16(K), PT.to_dev_bf16(V), mask_in=PT.to_dev_u16(mask))
+        torch.cuda.synchronize()
+        rows, vp = PT.host_bf16(c.bounds_rows()), PT.host_bf16(c.vpacked)
+        over = False
+        for b in range(B):
+            for h in range(Hkv):
+                m, off, packed = want[b][h]
+                n = min(int(off[-1]), cap)
+                over |= int(off[-1]) > cap
+                assert np.array_equal(rows[b, h], O.page_bounds(K[b, h]))
+                assert np.array_equal(PT.host_u16(c.mask)[b, h, :N], m)
+                assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[b, h, :N + 1], off)
+                assert np.array_equal(vp[b, h, :n], packed[:n])
+                assert np.all(vp[b, h, n:] == 0x7FC0)
+        assert int(c.dev_status.item()) == int(over)
