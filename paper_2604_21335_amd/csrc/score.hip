@@ -158,7 +158,7 @@ void score_mfma_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restri
 
 // The same scores with the query operands in shared memory (score_tiles.hpp): at most 128
 // registers, so four wavefronts per SIMD also for five to eight heads per KV head.
-template <int D, int R, bool PER_HEAD, int WAVES>
+template <int D, int R, bool PER_HEAD, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void score_lds_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restrict__ q,
                       float* __restrict__ score, int NP, int Hq, int Hkv, int tiles_per_block,
@@ -172,7 +172,7 @@ void score_lds_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restric
   const int t0 = blockIdx.x * tiles_per_block;
   const int t1 = min(t0 + tiles_per_block, ntiles);
   const uint16_t* qs = q + ((size_t)b * Hq + kvh * R) * D;
-  score_tile_range<D, R, PER_HEAD, WAVES, 1>(
+  score_tile_range<D, R, PER_HEAD, WAVES, 1, STREAM>(
       (const score_u32x4*)tiles + (size_t)stream * tiles_cap * T16 + lane,
       score + (size_t)stream * (PER_HEAD ? R : 1) * NP, NP, t0, t1, s_q, wave, lane, [&] {
         score_fill_q<D, R, 64 * WAVES>(qs, s_q);
@@ -240,6 +240,7 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const int R = s.Hq / s.Hkv;
   const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
   const int tcap = bounds_tiles(token_cap(s));  // tiles per stream in memory
+  constexpr int T16 = (D / 32) * 64;            // 16-byte units per tile
   // about three workgroups per CU (what the register budget keeps resident), so the whole
   // grid runs as one generation and the per-wavefront set-up is paid once per several tiles
   const int want_blocks = max(1, 768 / streams);
@@ -249,23 +250,31 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const u32x4* t4 = (const u32x4*)bounds;
   const uint16_t* q16 = (const uint16_t*)q;
   if (D == 128 && R > 4 && R <= 8) {
-    // query operands in shared memory.  Many small workgroups (about 2048: two tiles per
-    // wavefront on the headline shape) whose wavefronts request one tile at a time: measured,
-    // the memory system delivers more with fewer requests outstanding per wavefront (13.3 us
-    // against 14.6 with two tiles requested ahead and a third as many workgroups)
+    // Query operands in shared memory, one tile requested at a time per wavefront (measured: two
+    // requested ahead is slower at every grid).  Bounds of 32 MiB and more are read with
+    // streaming loads by about 1024 workgroups (12.4 us at 64 streams of 2048 pages, 67 MB, four
+    // tiles per wavefront; 13.2 with 2048 workgroups, 13.9 with ordinary loads and either).
+    // Smaller ones may still lie in the last-level cache and are faster with ordinary loads
+    // and as many workgroups as there are tiles for, up to 2048 (4 streams of 8192 pages,
+    // 17 MB: 5.6 us against 6.1 with streaming loads, 6.5 with 256 workgroups).
     constexpr int WV = 4;
-    const int want = max(1, 2048 / streams);
+    const bool stream_loads = (long long)streams * ntiles * T16 * 16 >= (32ll << 20);
+    const int want = max(1, (stream_loads ? 1024 : 2048) / streams);
     int tp = (ntiles + want - 1) / want;
     tp = (tp + WV - 1) / WV * WV;
     dim3 g2((ntiles + tp - 1) / tp, streams);
-#define STC_SCORE_LDS_CASE(RR)                                                                 \
-  case RR:                                                                                     \
-    if (per_head)                                                                              \
-      score_lds_kernel<D, RR, true, WV><<<g2, 64 * WV, 0, st>>>(t4, q16, score, NP, s.Hq,      \
-                                                                s.Hkv, tp, tcap);              \
-    else                                                                                       \
-      score_lds_kernel<D, RR, false, WV><<<g2, 64 * WV, 0, st>>>(t4, q16, score, NP, s.Hq,     \
-                                                                 s.Hkv, tp, tcap);             \
+#define STC_SCORE_LDS_GO(RR, PH, STREAM)                                                        \
+  score_lds_kernel<D, RR, PH, WV, STREAM><<<g2, 64 * WV, 0, st>>>(t4, q16, score, NP, s.Hq,     \
+                                                                  s.Hkv, tp, tcap)
+#define STC_SCORE_LDS_CASE(RR)                                                                  \
+  case RR:                                                                                      \
+    if (per_head) {                                                                             \
+      if (stream_loads) STC_SCORE_LDS_GO(RR, true, true);                                                \
+      else STC_SCORE_LDS_GO(RR, true, false);                                                   \
+    } else {                                                                                    \
+      if (stream_loads) STC_SCORE_LDS_GO(RR, false, true);                                               \
+      else STC_SCORE_LDS_GO(RR, false, false);                                                  \
+    }                                                                                           \
     break;
     switch (R) {
       STC_SCORE_LDS_CASE(5)
@@ -274,6 +283,7 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
       STC_SCORE_LDS_CASE(8)
     }
 #undef STC_SCORE_LDS_CASE
+#undef STC_SCORE_LDS_GO
     return;
   }
 #define STC_SCORE_CASE(RR)                                                                    \

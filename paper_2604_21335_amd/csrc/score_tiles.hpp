@@ -48,10 +48,12 @@ __device__ __forceinline__ void score_fill_q(const uint16_t* __restrict__ qs, un
 
 // Scores tiles t0 + wave, t0 + wave + WAVES, ... < t1 of one stream.  `base` = the stream's
 // tiles + lane; out = the stream's score row(s).  DEPTH tiles of the wavefront are requested
-// ahead (DEPTH - 1 in flight behind the one being computed).  `prologue` is run by every thread
+// ahead (DEPTH - 1 in flight behind the one being computed); STREAM: with loads that leave the
+// caches alone.  `prologue` is run by every thread
 // once the first tiles have been requested: it fills the operand table (score_fill_q) and
 // synchronises the workgroup, so that the latency of the query loads hides behind the tiles'.
-template <int D, int R, bool PER_HEAD, int WAVES, int DEPTH = 2, class Prologue>
+template <int D, int R, bool PER_HEAD, int WAVES, int DEPTH = 2, bool STREAM = false,
+          class Prologue>
 __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__ base,
                                                  float* __restrict__ out, int NP, int t0, int t1,
                                                  const unsigned char* qlds, int wave, int lane,
@@ -62,7 +64,8 @@ __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__
   auto load_tile = [&](score_u32x4 (&dst)[NJ], int tt) {
     const score_u32x4* pt = base + (size_t)min(tt, tlast) * T16;  // past the range: last tile again
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) dst[j] = pt[j * 64];
+    for (int j = 0; j < NJ; ++j)
+      dst[j] = STREAM ? __builtin_nontemporal_load(pt + j * 64) : pt[j * 64];
   };
   auto score_tile = [&](const score_u32x4 (&cur)[NJ], int tt) {
     float best = 0.f;
