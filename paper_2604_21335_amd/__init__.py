@@ -133,8 +133,16 @@ def _ptr(t, dtype=None, name="tensor"):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# The current stream's handle without building a torch.cuda.Stream object for it: 0.3 us per
+# call instead of 2.8, of about 12 that a small call takes to issue.  (A build of torch that
+# does not have the accessor is asked the long way.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _nbytes(t):
