@@ -49,3 +49,33 @@ def test_bounds_and_packed_copy_at_tile_edges(N, D, G, room):
                 assert np.array_equal(vp[b, h, :n], packed[:n])
                 assert np.all(vp[b, h, n:] == 0x7FC0)
         assert int(c.dev_status.item()) == int(over)
+
+
+@pytest.mark.parametrize("N,G,room", [(1, 8, 0), (33, 1, 2), (2047, 8, 1), (2048, 8, 0), (2049, 8, 0), (4096, 8, 0),
+                                      (4097, 8, 3), (8192, 8, 0), (8193, 8, 0), (16384, 2, 0), (16385, 2, 0),
+                                      (16385, 1, 0), (4095, 16, 0), (4097, 16, 0), (513, 4, 0)])
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("tied", [False, True])
+def test_global_budget_at_the_limits_of_its_one_workgroup_form(N, G, room, shared, tied):
+    """Sets of up to 65536 logits and 16384 tokens are selected by one workgroup (16, 32 or 64 keys
+    per thread), larger ones in passes over the chip: masks and offsets equal the oracle's for
+    both, with logits that are mostly equal and with a set per stream or per batch element."""
+    B, Hkv, D = 2, 2, 128
+    rng = np.random.default_rng(7 * N + G)
+    H = 1 if shared else Hkv
+    logits = rng.standard_normal((B, H, N, G)).astype(np.float32)
+    if tied:
+        logits = np.round(logits).astype(np.float32)
+        logits[rng.random(logits.shape) < 0.3] = -0.0
+    V = torch.zeros(B, Hkv, N, D, dtype=torch.bfloat16, device=DEV)
+    K = torch.zeros_like(V)
+    for gk in sorted({0, 1, (G + 1) // 2, G}):
+        c = stc.RoutedCache(B, Hkv, Hkv, D, N, G, 1, device=DEV, n_cap=N + room if room else 0)
+        c.build(K, V, logits=torch.from_numpy(logits).to(DEV), global_k=gk, shared=shared)
+        torch.cuda.synchronize()
+        for b in range(B):
+            for h in range(Hkv):
+                m = O.route_mask_global(logits[b, 0 if shared else h], N * gk)
+                assert np.array_equal(PT.host_u16(c.mask)[b, h, :N], m), (b, h, gk)
+                assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[b, h, :N + 1],
+                                      O.token_offsets(m, G))
