@@ -6,21 +6,34 @@
 // tree over adjacent channels, and the chunk sums are accumulated left to right; the bias is
 // added last.
 //
-// The products come from the matrix cores, exactly: v_mfma_f32_4x4x4_16b_bf16 multiplies, per
-// block, a 4x4 A (rows = 4 groups, 4 k-slots) with a 4x4 B (k-slots, columns = 4 tokens).  A
-// B register pair holds 4 adjacent channels of the lane's token as loaded; the A row holds the
-// weight of ONE of those channels in its slot and zeros in the other three, so every output is
-// a single product of two bf16 values (exact in float) plus exact zeros, whatever rounding the
-// unit applies to longer sums.  All additions are ordinary float additions in the fixed order.
+// The products and the first level of the tree come from the matrix cores, exactly.
+// v_mfma_f32_4x4x4_16b_bf16 multiplies, per block, a 4x4 A (rows = 4 groups, 4 k-slots) with a
+// 4x4 B (k-slots, columns = 4 tokens).  A B register pair holds 4 adjacent channels of the
+// lane's token as loaded; the A row holds the weight of ONE even channel in its slot and zeros
+// in the other three, so every output is a single product of two bf16 values (exact in float)
+// plus exact zeros, whatever rounding the unit applies to longer sums.
+// v_mfma_f32_4x4x1_16b_f32 then adds the odd neighbour's product: it has one k-slot, takes float
+// operands and rounds once, like fmaf (4 M random cases agree bit for bit, subnormal
+// products among them), and the product of two bf16 values is exact, so what it rounds is
+// the sum of the two products.  The other additions are ordinary float additions in the
+// fixed order.  The float unit does not read subnormal operands as zero as the bf16 unit does,
+// so they are replaced by zero on the way.
 //
 // Lane l of a wavefront: token 4*(l/32) + l%4 of a group of 8 tokens, channels
 // 16*((l/4)%8) .. +16 of the current chunk (two 16-byte loads of h).  The 16 blocks of the MFMA
 // are the 16 (token quad, 16-channel piece) pairs; the lane supplies the A row of group l%4
 // (+4 per further MFMA group) for its block's channels.  Per (token, group) the 16 products of
-// a lane are summed as a pair tree in the lane, the 8 pieces by the rotations and the row
-// exchange of chunk_tree_sum; the lanes with (l & 0x1c) == 4 hold the chunk sums and carry the
-// accumulators.  A wavefront works on TG groups of 8 tokens per chunk, so the weights of a
-// chunk are fetched and masked once for 8*TG tokens.
+// a lane are summed as a pair tree in the lane.  The 8 pieces are summed across lanes, several
+// groups at a time: a level of that tree needs a result in only half of the lanes, so after
+// each level two registers are merged into one.  In the end a lane carries the accumulator of
+// its token and the group that lane bits 2, 3 (and 4) name.  A wavefront works on TG groups of
+// 8 tokens per chunk, so the weights of a chunk are fetched and masked once for 8*TG tokens.
+//
+// Bound by memory and by the additions together.  Measured on 16 x 32768 tokens of 3584
+// channels, 8 groups (3.77 GB): 760 us (5.0 TB/s; 683 on constant data, which draw less power) against 915 with all additions on the vector
+// ALUs, a reduction of its own per group and half as many tokens per wavefront.  Streaming loads
+// are slower here (834 against 749 in an earlier form): the two requests of a chunk take
+// turns within each line.
 //
 // Inputs are zero or normal bf16 numbers (the matrix cores read subnormal bf16 inputs as
 // zero), with products in the normal float range.
@@ -32,156 +45,224 @@ namespace stc {
 typedef __attribute__((ext_vector_type(4))) short bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t router_u32x4;
 
 __device__ __forceinline__ bf16x4 router_bf16x4(uint32_t w0, uint32_t w1) {
   return __builtin_bit_cast(bf16x4, (u32x2){w0, w1});
 }
 
-template <int G>
+// TG groups of 8 tokens per wavefront.  SPLIT: the wavefronts of a workgroup work on the same
+// tokens and take the chunks in turn, for launches of few tokens; their chunk sums meet in LDS and
+// are accumulated there in the same order.
+constexpr int kSplitWaves = 8;
+constexpr int kSplitChunks = 64;  // chunk sums held in LDS at a time
+template <int G, int TG, bool SPLIT>
 struct RouterCfg {
   static constexpr int NH = (G + 3) / 4;        // MFMA row groups of 4 router outputs
-  static constexpr int TG = G == 16 ? 1 : 2;    // groups of 8 tokens per wavefront
+  static constexpr int NA = (NH + 1) / 2;       // accumulators per lane and token group
+  static constexpr int WAVES = SPLIT ? kSplitWaves : 4;
   static constexpr int WAVE_TOKENS = 8 * TG;
-  static constexpr int BLOCK_TOKENS = 4 * WAVE_TOKENS;
+  static constexpr int BLOCK_TOKENS = (SPLIT ? 1 : WAVES) * WAVE_TOKENS;
+  static_assert(!SPLIT || TG * NA <= kSplitWaves, "one wavefront per accumulator");
 };
 
-template <int G>
-__global__ __launch_bounds__(256) void router_logits_kernel(const uint4* __restrict__ h,
-                                                            const uint4* __restrict__ W,
+// The odd channel of a dword of two bf16 values as float, zero if it is subnormal (class bits:
+// zeros and subnormals of either sign; the even channel below it makes a zero a subnormal).
+__device__ __forceinline__ float odd_channel(uint32_t w) {
+  const bool zero = __builtin_amdgcn_classf(__uint_as_float(w), 0xf0);
+  return zero ? 0.f : bf16_hi(w);
+}
+
+// First two levels of the sum over the 4 lanes that share lane bits 0, 1, 4 and 5 (pieces
+// (0,1)(2,3), then both) for the four router outputs v[0..3]: the lane with bit 2 set holds
+// outputs 0 / 2, the other 1 / 3; bit 3 set: 0 / 1, clear: 2 / 3.
+__device__ __forceinline__ float fold_four(const float (&v)[4], bool bit2, bool bit3) {
+  // (every sum is taken in all lanes: a lane cannot read from one that a branch switched off)
+  const float s0 = v[0] + dpp_f32<0x124>(v[0]);  // row_ror:4, the piece before
+  const float s1 = v[1] + dpp_f32<0x12c>(v[1]);  // row_ror:12, the piece behind
+  const float s2 = v[2] + dpp_f32<0x124>(v[2]);
+  const float s3 = v[3] + dpp_f32<0x12c>(v[3]);
+  const float x01 = bit2 ? s0 : s1, x23 = bit2 ? s2 : s3;
+  const float y01 = x01 + dpp_f32<0x128>(x01), y23 = x23 + dpp_f32<0x128>(x23);
+  return bit3 ? y01 : y23;
+}
+
+template <int G, int TG, bool SPLIT>
+__global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_logits_kernel(
+                                                            const router_u32x4* __restrict__ h,
+                                                            const router_u32x4* __restrict__ W,
                                                             const float* __restrict__ bias,
                                                             float* __restrict__ logits, int N,
                                                             int d_model, int Hkv,
                                                             int bias_stride) {
-  using C = RouterCfg<G>;
-  constexpr int NH = C::NH, TG = C::TG;
+  using C = RouterCfg<G, TG, SPLIT>;
+  constexpr int NH = C::NH, NA = C::NA;
+  constexpr int STEP = SPLIT ? kSplitWaves : 1;
+  __shared__ float s_sum[SPLIT ? kSplitChunks * TG * NA * 64 : 1];
   const int b = blockIdx.y;
   if (bias) bias += (size_t)b * bias_stride;  // 0: one bias for the batch; G: one per element
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 3, dp = (lane >> 2) & 7, tq = lane >> 5;
-  const int t_first = blockIdx.x * C::BLOCK_TOKENS + wave * C::WAVE_TOKENS + 4 * tq + j;
+  const bool bit2 = lane & 4, bit3 = lane & 8;
+  const int t_first = blockIdx.x * C::BLOCK_TOKENS + (SPLIT ? 0 : wave * C::WAVE_TOKENS) +
+                      4 * tq + j;
   const int nc = d_model / 128;
   const int row16 = d_model / 8;  // 16-byte pieces per row
 
   // rows past the end repeat the last token (never stored)
-  const uint4* hp[TG];
+  const router_u32x4* hp[TG];
 #pragma unroll
   for (int g8 = 0; g8 < TG; ++g8)
     hp[g8] = h + ((size_t)b * N + min(t_first + 8 * g8, N - 1)) * row16 + dp * 2;
   // the A rows this lane supplies: router output 4*hh + j (none beyond G: zeros)
-  const uint4* wp[NH];
+  const router_u32x4* wp[NH];
 #pragma unroll
   for (int hh = 0; hh < NH; ++hh) wp[hh] = W + (size_t)min(4 * hh + j, G - 1) * row16 + dp * 2;
 
-  float acc[TG][NH][4];
+  float acc[TG][NA];
 #pragma unroll
   for (int g8 = 0; g8 < TG; ++g8)
 #pragma unroll
+    for (int a = 0; a < NA; ++a) acc[g8][a] = 0.f;
+
+  router_u32x4 hx[TG][2], wx[NH][2];
+  const int c_first = SPLIT ? min(wave, nc - 1) : 0;
+#pragma unroll
+  for (int g8 = 0; g8 < TG; ++g8)
+    hx[g8][0] = hp[g8][c_first * 16], hx[g8][1] = hp[g8][c_first * 16 + 1];
+#pragma unroll
+  for (int hh = 0; hh < NH; ++hh)
+    wx[hh][0] = wp[hh][c_first * 16], wx[hh][1] = wp[hh][c_first * 16 + 1];
+
+  for (int base = 0; base < nc; base += SPLIT ? kSplitChunks : nc) {
+  const int cend = SPLIT ? min(base + kSplitChunks, nc) : nc;
+  for (int c = base + (SPLIT ? wave : 0); c < cend; c += STEP) {
+    // A operands of this chunk, per dword of two channels: the even channel's weight alone in
+    // the low half, the odd channel's as float
+    uint32_t we[NH][8];
+    float wo[NH][8];
+#pragma unroll
     for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[g8][hh][i] = 0.f;
-
-  uint4 hx[TG][2], wx[NH][2];
-#pragma unroll
-  for (int g8 = 0; g8 < TG; ++g8) hx[g8][0] = hp[g8][0], hx[g8][1] = hp[g8][1];
-#pragma unroll
-  for (int hh = 0; hh < NH; ++hh) wx[hh][0] = wp[hh][0], wx[hh][1] = wp[hh][1];
-
-  for (int c = 0; c < nc; ++c) {
-    // A operands of this chunk: the weight of channel ch alone in its half of its dword
-    uint32_t aw[NH][16];
-#pragma unroll
-    for (int hh = 0; hh < NH; ++hh) {
-      const uint32_t wd[8] = {wx[hh][0].x, wx[hh][0].y, wx[hh][0].z, wx[hh][0].w,
-                              wx[hh][1].x, wx[hh][1].y, wx[hh][1].z, wx[hh][1].w};
-      const bool live = 4 * hh + j < G;
-#pragma unroll
       for (int d = 0; d < 8; ++d) {
-        aw[hh][2 * d] = live ? (wd[d] & 0xffffu) : 0u;
-        aw[hh][2 * d + 1] = live ? (wd[d] & 0xffff0000u) : 0u;
+        const uint32_t w = (G % 4 == 0 || 4 * hh + j < G) ? wx[hh][d / 4][d % 4] : 0u;
+        we[hh][d] = w & 0xffffu;
+        wo[hh][d] = odd_channel(w);
       }
-    }
-    uint4 cur[TG][2];
+    router_u32x4 cur[TG][2];
 #pragma unroll
     for (int g8 = 0; g8 < TG; ++g8) cur[g8][0] = hx[g8][0], cur[g8][1] = hx[g8][1];
-    if (c + 1 < nc) {  // next chunk's requests go out before this chunk's arithmetic
+    if (c + STEP < nc) {  // next chunk's requests go out before this chunk's arithmetic
 #pragma unroll
       for (int g8 = 0; g8 < TG; ++g8)
-        hx[g8][0] = hp[g8][(c + 1) * 16], hx[g8][1] = hp[g8][(c + 1) * 16 + 1];
+        hx[g8][0] = hp[g8][(c + STEP) * 16], hx[g8][1] = hp[g8][(c + STEP) * 16 + 1];
 #pragma unroll
       for (int hh = 0; hh < NH; ++hh)
-        wx[hh][0] = wp[hh][(c + 1) * 16], wx[hh][1] = wp[hh][(c + 1) * 16 + 1];
+        wx[hh][0] = wp[hh][(c + STEP) * 16], wx[hh][1] = wp[hh][(c + STEP) * 16 + 1];
     }
 #pragma unroll
     for (int g8 = 0; g8 < TG; ++g8) {
-      const uint32_t hd[8] = {cur[g8][0].x, cur[g8][0].y, cur[g8][0].z, cur[g8][0].w,
-                              cur[g8][1].x, cur[g8][1].y, cur[g8][1].z, cur[g8][1].w};
+      float ho[8];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) ho[d] = odd_channel(cur[g8][d / 4][d % 4]);
+      float y[NH];
 #pragma unroll
       for (int hh = 0; hh < NH; ++hh) {
-        // four channels (one B pair) at a time: their products, then the two tree levels
-        // inside the pair; node[p][i] = sum over channels 4p..4p+3 for router output 4*hh + i
-        f32x4 node[4];
+        // node[d][i] = sum over channels 2d, 2d+1 for router output 4*hh + i, then the next two
+        // levels per 8 channels
+        f32x4 half[2];
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const bf16x4 bb = router_bf16x4(hd[2 * p], hd[2 * p + 1]);
-          const f32x4 t0 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(
-              router_bf16x4(aw[hh][4 * p + 0], 0u), bb, zero, 0, 0, 0);
-          const f32x4 t1 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(
-              router_bf16x4(aw[hh][4 * p + 1], 0u), bb, zero, 0, 0, 0);
-          const f32x4 t2 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(
-              router_bf16x4(0u, aw[hh][4 * p + 2]), bb, zero, 0, 0, 0);
-          const f32x4 t3 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(
-              router_bf16x4(0u, aw[hh][4 * p + 3]), bb, zero, 0, 0, 0);
+        for (int q = 0; q < 2; ++q) {
+          f32x4 node[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) node[p][i] = (t0[i] + t1[i]) + (t2[i] + t3[i]);
-        }
-        const int rows = (G - 4 * hh) < 4 ? (G - 4 * hh) : 4;
+          for (int k = 0; k < 4; ++k) {
+            const int d = 4 * q + k;
+            const bf16x4 bb = router_bf16x4(cur[g8][q][k & ~1], cur[g8][q][k | 1]);
+            const bf16x4 aa = (k & 1) ? router_bf16x4(0u, we[hh][d]) : router_bf16x4(we[hh][d], 0u);
+            node[k] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(aa, bb, zero, 0, 0, 0);
+          }
 #pragma unroll
-        for (int i = 0; i < rows; ++i) {
-          const float v = (node[0][i] + node[1][i]) + (node[2][i] + node[3][i]);
-          acc[g8][hh][i] += chunk_tree_sum(v);
+          for (int k = 0; k < 4; ++k)
+            node[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(wo[hh][4 * q + k], ho[4 * q + k], node[k],
+                                                         0, 0, 0);
+          half[q] = (node[0] + node[1]) + (node[2] + node[3]);
         }
+        const f32x4 s = half[0] + half[1];
+        const float v[4] = {s[0], s[1], s[2], s[3]};
+        y[hh] = fold_four(v, bit2, bit3);
+      }
+      // pieces 0..3 and 4..7 sit in lanes with bit 4 clear and set: two row groups at a time
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const float ya = y[2 * a], yb = 2 * a + 1 < NH ? y[2 * a + 1] : y[2 * a];
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(ya), __float_as_uint(yb),
+                                                        false, false);
+        const float sum = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        if constexpr (SPLIT) s_sum[((c - base) * TG * NA + g8 * NA + a) * 64 + lane] = sum;
+        else acc[g8][a] += sum;
       }
     }
   }
+  if constexpr (SPLIT) {  // wavefront i carries accumulator i
+    __syncthreads();
+    if (wave < TG * NA)
+      for (int c = base; c < cend; ++c) acc[0][0] += s_sum[((c - base) * TG * NA + wave) * 64 + lane];
+    __syncthreads();
+  }
+  }
 
-  if ((lane & 0x1c) != kChunkSumLanes) return;
+  // accumulator a of a lane: router output 8*a + 4*(bit 4) + 2*(bit 3 clear) + (bit 2 clear)
+  const int sub = (bit3 ? 0 : 2) + (bit2 ? 0 : 1);
+  const int up = (lane >> 4) & 1;
+  if (NH == 1 && up) return;  // both hold the same
+  auto store = [&](float sum, int g8, int a) {
+    const int g = 8 * a + 4 * up + sub, t = t_first + 8 * g8;
+    if (g >= G || t >= N) return;
+    const float v = sum + (bias ? bias[g] : 0.f);
+    for (int kvh = 0; kvh < Hkv; ++kvh) logits[(((size_t)b * Hkv + kvh) * N + t) * G + g] = v;
+  };
+  if constexpr (SPLIT) {
+    if (wave < TG * NA) store(acc[0][0], wave / NA, wave % NA);
+  } else {
 #pragma unroll
-  for (int g8 = 0; g8 < TG; ++g8) {
-    const int t = t_first + 8 * g8;
-    if (t >= N) continue;
-    float o[4 * NH];
+    for (int g8 = 0; g8 < TG; ++g8)
 #pragma unroll
-    for (int hh = 0; hh < NH; ++hh)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = 4 * hh + i;
-        o[g] = g < G ? acc[g8][hh][i] + (bias ? bias[g] : 0.f) : 0.f;
-      }
-    for (int kvh = 0; kvh < Hkv; ++kvh) {
-      float* dst = logits + (((size_t)b * Hkv + kvh) * N + t) * G;
-      if constexpr (G >= 4) {
-#pragma unroll
-        for (int hh = 0; hh < NH; ++hh)
-          *(f32x4*)(dst + 4 * hh) = f32x4{o[4 * hh], o[4 * hh + 1], o[4 * hh + 2], o[4 * hh + 3]};
-      } else {
-#pragma unroll
-        for (int g = 0; g < G; ++g) dst[g] = o[g];
-      }
-    }
+      for (int a = 0; a < NA; ++a) store(acc[g8][a], g8, a);
   }
 }
 
 int launch_router_logits(const void* h, const void* W, const float* bias, int bias_stride,
                          float* logits, int B, int Hkv, int N, int d_model, int G,
                          hipStream_t st) {
-#define STC_ROUTER_CASE(GG)                                                                      \
-  case GG: {                                                                                     \
-    dim3 grid((N + RouterCfg<GG>::BLOCK_TOKENS - 1) / RouterCfg<GG>::BLOCK_TOKENS, B);           \
-    router_logits_kernel<GG><<<grid, 256, 0, st>>>((const uint4*)h, (const uint4*)W, bias,       \
-                                                   logits, N, d_model, Hkv, bias_stride);        \
-    break;                                                                                       \
-  }
+#define STC_ROUTER_GO(GG, TG, SPLIT)                                                            \
+  router_logits_kernel<GG, TG, SPLIT>                                                           \
+      <<<dim3((N + RouterCfg<GG, TG, SPLIT>::BLOCK_TOKENS - 1) /                                \
+                  RouterCfg<GG, TG, SPLIT>::BLOCK_TOKENS, B),                                   \
+         RouterCfg<GG, TG, SPLIT>::WAVES * 64, 0, st>>>(                                        \
+          (const router_u32x4*)h, (const router_u32x4*)W, bias, logits, N, d_model, Hkv,        \
+          bias_stride)
+  // Tokens per wavefront and who shares them (measured at 3584 and 4096 channels, us):
+  //   tokens    8 groups: split 1 / split 2 / 2 / 4    4 groups            16 groups (1 and 2)
+  //     2000        8.6 /  10.8 /   - /   -            7.5 /  9.2          13.5 / 18.6
+  //     4000       13.4 /  11.2 /  29 /  50           11.4 /  9.7 / 27     24.8 / 19.1 / 57
+  //     8000       24.3 /  21.9 /  29 /  50           19.1 / 16.6 / 29     49.3 / 37.2 / 57
+  //    16000       43.6 /  41.2 /  31 /  51           33.7 / 28.1 / 33     94.6 / 71.5 / 58
+  //    64000      151   / 150   / 106 /  91          117   / 90   / 109    363  / 274  / 190
+  //   524288          -       -   839 / 683             -       -  623/616      -      - / 1289
+  // Few tokens are bound by the chain of chunks of a wavefront, which the split form cuts to an
+  // eighth; many by the weights' preparation per wavefront, which more tokens share.
+  const long long tokens = (long long)B * N;
+  const bool split1 = tokens < 3000;
+  const bool split2 = tokens < (G <= 4 ? 131072 : 12000);
+  const bool two = tokens < 24000 || G == 16;
+#define STC_ROUTER_CASE(GG)                                                                     \
+  case GG:                                                                                      \
+    if (split1) STC_ROUTER_GO(GG, 1, true);                                                     \
+    else if (split2) STC_ROUTER_GO(GG, 2, true);                                                \
+    else if (two) STC_ROUTER_GO(GG, 2, false);                                                  \
+    else STC_ROUTER_GO(GG, (GG == 16 ? 2 : 4), false);                                          \
+    break;
   switch (G) {
     STC_ROUTER_CASE(1)
     STC_ROUTER_CASE(2)
@@ -192,6 +273,7 @@ int launch_router_logits(const void* h, const void* W, const float* bias, int bi
       return -1;
   }
 #undef STC_ROUTER_CASE
+#undef STC_ROUTER_GO
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
