@@ -86,7 +86,7 @@ __device__ __forceinline__ uint32_t block_exscan_once(uint32_t v, uint32_t* lds_
 // Top-k pages of a stream by one workgroup of THREADS threads with the keys held in
 // registers: thread t owns the IPT adjacent pages t*IPT .. (NP <= THREADS * IPT <= 65535).
 // The selected pages are handed to emit(position in the ascending list, page).  Each radix
-// pass is a shared-memory histogram of one key byte, which every wavefront then scans for
+// pass is a shared-memory histogram of one key digit, which every wavefront then scans for
 // itself (digits in descending order) to find the digit that holds the k-th largest key: no
 // broadcast and no second barrier.  The usual case (one pass, then at most 64 candidates
 // ranked directly) crosses five workgroup barriers.
@@ -94,7 +94,11 @@ template <int IPT, int THREADS, class Emit>
 __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP, int k,
                                            Emit emit) {
   constexpr int NW = THREADS / 64;
-  __shared__ __align__(16) int hist[256];
+  // Digit width: 8 bits, 10 from 4096 keys on, where a digit of 8 bits leaves more keys beside
+  // the k-th than are ranked directly, which costs a second pass.
+  constexpr int HB = THREADS * IPT > 2048 ? 10 : 8;
+  constexpr int BINS = 1 << HB, PER = BINS / 64;  // digits per lane of a wavefront's scan
+  __shared__ __align__(16) int hist[BINS];
   __shared__ uint32_t waves[NW];  // per-wavefront sums of the final scan
   __shared__ uint32_t s_min[NW], s_max[NW];
   __shared__ int s_ncand;
@@ -122,7 +126,7 @@ __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP,
 #pragma unroll
     for (int j = 0; j < IPT; ++j) key[j] = i0 + j < NP ? float_key(sc[i0 + j]) : 0u;
   }
-  if (tid < 256) hist[tid] = 0;
+  for (int i = tid; i < BINS; i += THREADS) hist[i] = 0;
   if (tid < 64) s_gt[tid] = 0, s_ge[tid] = 0;
   if (tid == 0) s_ncand = 0;
 
@@ -141,40 +145,45 @@ __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP,
   for (int w = 0; w < NW; ++w) kmin = min(kmin, s_min[w]), kmax = max(kmax, s_max[w]);
   const uint32_t diff = kmin ^ kmax;
   const int top = diff ? 31 - __clz(diff) : 0;  // highest differing bit
-  int shift = max(top - 7, 0);
-  uint32_t decided = shift + 8 < 32 ? ~((1u << (shift + 8)) - 1u) : 0u;  // key bits fixed so far
+  int shift = max(top - (HB - 1), 0);
+  uint32_t decided = shift + HB < 32 ? ~((1u << (shift + HB)) - 1u) : 0u;  // key bits fixed so far
   uint32_t prefix = kmax & decided;
   int remaining = k;  // rank of the k-th largest key among the keys sharing the prefix
   // The last window may overlap bits that are already fixed; keys are filtered on all
   // fixed bits, so the digit found repeats them.  The histogram is zero on entry to every
   // pass.
-  for (;; shift = max(shift - 8, 0)) {
+  for (;; shift = max(shift - HB, 0)) {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       const bool in = (key[j] & decided) == prefix;
-      if (in && i0 + j < NP) atomicAdd(&hist[(key[j] >> shift) & 255u], 1);
+      if (in && i0 + j < NP) atomicAdd(&hist[(key[j] >> shift) & (BINS - 1u)], 1);
     }
     __syncthreads();
     // Every wavefront finds the digit for itself (no broadcast, no second barrier): lane l
-    // looks at digits 255-4l .. 252-4l, a wavefront scan gives the keys with a larger digit.
-    const int4 h4 = *(const int4*)&hist[252 - 4 * lane];
-    const int c4[4] = {h4.w, h4.z, h4.y, h4.x};
-    const int mine4 = c4[0] + c4[1] + c4[2] + c4[3];
-    int above = (int)wave_scan((uint32_t)mine4, OpAdd{}, 0u) - mine4;
+    // looks at PER adjacent digits in descending order, a wavefront scan gives the keys with a
+    // larger digit.
+    int cd[PER], mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; j += 4) {
+      const int4 h4 = *(const int4*)&hist[BINS - 4 - j - PER * lane];
+      cd[j] = h4.w, cd[j + 1] = h4.z, cd[j + 2] = h4.y, cd[j + 3] = h4.x;
+      mine += (h4.w + h4.z) + (h4.y + h4.x);
+    }
+    int above = (int)wave_scan((uint32_t)mine, OpAdd{}, 0u) - mine;
     int f_digit = 0, f_above = 0, f_cnt = 0;
     bool found = false;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool hit = above < remaining && remaining <= above + c4[j];
-      if (hit) f_digit = 255 - 4 * lane - j, f_above = above, f_cnt = c4[j];
+    for (int j = 0; j < PER; ++j) {
+      const bool hit = above < remaining && remaining <= above + cd[j];
+      if (hit) f_digit = BINS - 1 - PER * lane - j, f_above = above, f_cnt = cd[j];
       found |= hit;
-      above += c4[j];
+      above += cd[j];
     }
     const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(found)) - 1);
     const int digit = __builtin_amdgcn_readlane(f_digit, src);
     const int c = __builtin_amdgcn_readlane(f_cnt, src);  // keys that share the new prefix
     remaining -= __builtin_amdgcn_readlane(f_above, src);
-    prefix = (prefix & ~(255u << shift)) | ((uint32_t)digit << shift);
+    prefix = (prefix & ~((BINS - 1u) << shift)) | ((uint32_t)digit << shift);
     decided = ~((1u << shift) - 1u);
     if (shift == 0) break;
     if (c <= 64) {
@@ -216,7 +225,7 @@ __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP,
     }
     // another pass: the histogram is cleared once every wavefront has read it
     __syncthreads();
-    if (tid < 256) hist[tid] = 0;
+    for (int i = tid; i < BINS; i += THREADS) hist[i] = 0;
     __syncthreads();
   }
   // prefix = key of the k-th largest score; `remaining` of the pages equal to it are
