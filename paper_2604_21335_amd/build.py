@@ -11,7 +11,7 @@ BENCH_LIB_PATH = os.path.join(PKG_DIR, "libstc_bench.so")   # benchmark-only hel
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 
 SOURCES = ["stc_api.hip", "bounds.hip", "router.hip", "route_pack.hip", "flush.hip",
-           "score.hip", "select.hip", "attention.hip"]
+           "score.hip", "select.hip", "attention.hip", "step.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
@@ -22,7 +22,8 @@ HIPCC_FLAGS = [
 # matrix-core results are consumed by vector instructions right away, so keep them in
 # ordinary vector registers (no copies out of the accumulation registers)
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-FILE_FLAGS = {"score.hip": _VGPR_MFMA, "attention.hip": _VGPR_MFMA, "router.hip": _VGPR_MFMA}
+FILE_FLAGS = {"score.hip": _VGPR_MFMA, "attention.hip": _VGPR_MFMA, "step.hip": _VGPR_MFMA,
+              "router.hip": _VGPR_MFMA}
 
 
 def _hipcc():

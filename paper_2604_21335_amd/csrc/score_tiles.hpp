@@ -19,20 +19,21 @@ __host__ __device__ constexpr int score_q_lds_bytes() {
   return ((R + 3) / 4) * (D / 8) * 64 * 8;
 }
 
-// Fills the operand table for the R heads at `qs` ([R][D] bf16).  Entry (g, c, lane) is the A
+// Fills the operand table for the first `heads` of R heads at `qs` ([R][D] bf16).  Entry (g, c, lane) is the A
 // operand of lane `lane` for channel c of its chunk and head 4g + lane%4: the query value in
 // the k-slot of the channel's minimum when it is negative, of its maximum otherwise, zeros in
 // the three other slots (the channel pair of a B operand occupies two slots each).  All
 // threads of the workgroup call it; the caller synchronises before the table is read.
 template <int D, int R, int THREADS>
-__device__ __forceinline__ void score_fill_q(const uint16_t* __restrict__ qs, unsigned char* qlds) {
+__device__ __forceinline__ void score_fill_q(const uint16_t* __restrict__ qs, unsigned char* qlds,
+                                             int heads = R) {
   constexpr int CH = D / 8, NG = (R + 3) / 4, PIECES = CH / 8;  // 16-byte pieces per chunk
   // one work item = 8 adjacent channels of one (head group, lane): a single 16-byte load
   for (int it = threadIdx.x; it < NG * PIECES * 64; it += THREADS) {
     const int l = it & 63, piece = (it >> 6) % PIECES, g = it / (64 * PIECES);
     const int head = 4 * g + (l & 3), e = (l >> 2) & 7;
     score_u32x4 v = {0u, 0u, 0u, 0u};
-    if (head < R) v = *(const score_u32x4*)(qs + head * D + e * CH + piece * 8);
+    if (head < heads) v = *(const score_u32x4*)(qs + head * D + e * CH + piece * 8);
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -52,12 +53,13 @@ __device__ __forceinline__ void score_fill_q(const uint16_t* __restrict__ qs, un
 // caches alone.  `prologue` is run by every thread
 // once the first tiles have been requested: it fills the operand table (score_fill_q) and
 // synchronises the workgroup, so that the latency of the query loads hides behind the tiles'.
+// Heads from `heads` on count for nothing.
 template <int D, int R, bool PER_HEAD, int WAVES, int DEPTH = 2, bool STREAM = false,
           class Prologue>
 __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__ base,
                                                  float* __restrict__ out, int NP, int t0, int t1,
                                                  const unsigned char* qlds, int wave, int lane,
-                                                 Prologue prologue) {
+                                                 Prologue prologue, int heads = R) {
   constexpr int CH = D / 8, NJ = CH / 4, NG = (R + 3) / 4, T16 = NJ * 64;
   const int tlast = t1 - 1;
   uint32_t qoff = lane * 8;
@@ -102,7 +104,7 @@ __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__
         const float s = chunk_tree_sum(u[0][i]);
         if (PER_HEAD) {
           if (writer) out[(size_t)(4 * g + i) * NP + page] = s == 0.f ? 0.f : s;
-        } else {
+        } else if (4 * g + i < heads) {
           best = (g == 0 && i == 0) ? s : fmaxf(best, s);
         }
       }

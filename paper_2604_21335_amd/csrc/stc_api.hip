@@ -296,6 +296,11 @@ int decode_step_impl(const stc_shape_t* shape, const void* q, const void* bounds
                ? STC_ERR_LAUNCH
                : STC_OK;
   }
+  if (stc::step_is_one_kernel(*shape, k_pages, tail_pages))
+    return stc::launch_step(*shape, q, bounds, K, vpacked, mask, tok_off, k_pages, K_tail, V_tail,
+                            n_tail, tail_cap, (float*)ws, page_idx, out, st)
+               ? STC_ERR_LAUNCH
+               : STC_OK;
   if (!stc::attention_can_select(*shape, k_pages, tail_pages)) {
     if (stc::launch_select(*shape, q, bounds, k_pages, page_idx, (float*)ws, false, st) ||
         stc::launch_attention(*shape, q, K, vpacked, mask, tok_off,

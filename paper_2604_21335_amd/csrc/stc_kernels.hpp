@@ -63,6 +63,12 @@ int launch_attention(const stc_shape_t& s, const void* q, const void* K, const v
 // their stream from these scores themselves and write the list to sel_list.  Only if
 // attention_can_select().
 bool attention_can_select(const stc_shape_t& s, int k_pages, int tail_pages);
+// The whole step by one workgroup per stream, in one launch.  Only if step_is_one_kernel().
+bool step_is_one_kernel(const stc_shape_t& s, int k_pages, int tail_pages);
+int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const void* K,
+                const void* vpacked, const uint16_t* mask, const uint32_t* tok_off, int k_pages,
+                const void* K_tail, const void* V_tail, int n_tail, int tail_cap, float* score,
+                int32_t* list, float* out, hipStream_t st);
 // Union of the page lists of the query heads of every KV head (ascending, padded with -1) and
 // the heads that selected each page.
 int launch_union_pages(const stc_shape_t& s, const int32_t* page_idx_per_head, int k_pages,
