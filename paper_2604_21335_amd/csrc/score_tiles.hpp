@@ -103,7 +103,8 @@ __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__
       for (int i = 0; i < rows; ++i) {
         const float s = chunk_tree_sum(u[0][i]);
         if (PER_HEAD) {
-          if (writer) out[(size_t)(4 * g + i) * NP + page] = s == 0.f ? 0.f : s;
+          if (writer && 4 * g + i < heads)
+            out[(size_t)(4 * g + i) * NP + page] = s == 0.f ? 0.f : s;
         } else if (4 * g + i < heads) {
           best = (g == 0 && i == 0) ? s : fmaxf(best, s);
         }
