@@ -5,14 +5,17 @@
 
 namespace stc {
 
+typedef __attribute__((ext_vector_type(4))) float logit4;
+
 // The G logits of one token (16-byte loads when G is a multiple of 4: the row is then
-// 16-byte aligned).
-template <int G>
+// 16-byte aligned).  STREAM: with loads that leave the caches alone.
+template <int G, bool STREAM = false>
 __device__ __forceinline__ void load_token_logits(const float* __restrict__ lp, float (&a)[G]) {
   if constexpr ((G & 3) == 0) {
 #pragma unroll
     for (int q = 0; q < G / 4; ++q) {
-      const float4 v = *(const float4*)(lp + 4 * q);
+      const logit4* p = (const logit4*)(lp + 4 * q);
+      const logit4 v = STREAM ? __builtin_nontemporal_load(p) : *p;
       a[4 * q] = v.x, a[4 * q + 1] = v.y, a[4 * q + 2] = v.z, a[4 * q + 3] = v.w;
     }
   } else {
@@ -23,10 +26,10 @@ __device__ __forceinline__ void load_token_logits(const float* __restrict__ lp, 
 
 // Routing mask of one token: bit g set iff group g is among the c largest of its G logits
 // (equal logits: the lower group first).
-template <int G>
+template <int G, bool STREAM>
 __device__ __forceinline__ uint32_t rank_mask_g(const float* __restrict__ lp, int c) {
   float a[G];
-  load_token_logits<G>(lp, a);
+  load_token_logits<G, STREAM>(lp, a);
   uint32_t m = 0;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -41,13 +44,14 @@ __device__ __forceinline__ uint32_t rank_mask_g(const float* __restrict__ lp, in
 
 // The same for a group count known at run time (a power of two up to 16, uniform over the
 // launch: the switch is a scalar branch).
+template <bool STREAM = false>
 __device__ __forceinline__ uint32_t rank_mask(const float* __restrict__ lp, int c, int G) {
   switch (G) {
-    case 1: return rank_mask_g<1>(lp, c);
-    case 2: return rank_mask_g<2>(lp, c);
-    case 4: return rank_mask_g<4>(lp, c);
-    case 8: return rank_mask_g<8>(lp, c);
-    case 16: return rank_mask_g<16>(lp, c);
+    case 1: return rank_mask_g<1, STREAM>(lp, c);
+    case 2: return rank_mask_g<2, STREAM>(lp, c);
+    case 4: return rank_mask_g<4, STREAM>(lp, c);
+    case 8: return rank_mask_g<8, STREAM>(lp, c);
+    case 16: return rank_mask_g<16, STREAM>(lp, c);
     default: return 0u;
   }
 }

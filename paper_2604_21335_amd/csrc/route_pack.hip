@@ -40,24 +40,40 @@ __device__ __forceinline__ int block_exscan_256(int v, int* lds4, int* total) {
   return base + inc - v;
 }
 
-// Step 1: routing mask of every token and the number of kept groups per chunk.
-__global__ __launch_bounds__(kChunk) void route_mask_kernel(
-    int mode, const float* __restrict__ logits, const uint8_t* __restrict__ kcount, int fixed_k,
-    const uint16_t* mask_in, uint16_t* mask, uint32_t* __restrict__ chunk_sum, int N, int G,
-    int nchunks, int Ncap, int mask_in_stride, int share) {
+// Where the routing masks come from: given, or the best groups of each token's logits.
+struct RouteInputs {
+  int mode;
+  const float* logits;
+  const uint8_t* kcount;
+  int fixed_k;
+  const uint16_t* mask_in;  // may be the array that the masks are written to
+  int share;                // streams that read one set of these
+};
+
+// Routing mask of token t (< N) of a stream.
+template <bool STREAM>
+__device__ __forceinline__ uint32_t route_token(const RouteInputs& in, int stream, int t, int N,
+                                                int G) {
+  const size_t tok = (size_t)(stream / in.share) * N + t;  // the inputs are dense
+  if (in.mode == STC_ROUTE_MASK) return in.mask_in[tok] & ((1u << G) - 1u);
+  const int c = in.kcount ? (int)in.kcount[tok] : in.fixed_k;
+  return rank_mask<STREAM>(in.logits + tok * G, min(c, G), G);
+}
+
+// Step 1: routing mask of every token and the number of kept groups per chunk.  STREAM: logits
+// that are read once and do not fit the caches go past them (routing and packing of 64 streams of
+// 32768 tokens, 67 MB of logits: 9 us less, most of it in the packed copy behind, which finds
+// the caches empty).
+template <bool STREAM>
+__global__ __launch_bounds__(kChunk) void route_mask_kernel(const RouteInputs in, uint16_t* mask,
+                                                            uint32_t* __restrict__ chunk_sum,
+                                                            int N, int G, int nchunks, int Ncap) {
   __shared__ int red[4];
   const int stream = blockIdx.y;
-  const int src = stream / share;  // the routing inputs of `share` streams are one set
   const int t = blockIdx.x * kChunk + threadIdx.x;
   uint32_t m = 0;
   if (t < N) {
-    const size_t tok = (size_t)src * N + t;  // dense inputs: logits, kcount
-    if (mode == STC_ROUTE_MASK) {
-      m = mask_in[(size_t)src * mask_in_stride + t] & ((1u << G) - 1u);
-    } else {
-      int c = kcount ? (int)kcount[tok] : fixed_k;
-      m = rank_mask(logits + tok * G, min(c, G), G);
-    }
+    m = route_token<STREAM>(in, stream, t, N, G);
     mask[(size_t)stream * Ncap + t] = (uint16_t)m;
   }
   const int tot = block_sum_256(__popc(m), red);
@@ -415,13 +431,19 @@ __global__ __launch_bounds__(256) void scan_chunks_kernel(uint32_t* chunk_sum, u
 // where it belongs, 256 tokens per workgroup, through the caches.  128 tokens per workgroup
 // 128 us, 32: 132, with the values requested before the masks are known 129, with streaming
 // loads or streaming stores alone 143 and 141.
-// SCAN: chunk_sum holds the chunks' own sums, and every workgroup adds up those in front of its
-// chunk itself (the last one also writes the stream's total); otherwise they have been scanned.
+// What is in front of a workgroup's tokens, by FORM:
+//   kPackSums     chunk_sum holds the chunks' own sums, and every workgroup adds up those in front
+//                 of its chunk itself
+//   kPackScanned  they have been scanned by a launch of its own, which also wrote the totals
+//   kPackRoute    streams of a single chunk (256 tokens): the workgroup routes its tokens and those
+//                 in front of them itself, so that no launch for the masks is needed (64 x 32
+//                 streams of 208 tokens, compaction and bounds included: 129.5 us for 134.5)
+enum { kPackSums, kPackScanned, kPackRoute };
 constexpr int kPackTokens = 64;
 
-template <int D, bool SCAN>
+template <int D, int FORM>
 __global__ __launch_bounds__(kChunk) void pack_kernel(const pack_u32x4* __restrict__ V,
-                                                      const uint16_t* __restrict__ mask,
+                                                      const RouteInputs in, uint16_t* mask,
                                                       const uint32_t* __restrict__ chunk_sum,
                                                       uint32_t* __restrict__ tok_off,
                                                       pack_u32x4* __restrict__ vpacked,
@@ -436,19 +458,28 @@ __global__ __launch_bounds__(kChunk) void pack_kernel(const pack_u32x4* __restri
   const int stream = blockIdx.y;
   const int t0 = blockIdx.x * kPackTokens;
   const int chunk = t0 / kChunk;
-  const uint32_t* cs = chunk_sum + (size_t)stream * nchunks;
   uint32_t* off_s = tok_off + (size_t)stream * (Ncap + 1);
   // thread i looks at token i of the chunk, up to the end of this workgroup's tokens
   const int t = chunk * kChunk + threadIdx.x;
-  uint32_t m = 0;
-  if (t < N && t < t0 + kPackTokens) m = mask[(size_t)stream * Ncap + t];
-  uint32_t before;  // kept groups in front of the chunk
-  if constexpr (SCAN) {
-    uint32_t part = 0;
-    for (int i = threadIdx.x; i < chunk; i += kChunk) part += cs[i];
-    before = (uint32_t)block_sum_256((int)part, red2);
-  } else {
-    before = cs[chunk];
+  uint16_t* mask_t = mask + (size_t)stream * Ncap + t;
+  uint32_t m = 0, before = 0;  // the token's mask; kept groups in front of the chunk
+  if (t < N && t < t0 + kPackTokens) {
+    if constexpr (FORM == kPackRoute) {
+      m = route_token<false>(in, stream, t, N, G);
+      if (t >= t0) *mask_t = (uint16_t)m;
+    } else {
+      m = *mask_t;
+    }
+  }
+  if constexpr (FORM != kPackRoute) {
+    const uint32_t* cs = chunk_sum + (size_t)stream * nchunks;
+    if constexpr (FORM == kPackSums) {
+      uint32_t part = 0;
+      for (int i = threadIdx.x; i < chunk; i += kChunk) part += cs[i];
+      before = (uint32_t)block_sum_256((int)part, red2);
+    } else {
+      before = cs[chunk];
+    }
   }
   int upto;
   const int ex = block_exscan_256(__popc(m), red, &upto);
@@ -460,7 +491,7 @@ __global__ __launch_bounds__(kChunk) void pack_kernel(const pack_u32x4* __restri
     s_off[rel] = off;
     s_mask[rel] = m;  // 0 behind the last token
   }
-  if (threadIdx.x == 0 && SCAN && t0 + kPackTokens >= N) {
+  if (threadIdx.x == 0 && FORM != kPackScanned && t0 + kPackTokens >= N) {
     off_s[N] = end;
     if (dev_status && (long long)end > cap) *dev_status = 1;
   }
@@ -552,6 +583,8 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
   const RouteWs lay = route_ws_layout(s);
   uint32_t* chunk = (uint32_t*)((char*)ws + lay.chunk_sum);
   dim3 grid(nchunks, streams);
+  const RouteInputs in{mode, logits, kcount, fixed_k, mask_in, share};
+  bool in_pack = false;  // the packed copy routes the tokens itself
   if (mode == STC_ROUTE_GLOBAL) {
     uint32_t* chunk_eq = (uint32_t*)((char*)ws + lay.chunk_eq);
     uint32_t* hist = (uint32_t*)((char*)ws + lay.hist);
@@ -612,8 +645,16 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
 #undef STC_GLOBAL_MASK
     }
   } else {
-    route_mask_kernel<<<grid, kChunk, 0, st>>>(mode, logits, kcount, fixed_k, mask_in, mask, chunk,
-                                               s.N, s.G, nchunks, Ncap, s.N, share);
+    in_pack = nchunks == 1;
+    if (!in_pack) {
+      // logits that several streams read come from the caches after the first
+      const bool stream_loads = mode == STC_ROUTE_TOPK && share == 1 &&
+                                (long long)streams * s.N * s.G * 4 >= (32ll << 20);
+      if (stream_loads)
+        route_mask_kernel<true><<<grid, kChunk, 0, st>>>(in, mask, chunk, s.N, s.G, nchunks, Ncap);
+      else
+        route_mask_kernel<false><<<grid, kChunk, 0, st>>>(in, mask, chunk, s.N, s.G, nchunks, Ncap);
+    }
   }
   if (hipGetLastError() != hipSuccess) return -1;
   // Up to this many chunks per stream (524288 tokens) a workgroup of the packed copy adds up
@@ -626,17 +667,21 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
     if (hipGetLastError() != hipSuccess) return -1;
   }
   dim3 pgrid((s.N + kPackTokens - 1) / kPackTokens, streams);
-#define STC_PACK(DD, SCAN)                                                                   \
-  pack_kernel<DD, SCAN><<<pgrid, kChunk, 0, st>>>((const pack_u32x4*)V, mask, chunk, tok_off, \
-                                                 (pack_u32x4*)vpacked, dev_status, s.N, s.G, \
-                                                 nchunks, (long long)s.v_cap_groups, Ncap)
+#define STC_PACK(DD, FORM)                                                                    \
+  pack_kernel<DD, FORM><<<pgrid, kChunk, 0, st>>>((const pack_u32x4*)V, in, mask, chunk,      \
+                                                  tok_off, (pack_u32x4*)vpacked, dev_status,  \
+                                                  s.N, s.G, nchunks,                          \
+                                                  (long long)s.v_cap_groups, Ncap)
+#define STC_PACK_FORMS(DD)                                                                    \
+  if (in_pack) STC_PACK(DD, kPackRoute);                                                      \
+  else if (fold) STC_PACK(DD, kPackSums);                                                     \
+  else STC_PACK(DD, kPackScanned);
   if (s.D == 128) {
-    if (fold) STC_PACK(128, true);
-    else STC_PACK(128, false);
+    STC_PACK_FORMS(128)
   } else {
-    if (fold) STC_PACK(64, true);
-    else STC_PACK(64, false);
+    STC_PACK_FORMS(64)
   }
+#undef STC_PACK_FORMS
 #undef STC_PACK
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
