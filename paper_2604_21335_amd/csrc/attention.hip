@@ -20,9 +20,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams 
 }
 
 // Merge the split partials of one query head in ascending split order.  Each
-// thread owns one channel; partials are fetched 8 splits at a time (one round of
-// loads for up to 8 splits) and folded in with a running maximum.
-template <int D>
+// thread owns one channel; partials are fetched BATCH splits at a time (one round of
+// loads for up to BATCH splits) and folded in with a running maximum.  Bound by latency: a launch
+// and a round trip to memory per batch (28 layers of 16 splits: 606 -> 603 us per step with
+// batches of 16 instead of 8).
+template <int D, int BATCH>
 __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict__ partial,
                                                          float* __restrict__ out, int splits) {
   constexpr int ST = partial_stride(D);
@@ -30,20 +32,20 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
   const int c = threadIdx.x;
   const float* pr = partial + (size_t)head * splits * ST;
   float m = kNegBig, l = 0.f, a = 0.f;
-  for (int s0 = 0; s0 < splits; s0 += 8) {
-    float ms[8], ls[8], as[8];
+  for (int s0 = 0; s0 < splits; s0 += BATCH) {
+    float ms[BATCH], ls[BATCH], as[BATCH];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < BATCH; ++i) {
       const float* ps = pr + min(s0 + i, splits - 1) * ST;
       ms[i] = ps[0], ls[i] = ps[1], as[i] = ps[2 + c];
     }
     float mb = m;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) mb = fmaxf(mb, s0 + i < splits ? ms[i] : kNegBig);
+    for (int i = 0; i < BATCH; ++i) mb = fmaxf(mb, s0 + i < splits ? ms[i] : kNegBig);
     const float r = __builtin_amdgcn_exp2f(m - mb);
     l *= r, a *= r, m = mb;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < BATCH; ++i) {
       const float w = s0 + i < splits ? __builtin_amdgcn_exp2f(ms[i] - mb) : 0.f;
       l = fmaf(w, ls[i], l);
       a = fmaf(w, as[i], a);
@@ -199,9 +201,10 @@ static AttnParams attn_params(const stc_shape_t& s, const stc_shape_t& s0, const
 // 23.2 us; 2048 streams of 13 pages, 172 MB: 30.1 against 32.7; 64 of 128 pages, 50 MB: 16.2
 // against 17.1).  Below 16 MiB of keys the gain is within 1 % where the pages come from memory
 // (28 layers of 4 of 256 pages, 6 MB each: 612 against 618 per step), and up to 5 % are
-// lost where they still lie in the last-level cache.
-static bool streaming_loads(const stc_shape_t& s, int pages) {
-  return (long long)s.B * s.Hkv * pages * kPage * s.D * 2 >= (16ll << 20);
+// lost where they still lie in the last-level cache.  Pages that several query heads of a KV head
+// select (kv_div > 1) count once: they come from the caches after the first.
+static bool streaming_loads(const stc_shape_t& s, int pages, int kv_div) {
+  return (long long)s.B * s.Hkv * pages * kPage * s.D * 2 >= (16ll << 20) * kv_div;
 }
 
 int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const void* vpacked,
@@ -225,33 +228,39 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
     a.p.nx = kXcds;
     a.grid = dim3(plan.splits * streams, 1);
   }
-  const bool stream_loads = streaming_loads(s, k_pages + tail_pages);
+  const bool stream_loads = streaming_loads(s, k_pages + tail_pages, s.Hkv / s0.Hkv);
   const bool tail = tail_pages > 0, select = sel_score != nullptr;
   const int rc = s.D == 128 ? attn_dispatch<128>(a, plan, tail, select, stream_loads)
                             : attn_dispatch<64>(a, plan, tail, select, stream_loads);
   if (rc) return -1;
   if (plan.splits > 1) {
-    if (s.D == 128)
-      attn_combine_kernel<128><<<s.B * s.Hq, 128, 0, st>>>(a.p.partial, out, plan.splits);
-    else
-      attn_combine_kernel<64><<<s.B * s.Hq, 64, 0, st>>>(a.p.partial, out, plan.splits);
+#define STC_COMBINE(DD, BATCH) \
+  attn_combine_kernel<DD, BATCH><<<s.B * s.Hq, DD, 0, st>>>(a.p.partial, out, plan.splits)
+    if (s.D == 128) {
+      if (plan.splits <= 8) STC_COMBINE(128, 8);
+      else STC_COMBINE(128, 16);
+    } else {
+      if (plan.splits <= 8) STC_COMBINE(64, 8);
+      else STC_COMBINE(64, 16);
+    }
+#undef STC_COMBINE
     if (hipGetLastError() != hipSuccess) return -1;
   }
   return 0;
 }
 
 // One workgroup per stream does the whole step where the attention has no splits anyway, all
-// workgroups are resident at once, and scoring a stream in one workgroup costs less than the
-// launches it saves: streams of few pages, or enough streams that the chip is full either way
-// (score_can_select; more than 4 heads per KV head take twice as long per page).  Step in us,
-// one launch / several: 8 streams of 64 pages 8.0 / 9.5; 32 of 125 pages, 16 kept 10.1 / 11.1;
-// 256 of 256 pages, 64 kept 29.4 / 30.9; 256 of 1024 pages with 7 heads, 96 kept 54.2 / 56.2; D = 64,
-// 256 of 256 pages, 32 kept 13.6 / 16.2.  Not: 8 streams of 500 pages 12.6 / 11.0; 64 of 250
-// pages with 7 heads 13.7 / 13.3; 512 of 250 pages at D = 128 (two rounds) 31.8 / 27.3.
+// workgroups are resident at once, and scoring a stream in one workgroup costs no more than the
+// launches it saves: streams of few pages (more than 4 heads per KV head take twice as long per
+// page), or enough streams that the chip is full either way.  Step in us, one launch / several:
+// 8 streams of 64 pages 8.0 / 9.5; 32 of 125 pages, 16 kept 10.1 / 11.1; 256 of 256 pages, 64 kept
+// 29.4 / 30.9; D = 64, 256 of 256 pages, 32 kept 13.6 / 16.2; 256 of 1024 pages with 7 heads, 96
+// kept 54.2 / 54.  Not: 8 streams of 500 pages 12.6 / 11.0; 64 of 250 pages with 7 heads 13.7 /
+// 13.3; 512 of 250 pages at D = 128 (two rounds) 31.8 / 27.3.
 bool step_is_one_kernel(const stc_shape_t& s, int k_pages, int tail_pages) {
-  const int NP = (s.N + kPage - 1) / kPage, streams = s.B * s.Hkv;
-  if (NP > kStepKeys || streams > resident_streams(s) || !score_can_select(s, k_pages)) return false;
-  if (s.Hq / s.Hkv > 4 && NP > 192 && streams < 192) return false;
+  const int NP = (s.N + kPage - 1) / kPage, streams = s.B * s.Hkv, R = s.Hq / s.Hkv;
+  if (k_pages >= NP || R > 8 || streams > resident_streams(s)) return false;
+  if (!(NP <= (R <= 4 ? 256 : 192) || (streams >= 192 && NP <= kStepKeys))) return false;
   return attention_plan(s, k_pages + tail_pages).splits == 1;
 }
 
@@ -265,7 +274,7 @@ int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const v
       attn_params(s, s, plan, q, K, vpacked, mask, tok_off, nullptr, k_pages, K_tail, V_tail, n_tail,
                   tail_cap, nullptr, nullptr, list, out, nullptr);
   return launch_step_kernel(p, s.D, s.B * s.Hkv, bounds, bounds_tiles(token_cap(s)), score,
-                            tail_pages > 0, streaming_loads(s, k_pages + tail_pages), st);
+                            tail_pages > 0, streaming_loads(s, k_pages + tail_pages, 1), st);
 }
 
 // New token of every stream -> row n_tail of the stream's uncompressed tail (K and V).

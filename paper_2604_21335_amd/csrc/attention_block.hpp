@@ -125,7 +125,7 @@ struct AttnParams {
 
 // Keys that the selection inside a step kernel holds (pages per stream at most), and the bounds
 // tiles that a wavefront of it has in flight.
-constexpr int kStepKeys = 2048;
+constexpr int kStepKeys = 1024;
 constexpr int kStepTilesAhead = 2;
 
 // One launch for a whole step (step.hip): one workgroup of 8 wavefronts per stream, no splits.
