@@ -61,9 +61,8 @@ __device__ __forceinline__ uint32_t route_token(const RouteInputs& in, int strea
 }
 
 // Step 1: routing mask of every token and the number of kept groups per chunk.  STREAM: logits
-// that are read once and do not fit the caches go past them (routing and packing of 64 streams of
-// 32768 tokens, 67 MB of logits: 9 us less, most of it in the packed copy behind, which finds
-// the caches empty).
+// that are read once and do not fit the caches go past them (64 streams of 32768 tokens, 67 MB of
+// logits: 9 us less, this launch and the packed copy behind it together).
 template <bool STREAM>
 __global__ __launch_bounds__(kChunk) void route_mask_kernel(const RouteInputs in, uint16_t* mask,
                                                             uint32_t* __restrict__ chunk_sum,
@@ -290,8 +289,8 @@ __global__ __launch_bounds__(kChunk) void global_mask_kernel(
   if (threadIdx.x == 0) chunk_sum[(size_t)stream * nchunks + blockIdx.x] = (uint32_t)tot;
 }
 
-// The whole selection of one set of logits, masks and chunk sums included, by one workgroup with
-// the keys in registers: thread i owns the KPT / G adjacent tokens from i * KPT / G on.  Same
+// The whole selection of one set of logits, masks and chunk sums of every gridDim.y-th stream of
+// the set included, by one workgroup with the keys in registers: thread i owns the KPT / G adjacent tokens from i * KPT / G on.  Same
 // digits and same order among equal keys as the kernels above.  Bound by latency (histograms
 // in LDS, three block scans).  Routing and packing of 8 x 32 streams of 4096 tokens with one set of
 // 32768 logits per batch element: 26 us less than with the nine launches above, all of which
@@ -306,6 +305,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   __shared__ uint32_t hist[kGlobalBins];
   __shared__ uint32_t waves[kGlobalThreads / 64];
   __shared__ uint32_t s_pick[3];  // digit, rank inside it, keys that have it
+  __shared__ uint32_t s_count;
   __shared__ __align__(4) uint16_t s_mask[kSmallTokens];
   __shared__ uint32_t s_chunk[kSmallTokens / kChunk];
   const int tid = threadIdx.x;
@@ -321,8 +321,88 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   }
   for (int i = tid; i < kSmallTokens / kChunk; i += kGlobalThreads) s_chunk[i] = 0u;
   uint32_t prefix = 0u, decided = 0u, remaining = budget;
-  bool take_all = false;
+  bool take_all = false, found = false;
+  // Bins of equal width between the smallest and the largest logit spread the keys over the
+  // histogram (a digit of the key's bits puts logits that share sign and exponent into a few
+  // bins, whose atomics then wait for each other).  The bin is monotone in the logit.
+  float lo = 0.f, scale = 0.f;
+  uint32_t bin_of_kth = 0u;
+  auto bin = [&](uint32_t k) -> uint32_t {
+    const float f = __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
+    return min((uint32_t)((f - lo) * scale), (uint32_t)(kGlobalBins - 1));
+  };
   if (budget > 0) {
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+    for (int i = 0; i < TPT; ++i)
+#pragma unroll
+      for (int g = 0; g < G; ++g) kmin = min(kmin, key[i][g]), kmax = max(kmax, key[i][g]);
+    for (int d = 32; d >= 1; d >>= 1) {
+      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
+      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
+    }
+    if ((tid & 63) == 0) hist[tid >> 6] = kmin, hist[64 + (tid >> 6)] = kmax;
+    __syncthreads();
+    for (int w = 0; w < kGlobalThreads / 64; ++w)
+      kmin = min(kmin, hist[w]), kmax = max(kmax, hist[64 + w]);
+    __syncthreads();
+    lo = __uint_as_float((kmin & 0x80000000u) ? kmin & 0x7fffffffu : ~kmin);
+    const float hi = __uint_as_float((kmax & 0x80000000u) ? kmax & 0x7fffffffu : ~kmax);
+    scale = (float)(kGlobalBins - 1) / (hi - lo);
+    // one value everywhere, or a range that float cannot divide: every key is in bin 0
+    if (!(hi > lo) || !(hi - lo < 3.0e38f) || !(scale < 3.0e38f)) lo = 0.f, scale = 0.f;
+  }
+  if (budget > 0 && scale > 0.f) {
+#pragma unroll
+    for (int j = 0; j < kGlobalBins / kGlobalThreads; ++j) hist[j * kGlobalThreads + tid] = 0u;
+    if (tid == 0) s_count = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TPT; ++i)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (t0 + i < N) atomicAdd(&hist[bin(key[i][g])], 1u);
+    __syncthreads();
+    uint32_t c[4], own = 0, tot;  // descending bins, as below
+#pragma unroll
+    for (int j = 0; j < 4; ++j) own += c[j] = hist[kGlobalBins - 1 - (4 * tid + j)];
+    uint32_t above = block_exscan_1024(own, waves, &tot);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (above < remaining && remaining <= above + c[j]) {
+        s_pick[0] = (uint32_t)(kGlobalBins - 1 - (4 * tid + j));
+        s_pick[1] = remaining - above;
+        s_pick[2] = c[j];
+      }
+      above += c[j];
+    }
+    __syncthreads();
+    bin_of_kth = s_pick[0];
+    remaining = s_pick[1];
+    const uint32_t cnt = s_pick[2];
+    if (cnt <= (uint32_t)kGlobalThreads) {  // list the bin's keys and rank them, one per thread
+#pragma unroll
+      for (int i = 0; i < TPT; ++i)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          if (t0 + i < N && bin(key[i][g]) == bin_of_kth)
+            hist[atomicAdd(&s_count, 1u)] = key[i][g];
+      __syncthreads();
+      if (tid < (int)cnt) {
+        const uint32_t mine = hist[tid];
+        uint32_t gt = 0, ge = 0;
+        for (uint32_t j = 0; j < cnt; ++j) gt += hist[j] > mine, ge += hist[j] >= mine;
+        if (gt < remaining && remaining <= ge)  // equal keys agree
+          s_pick[0] = mine, s_pick[1] = remaining - gt, s_pick[2] = ge - gt;
+      }
+      __syncthreads();
+      prefix = s_pick[0];
+      remaining = s_pick[1];
+      take_all = s_pick[1] == s_pick[2];
+      found = true;
+    }
+  }
+  if (budget > 0 && !found) {  // digit by digit, within the bin
     for (int pass = 0; pass < 3; ++pass) {
       const int shift = global_shift(pass);
       const uint32_t bins = global_bins(pass);
@@ -333,7 +413,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
       for (int i = 0; i < TPT; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          if (t0 + i < N && (key[i][g] & decided) == prefix)
+          if (t0 + i < N && (key[i][g] & decided) == prefix && bin(key[i][g]) == bin_of_kth)
             atomicAdd(&hist[(key[i][g] >> shift) & (bins - 1)], 1u);
       __syncthreads();
       // thread t owns the 4 adjacent digits 4095-4t .. 4092-4t (bins past `bins` are empty)
@@ -384,7 +464,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   }
   if (kept) atomicAdd(&s_chunk[t0 / kChunk], (uint32_t)kept);  // TPT divides the chunk
   __syncthreads();
-  for (int r = 0; r < share; ++r) {
+  for (int r = blockIdx.y; r < share; r += gridDim.y) {
     const size_t stream = (size_t)blockIdx.x * share + r;
     uint16_t* dst = mask + stream * Ncap;
     if ((Ncap & 1) == 0) {  // two masks at a time
@@ -594,9 +674,12 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
     const int sets = streams / share;
     // one workgroup holds the keys of a set (16, 32 or 64 per thread) and its masks
     if (n <= 64u * kGlobalThreads && s.N <= kSmallTokens) {
+      // the streams of a set are shared out among workgroups that each repeat the selection, as
+      // long as there are CUs for them: one CU takes long to write many streams' masks
+      const int parts = max(1, min(share, 256 / sets));
 #define STC_GLOBAL_SMALL(GG, KPT)                                                             \
-  global_small_kernel<GG, KPT><<<sets, kGlobalThreads, 0, st>>>(logits, mask, chunk, s.N,     \
-                                                                nchunks, Ncap, budget, share)
+  global_small_kernel<GG, KPT><<<dim3(sets, parts), kGlobalThreads, 0, st>>>(                 \
+      logits, mask, chunk, s.N, nchunks, Ncap, budget, share)
 #define STC_GLOBAL_SMALL_CASE(GG)                                                             \
   case GG:                                                                                    \
     if (n <= 16u * kGlobalThreads) STC_GLOBAL_SMALL(GG, 16);                                  \
