@@ -196,15 +196,20 @@ static AttnParams attn_params(const stc_shape_t& s, const stc_shape_t& s0, const
                     s.Hkv / s0.Hkv, page_heads, token_cap(s), sel_score, sel_list, plan.pairs, 0};
 }
 
-// K rows and value runs are read once per step.  Launches of many pages read them with
-// streaming loads, which leave the caches alone (256 streams of 64 pages, 104 MB: 20.9 against
-// 23.2 us; 2048 streams of 13 pages, 172 MB: 30.1 against 32.7; 64 of 128 pages, 50 MB: 16.2
-// against 17.1).  Below 16 MiB of keys the gain is within 1 % where the pages come from memory
-// (28 layers of 4 of 256 pages, 6 MB each: 612 against 618 per step), and up to 5 % are
-// lost where they still lie in the last-level cache.  Pages that several query heads of a KV head
-// select (kv_div > 1) count once: they come from the caches after the first.
-static bool streaming_loads(const stc_shape_t& s, int pages, int kv_div) {
-  return (long long)s.B * s.Hkv * pages * kPage * s.D * 2 >= (16ll << 20) * kv_div;
+// K rows and value runs are read once per step.  Where the keys and bounds of a step are a good
+// part of what the last-level cache holds (256 MB), they are read with streaming loads, which leave
+// the caches alone (256 streams of 64 pages, 104 MB of keys and values: 20.9 against 23.2 us;
+// 2048 streams of 13 pages, 172 MB: 30.1 against 32.7; 64 of 128 pages, 50 MB, beside 67 MB of
+// bounds: 16.2 against 17.1).  Smaller steps may find them in that cache, and there streaming
+// loads cost 5 % (128 streams of 40 pages, 21 MB of keys: 21.1 us per step against 19.8).
+// Pages that several query heads of a KV head select (kv_div > 1) count once: they come from the
+// caches after the first.
+static bool streaming_loads(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
+  const int NP = (s.N + kPage - 1) / kPage;
+  const long long streams = (long long)s.B * s.Hkv / kv_div;
+  const long long keys = streams * (k_pages + tail_pages) * kPage * s.D * 2;
+  const long long bounds = k_pages < NP ? streams * NP * s.D * 4 : 0;
+  return keys + bounds >= (80ll << 20);
 }
 
 int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const void* vpacked,
@@ -228,7 +233,7 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
     a.p.nx = kXcds;
     a.grid = dim3(plan.splits * streams, 1);
   }
-  const bool stream_loads = streaming_loads(s, k_pages + tail_pages, s.Hkv / s0.Hkv);
+  const bool stream_loads = streaming_loads(s, k_pages, tail_pages, s.Hkv / s0.Hkv);
   const bool tail = tail_pages > 0, select = sel_score != nullptr;
   const int rc = s.D == 128 ? attn_dispatch<128>(a, plan, tail, select, stream_loads)
                             : attn_dispatch<64>(a, plan, tail, select, stream_loads);
@@ -274,7 +279,7 @@ int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const v
       attn_params(s, s, plan, q, K, vpacked, mask, tok_off, nullptr, k_pages, K_tail, V_tail, n_tail,
                   tail_cap, nullptr, nullptr, list, out, nullptr);
   return launch_step_kernel(p, s.D, s.B * s.Hkv, bounds, bounds_tiles(token_cap(s)), score,
-                            tail_pages > 0, streaming_loads(s, k_pages + tail_pages, 1), st);
+                            tail_pages > 0, streaming_loads(s, k_pages, tail_pages, 1), st);
 }
 
 // New token of every stream -> row n_tail of the stream's uncompressed tail (K and V).

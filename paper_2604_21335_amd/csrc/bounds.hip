@@ -33,8 +33,9 @@ constexpr int kBoundsWavePages = 2;  // adjacent pages per wavefront, all reques
 // the lanes l + LPR*i hold the same channels of different rows.  Minima and maxima are taken
 // on packed 16-bit integers, first over a lane's own rows, then across lanes by swapping halves
 // of register pairs, which leaves every lane with the minimum and maximum of two channels.
-// Bound by memory (K is read once, 1/8 of it written).  K is larger than the caches wherever
-// the time matters, so it is read with streaming loads that leave them alone.  Measured on 64
+// Bound by memory (K is read once, 1/8 of it written).  K is read with streaming loads, which
+// leave the caches alone, also where it was written just before (2048 streams of 208 tokens,
+// 122 MB, behind their compaction: 23.5 us, 30.3 with ordinary loads).  Measured on 64
 // streams of 32768 tokens (604 MB): 95.8 us (6.3 TB/s) against 106.5 with ordinary loads, 113
 // with 4 pages per wavefront, 124-137 with wavefronts that walk a run of pages, and 131 for
 // the form before, in which a thread walked the 16 rows of a page four loads at a time (a request

@@ -71,14 +71,13 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const u32x4* t4 = (const u32x4*)bounds;
   const uint16_t* q16 = (const uint16_t*)q;
   // Query operands in shared memory, one tile requested at a time per wavefront (measured: two
-  // requested ahead is slower at every grid).  Bounds of 64 MiB and more are read with
-  // streaming loads by about 1024 workgroups (12.4 us at 64 streams of 2048 pages, 67 MB, four
-  // tiles per wavefront; 13.2 with 2048 workgroups, 13.9 with ordinary loads and either).
-  // Smaller ones may still lie in the last-level cache and are faster with ordinary loads
-  // and as many workgroups as there are tiles for, up to 2048 (4 streams of 8192 pages,
-  // 17 MB: 5.6 us against 6.1 with streaming loads, 6.5 with 256 workgroups).
+  // requested ahead is slower at every grid), about 1024 workgroups.  Bounds of 64 MiB and more are
+  // read with streaming loads (64 streams of 2048 pages, 67 MB: 12.4 us; 13.2 with 2048
+  // workgroups, 13.9 with ordinary loads).  Smaller ones may still lie in the last-level cache,
+  // where ordinary loads are faster (4 streams of 8192 pages, 17 MB: 5.4 us against 6.1; with
+  // 2048 workgroups 256 streams of 256 pages take 7.3 us instead of 6.5).
   const bool stream_loads = (long long)streams * ntiles * T16 * 16 >= (64ll << 20);
-  const int want = max(1, (stream_loads ? 1024 : 2048) / streams);
+  const int want = max(1, 1024 / streams);
   int tp = (ntiles + want - 1) / want;
   tp = (tp + WV - 1) / WV * WV;
   const dim3 grid((ntiles + tp - 1) / tp, streams);
