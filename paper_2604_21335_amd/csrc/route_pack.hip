@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kChunk) void global_mask_kernel(
 }
 
 // The whole selection of one set of logits, masks and chunk sums of every gridDim.y-th stream of
-// the set included, by one workgroup with the keys in registers: thread i owns the KPT / G adjacent tokens from i * KPT / G on.  Same
+// the set included, by one workgroup with the keys in registers: thread i owns the tokens i, i + 1024, ...  Same
 // digits and same order among equal keys as the kernels above.  Bound by latency (histograms
 // in LDS, three block scans).  Routing and packing of 8 x 32 streams of 4096 tokens with one set of
 // 32768 logits per batch element: 26 us less than with the nine launches above, all of which
@@ -301,7 +301,7 @@ template <int G, int KPT>
 __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     const float* __restrict__ logits, uint16_t* __restrict__ mask,
     uint32_t* __restrict__ chunk_sum, int N, int nchunks, int Ncap, uint32_t budget, int share) {
-  constexpr int TPT = KPT / G;  // tokens per thread
+  constexpr int TPT = KPT / G;  // tokens per thread: tid, tid + 1024, ...
   __shared__ uint32_t hist[kGlobalBins];
   __shared__ uint32_t waves[kGlobalThreads / 64];
   __shared__ uint32_t s_pick[3];  // digit, rank inside it, keys that have it
@@ -309,13 +309,13 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   __shared__ __align__(4) uint16_t s_mask[kSmallTokens];
   __shared__ uint32_t s_chunk[kSmallTokens / kChunk];
   const int tid = threadIdx.x;
-  const int t0 = tid * TPT;
+  auto token = [&](int i) { return i * kGlobalThreads + tid; };
   const float* a = logits + (size_t)blockIdx.x * N * G;
   uint32_t key[TPT][G];
 #pragma unroll
   for (int i = 0; i < TPT; ++i) {
     float lg[G];
-    load_token_logits<G>(a + (size_t)min(t0 + i, N - 1) * G, lg);
+    load_token_logits<G>(a + (size_t)min(token(i), N - 1) * G, lg);
 #pragma unroll
     for (int g = 0; g < G; ++g) key[i][g] = logit_key(lg[g]);
   }
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     for (int i = 0; i < TPT; ++i)
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        if (t0 + i < N) atomicAdd(&hist[bin(key[i][g])], 1u);
+        if (token(i) < N) atomicAdd(&hist[bin(key[i][g])], 1u);
     __syncthreads();
     uint32_t c[4], own = 0, tot;  // descending bins, as below
 #pragma unroll
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
       for (int i = 0; i < TPT; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          if (t0 + i < N && bin(key[i][g]) == bin_of_kth)
+          if (token(i) < N && bin(key[i][g]) == bin_of_kth)
             hist[atomicAdd(&s_count, 1u)] = key[i][g];
       __syncthreads();
       if (tid < (int)cnt) {
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
       for (int i = 0; i < TPT; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          if (t0 + i < N && (key[i][g] & decided) == prefix && bin(key[i][g]) == bin_of_kth)
+          if (token(i) < N && (key[i][g] & decided) == prefix && bin(key[i][g]) == bin_of_kth)
             atomicAdd(&hist[(key[i][g] >> shift) & (bins - 1)], 1u);
       __syncthreads();
       // thread t owns the 4 adjacent digits 4095-4t .. 4092-4t (bins past `bins` are empty)
@@ -438,31 +438,33 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
       take_all = s_pick[1] == s_pick[2];
     }
   }
-  uint32_t e = 0;  // equal keys in front of this thread's
-  if (budget > 0 && !take_all) {
-    uint32_t eq = 0, tot;
-#pragma unroll
-    for (int i = 0; i < TPT; ++i)
-#pragma unroll
-      for (int g = 0; g < G; ++g) eq += t0 + i < N && key[i][g] == prefix;
-    e = block_exscan_1024(eq, waves, &tot);
-  }
-  __syncthreads();  // (no pass: the chunk counters are cleared)
-  int kept = 0;
+  if (budget == 0 || take_all) __syncthreads();  // (no scan below: the chunk counters are cleared)
+  uint32_t before = 0;  // equal keys of tokens in front of the current 1024
 #pragma unroll
   for (int i = 0; i < TPT; ++i) {
-    uint32_t m = 0;
-    if (budget > 0 && t0 + i < N) {
+    const int t = token(i);
+    uint32_t m = 0, e = 0;
+    if (budget > 0) {
+      if (!take_all) {  // equal keys are taken in token order
+        uint32_t eq = 0, tot;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        if (key[i][g] > prefix) m |= 1u << g;
-        else if (key[i][g] == prefix && (take_all || e++ < remaining)) m |= 1u << g;
+        for (int g = 0; g < G; ++g) eq += t < N && key[i][g] == prefix;
+        e = before + block_exscan_1024(eq, waves, &tot);
+        before += tot;
       }
-      kept += __popc(m);
+      if (t < N) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          if (key[i][g] > prefix) m |= 1u << g;
+          else if (key[i][g] == prefix && (take_all || e++ < remaining)) m |= 1u << g;
+        }
+      }
     }
-    if (t0 + i < N) s_mask[t0 + i] = (uint16_t)m;
+    if (t < N) s_mask[t] = (uint16_t)m;
+    int kept = __popc(m);  // the 64 tokens of a wavefront lie in one chunk
+    for (int d = 32; d >= 1; d >>= 1) kept += __shfl_xor(kept, d);
+    if ((tid & 63) == 0 && kept) atomicAdd(&s_chunk[t / kChunk], (uint32_t)kept);
   }
-  if (kept) atomicAdd(&s_chunk[t0 / kChunk], (uint32_t)kept);  // TPT divides the chunk
   __syncthreads();
   for (int r = blockIdx.y; r < share; r += gridDim.y) {
     const size_t stream = (size_t)blockIdx.x * share + r;
