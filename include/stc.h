@@ -218,8 +218,9 @@ int stc_decode_attention(const stc_shape_t *shape, const void *q, const void *K,
  * One decode step of the compressed cache: the page selection of stc_select_pages (Quest
  * bound scores, top-k_pages per stream; Sec. 3.4) followed by the attention of
  * stc_decode_attention over the selected pages (Sec. 3.3), with the same results bit for
- * bit as the two calls in a row.  The attention workgroups select their stream's pages from
- * the page scores themselves, which saves the launch that orders the scores.
+ * bit as the two calls in a row.  Which launches do it depends on the shape: one workgroup per
+ * stream does the whole step, or the attention workgroups select their stream's pages from the
+ * page scores themselves, or the selection is a launch of its own.
  *   q, bounds, K, vpacked, mask, tok_off, k_pages, out: as in the two calls
  *   page_idx [B, Hkv, k_pages] int32, out: the selected pages, ascending (required)
  *   ws       stc_workspace_bytes(shape, STC_WS_STEP, k_pages) bytes

@@ -79,3 +79,24 @@ def test_global_budget_at_the_limits_of_its_one_workgroup_form(N, G, room, share
                 assert np.array_equal(PT.host_u16(c.mask)[b, h, :N], m), (b, h, gk)
                 assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[b, h, :N + 1],
                                       O.token_offsets(m, G))
+
+
+@pytest.mark.parametrize("N", [524288, 524289, 524289 + 700])
+def test_packed_copy_on_both_sides_of_the_scan_launch(N):
+    """Up to 2048 chunks of 256 tokens the packed copy adds up the chunk sums itself, beyond a launch
+    scans them: offsets and packed values equal the oracle's."""
+    D, G = 64, 8
+    rng = np.random.default_rng(N)
+    V = rng.integers(0, 1 << 16, size=(1, 1, N, D)).astype(np.uint16) & 0xBFFF
+    mask = rng.integers(0, 1 << G, size=(1, 1, N)).astype(np.uint16)
+    c = stc.RoutedCache(1, 1, 1, D, N, G, 1, device=DEV)
+    c.vpacked.view(torch.int16).fill_(0x7FC0)
+    c.build(torch.zeros(1, 1, N, D, dtype=torch.bfloat16, device=DEV), PT.to_dev_bf16(V),
+            mask_in=PT.to_dev_u16(mask))
+    torch.cuda.synchronize()
+    off = O.token_offsets(mask[0, 0], G)
+    kept = ((mask[0, 0][:, None] >> np.arange(G, dtype=np.uint16)) & 1).astype(bool)
+    packed = V.reshape(N, G, D // G)[kept]
+    assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[0, 0], off)
+    vp = PT.host_bf16(c.vpacked)[0, 0]
+    assert np.array_equal(vp[:len(packed)], packed) and np.all(vp[len(packed):] == 0x7FC0)
