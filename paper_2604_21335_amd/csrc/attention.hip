@@ -5,7 +5,7 @@
 namespace stc {
 
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
-__global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams P) {
+__global__ __launch_bounds__(64 * WAVES, MULTI && D == 64 ? 4 : 1) void attn_mfma_kernel(const AttnParams P) {
   extern __shared__ __align__(16) unsigned char lds[];  // WAVES * AttnCfg<D>::WAVE_LDS bytes
   int stream = blockIdx.y, split = blockIdx.x;
   if (P.nx > 0) {

@@ -13,7 +13,7 @@ namespace stc {
 // Bound by memory while many workgroups are in different parts, by the chain of dependent
 // accesses of one stream where there are few.
 template <int D, int RM, bool TAIL, bool STREAM>
-__global__ __launch_bounds__(512) void step_kernel(const AttnParams P,
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnParams P,
                                                    const score_u32x4* __restrict__ tiles,
                                                    int tiles_cap, float* __restrict__ score) {
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
