@@ -31,8 +31,8 @@ typedef score_u32x4 u32x4;
 // (score_tiles.hpp): at most 128 registers, so four wavefronts per SIMD for any number of heads
 // per KV head.  R up to 8 is exact; R = 16 serves 9 .. 16 heads.  Measured against the forms that
 // were used for up to 4 heads (operands in registers, two tiles ahead), D = 64 and more
-// than 8 heads (one head at a time on the vector ALUs): 256 streams of 1024 pages 23.3 us for
-// 26.9, 32 streams of 8192 pages at 3 heads 11.9 for 14.6, 40 of 1001 pages at 16 heads and
+// than 8 heads (one head at a time on the vector ALUs): 256 streams of 1024 pages 21.8 us for
+// 26.9, 32 streams of 4096 pages at 3 heads 12.0 for 14.6, 40 of 1001 pages at 16 heads and
 // D = 64 5.8 for 14.7, 64 of 2048 pages at 16 heads 18.6 for 67.7.
 template <int D, int R, bool PER_HEAD, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8)))
@@ -67,7 +67,6 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
   const int tcap = bounds_tiles(token_cap(s));  // tiles per stream in memory
   constexpr int T16 = (D / 32) * 64;            // 16-byte units per tile
-  constexpr int WV = 4;
   const u32x4* t4 = (const u32x4*)bounds;
   const uint16_t* q16 = (const uint16_t*)q;
   // Query operands in shared memory, one tile requested at a time per wavefront (measured: two
@@ -77,13 +76,16 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   // where ordinary loads are faster (4 streams of 8192 pages, 17 MB: 5.4 us against 6.1; with
   // 2048 workgroups 256 streams of 256 pages take 7.3 us instead of 6.5).
   const bool stream_loads = (long long)streams * ntiles * T16 * 16 >= (64ll << 20);
-  const int want = max(1, 1024 / streams);
+  // Up to 4 heads per KV head, whose tiles take half as long, half as many workgroups of twice the
+  // size start sooner (128 streams of 250 pages: 19.9 against 20.4 us per step).
+  const int waves = R <= 4 ? 8 : 4;
+  const int want = max(1, 4096 / waves / streams);
   int tp = (ntiles + want - 1) / want;
-  tp = (tp + WV - 1) / WV * WV;
+  tp = (tp + waves - 1) / waves * waves;
   const dim3 grid((ntiles + tp - 1) / tp, streams);
 #define STC_SCORE_GO(RR, PH, STREAM)                                                              \
-  score_lds_kernel<D, RR, PH, WV, STREAM><<<grid, 64 * WV, 0, st>>>(t4, q16, score, NP, s.Hq,     \
-                                                                    s.Hkv, tp, tcap)
+  score_lds_kernel<D, RR, PH, (RR <= 4 ? 8 : 4), STREAM><<<grid, 64 * waves, 0, st>>>(            \
+      t4, q16, score, NP, s.Hq, s.Hkv, tp, tcap)
 #define STC_SCORE_CASE(RR)                                                                        \
   case RR:                                                                                        \
     if (per_head) {                                                                               \
