@@ -100,3 +100,26 @@ def test_packed_copy_on_both_sides_of_the_scan_launch(N):
     assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[0, 0], off)
     vp = PT.host_bf16(c.vpacked)[0, 0]
     assert np.array_equal(vp[:len(packed)], packed) and np.all(vp[len(packed):] == 0x7FC0)
+
+
+@pytest.mark.parametrize("N", [1, 64, 65, 208, 256, 257])
+def test_masks_given_in_the_array_they_are_written_to(N):
+    """mask_in may be the mask array itself: streams of one chunk, whose packing workgroups also
+    read the masks of tokens in front of theirs, and longer ones; bits past the groups are cleared."""
+    B, Hkv, D, G = 3, 5, 128, 8
+    rng = np.random.default_rng(N)
+    V = randn_bf16(rng, (B, Hkv, N, D))
+    given = rng.integers(0, 1 << 16, size=(B, Hkv, N)).astype(np.uint16)
+    c = stc.RoutedCache(B, Hkv, Hkv, D, N, G, 1, device=DEV)
+    c.vpacked.view(torch.int16).fill_(0x7FC0)
+    c.mask.copy_(PT.to_dev_u16(given))
+    c.build(torch.zeros(B, Hkv, N, D, dtype=torch.bfloat16, device=DEV), PT.to_dev_bf16(V), mask_in=c.mask)
+    torch.cuda.synchronize()
+    vp = PT.host_bf16(c.vpacked)
+    for b in range(B):
+        for h in range(Hkv):
+            m = given[b, h] & np.uint16((1 << G) - 1)
+            off = O.token_offsets(m, G)
+            assert np.array_equal(PT.host_u16(c.mask)[b, h], m)
+            assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[b, h], off)
+            assert np.array_equal(vp[b, h, :int(off[-1])], O.pack_values(V[b, h], m, off, G))
