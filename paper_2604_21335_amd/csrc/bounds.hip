@@ -27,6 +27,7 @@ __device__ __forceinline__ i16x2 fold_pair(i16x2 a, i16x2 b, Op op) {
 }
 
 constexpr int kBoundsWavePages = 2;  // adjacent pages per wavefront, all requested at once
+constexpr int kBoundsStreamWaves = 7;  // streams of at most this many wavefronts are one workgroup
 
 // One wavefront takes 2 adjacent pages.  Every request is 1 KiB of adjacent addresses (4 token
 // rows at D = 128, 8 at D = 64): lane l receives channels 8*(l % LPR) .. +8 of row l / LPR, so
@@ -40,19 +41,22 @@ constexpr int kBoundsWavePages = 2;  // adjacent pages per wavefront, all reques
 // with 4 pages per wavefront, 124-137 with wavefronts that walk a run of pages, and 131 for
 // the form before, in which a thread walked the 16 rows of a page four loads at a time (a request
 // was four pieces of 256 bytes in four pages).
+// A workgroup is 4 wavefronts.  A stream of up to 7 is one workgroup that has no wavefronts for the
+// padding pages of its last tile: the one with the last page writes their zeros (2048 streams of
+// 130 tokens, 9 pages in two tiles: 16.2 us, 19.4 with wavefronts for the padding; at 8 wavefronts two workgroups are as
+// good, 24.4 us, and one of 8 is slower, 25.9).
 template <int D>
-__global__ __launch_bounds__(256) void bounds_kernel(const bounds_u32x4* __restrict__ K,
-                                                     uint32_t* __restrict__ bounds, int N, int NP,
-                                                     int Ncap) {
+__global__ __launch_bounds__(64 * kBoundsStreamWaves) void bounds_kernel(
+    const bounds_u32x4* __restrict__ K, uint32_t* __restrict__ bounds, int N, int NP, int Ncap) {
   constexpr int LPR = D / 8;            // lanes per token row
   constexpr int RPL = 64 / LPR;         // rows per request
   constexpr int NLD = kPage / RPL;      // requests per page
   constexpr int PW = kBoundsWavePages;
   const int stream = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p0 = (blockIdx.x * 4 + wave) * PW;
-  const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
-  if (p0 >= ntiles * kBoundsTilePages) return;
+  const int p0 = (blockIdx.x * (blockDim.x >> 6) + wave) * PW;
+  const int ptile = (NP + kBoundsTilePages - 1) / kBoundsTilePages * kBoundsTilePages;
+  if (p0 >= ptile) return;
   const int piece = lane % LPR, row = lane / LPR;
   const bounds_u32x4* Ks = K + (size_t)stream * Ncap * LPR + piece;
   // rows past the last token repeat it, which changes neither minimum nor maximum
@@ -66,6 +70,12 @@ __global__ __launch_bounds__(256) void bounds_kernel(const bounds_u32x4* __restr
   uint32_t* tiles = bounds + (size_t)stream * bounds_tiles(Ncap) * bounds_tile_dwords(D);
   auto lo = [](i16x2 a, i16x2 b) { return __builtin_elementwise_min(a, b); };
   auto hi = [](i16x2 a, i16x2 b) { return __builtin_elementwise_max(a, b); };
+  const int c = 8 * piece + 2 * (lane >> 4);
+  auto put = [&](int page, bounds_u32x2 w) {
+    if (D == 128 || (lane & 8) == 0)
+      *(bounds_u32x2*)(tiles + (size_t)(page / kBoundsTilePages) * bounds_tile_dwords(D) +
+                       bounds_tile_unit(D, page % kBoundsTilePages, c) * 4 + c % 4) = w;
+  };
 #pragma unroll
   for (int p = 0; p < PW; ++p) {
     i16x2 mn[4], mx[4];  // channels 8*piece + 2*d, +1
@@ -87,29 +97,28 @@ __global__ __launch_bounds__(256) void bounds_kernel(const bounds_u32x4* __restr
     }
     uint32_t mnw = __builtin_bit_cast(uint32_t, bf16_order2(a));
     uint32_t mxw = __builtin_bit_cast(uint32_t, bf16_order2(b));
-    const int page = p0 + p;
-    if (page >= NP) mnw = mxw = 0u;  // padding pages of the stream's last tile
+    if (p0 + p >= NP) mnw = mxw = 0u;  // a padding page of the stream's last tile
     // minimum in the low half, maximum in the high half of each channel's dword
-    const bounds_u32x2 w = {(mnw & 0xffffu) | (mxw << 16), (mnw >> 16) | (mxw & 0xffff0000u)};
-    const int c = 8 * piece + 2 * (lane >> 4);
-    if (D == 128 || (lane & 8) == 0)
-      *(bounds_u32x2*)(tiles + (size_t)(page / kBoundsTilePages) * bounds_tile_dwords(D) +
-                       bounds_tile_unit(D, page % kBoundsTilePages, c) * 4 + c % 4) = w;
+    put(p0 + p, bounds_u32x2{(mnw & 0xffffu) | (mxw << 16), (mnw >> 16) | (mxw & 0xffff0000u)});
   }
+  if (gridDim.x == 1 && p0 + PW >= NP)  // the padding pages behind the last wavefront's own
+    for (int page = p0 + PW; page < ptile; ++page) put(page, bounds_u32x2{0u, 0u});
 }
 
 int launch_bounds(const stc_shape_t& s, const void* K, void* bounds, hipStream_t st) {
   const int NP = (s.N + kPage - 1) / kPage;
   const int streams = s.B * s.Hkv;
-  const int pages_per_block = 4 * kBoundsWavePages;
-  const int pages = (NP + kBoundsTilePages - 1) / kBoundsTilePages * kBoundsTilePages;
-  dim3 grid((pages + pages_per_block - 1) / pages_per_block, streams);
+  const int need = (NP + kBoundsWavePages - 1) / kBoundsWavePages;  // wavefronts with a page
+  const bool one = need <= kBoundsStreamWaves;
+  const int waves = one ? need : 4;
+  const int ptile = (NP + kBoundsTilePages - 1) / kBoundsTilePages * kBoundsTilePages;
+  dim3 grid(one ? 1 : (ptile / kBoundsWavePages + waves - 1) / waves, streams);
   if (s.D == 128)
-    bounds_kernel<128><<<grid, 256, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N, NP,
-                                             token_cap(s));
+    bounds_kernel<128><<<grid, 64 * waves, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N,
+                                                    NP, token_cap(s));
   else
-    bounds_kernel<64><<<grid, 256, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N, NP,
-                                            token_cap(s));
+    bounds_kernel<64><<<grid, 64 * waves, 0, st>>>((const bounds_u32x4*)K, (uint32_t*)bounds, s.N,
+                                                   NP, token_cap(s));
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -51,6 +51,36 @@ def test_bounds_and_packed_copy_at_tile_edges(N, D, G, room):
         assert int(c.dev_status.item()) == int(over)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N", [1, 16, 17, 32, 33, 97, 128, 130, 145, 208, 225, 241, 256, 257, 273, 289])
+@pytest.mark.parametrize("room", [0, 200])
+def test_bounds_of_short_streams_and_their_padding_pages(D, N, room):
+    """Streams of up to 8 wavefronts of 2 pages are one workgroup, longer ones several of 4: bounds
+    equal the oracle's, the padding pages of the last tile hold zeros, further tiles are untouched."""
+    B, Hkv = 2, 5
+    rng = np.random.default_rng(31 * N + D)
+    K = randn_bf16(rng, (B, Hkv, N, D))
+    c = stc.RoutedCache(B, Hkv, Hkv, D, N, 1, 1, device=DEV, n_cap=N + room if room else 0)
+    if room:
+        c.K.fill_(float("inf"))                            # rows behind the last token count for nothing
+        c.K[:, :, :N].copy_(PT.to_dev_bf16(K))
+    else:
+        c.K = PT.to_dev_bf16(K)
+    c.bounds.view(torch.int16).fill_(0x7FC0)
+    stc.stc_build_page_bounds(c.shape, c.K, c.bounds)
+    torch.cuda.synchronize()
+    rows = PT.host_bf16(c.bounds_rows())
+    NP = (N + 15) // 16
+    nt = (NP + 7) // 8
+    raw = PT.host_bf16(c.bounds).reshape(B * Hkv, -1, D // 32, 2, 8, 4, 4, 2)
+    for b in range(B):
+        for h in range(Hkv):
+            assert np.array_equal(rows[b, h], O.page_bounds(K[b, h]))
+    for page in range(NP, 8 * nt):
+        assert not raw[:, page // 8, :, page % 8 // 4, :, page % 4].any()
+    assert np.all(raw[:, nt:] == 0x7FC0)
+
+
 @pytest.mark.parametrize("N,G,room", [(1, 8, 0), (33, 1, 2), (2047, 8, 1), (2048, 8, 0), (2049, 8, 0), (4096, 8, 0),
                                       (4097, 8, 3), (8192, 8, 0), (8193, 8, 0), (16384, 2, 0), (16385, 2, 0),
                                       (16385, 1, 0), (4095, 16, 0), (4097, 16, 0), (513, 4, 0)])
