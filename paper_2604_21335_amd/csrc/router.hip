@@ -75,11 +75,18 @@ __device__ __forceinline__ float odd_channel(uint32_t w) {
 
 // First two levels of the sum over the 4 lanes that share lane bits 0, 1, 4 and 5 (pieces
 // (0,1)(2,3), then both) for the four router outputs v[0..3]: the lane with bit 2 set holds
-// outputs 0 / 2, the other 1 / 3; bit 3 set: 0 / 1, clear: 2 / 3.
+// outputs 0 / 2, the other 1 / 3; bit 3 set: 0 / 1, clear: 2 / 3.  Of fewer than four outputs only
+// the sums that the lanes of an output hold are taken.
+template <int OUTPUTS>
 __device__ __forceinline__ float fold_four(const float (&v)[4], bool bit2, bool bit3) {
   // (every sum is taken in all lanes: a lane cannot read from one that a branch switched off)
   const float s0 = v[0] + dpp_f32<0x124>(v[0]);  // row_ror:4, the piece before
+  if constexpr (OUTPUTS == 1) return s0 + dpp_f32<0x128>(s0);
   const float s1 = v[1] + dpp_f32<0x12c>(v[1]);  // row_ror:12, the piece behind
+  if constexpr (OUTPUTS == 2) {
+    const float x = bit2 ? s0 : s1;
+    return x + dpp_f32<0x128>(x);
+  }
   const float s2 = v[2] + dpp_f32<0x124>(v[2]);
   const float s3 = v[3] + dpp_f32<0x12c>(v[3]);
   const float x01 = bit2 ? s0 : s1, x23 = bit2 ? s2 : s3;
@@ -106,6 +113,8 @@ __global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_
   const bool bit2 = lane & 4, bit3 = lane & 8;
   const int t_first = blockIdx.x * C::BLOCK_TOKENS + (SPLIT ? 0 : wave * C::WAVE_TOKENS) +
                       4 * tq + j;
+  if constexpr (!SPLIT)  // a wavefront behind the last token (no barriers in this form)
+    if (blockIdx.x * C::BLOCK_TOKENS + wave * C::WAVE_TOKENS >= N) return;
   const int nc = d_model / 128;
   const int row16 = d_model / 8;  // 16-byte pieces per row
 
@@ -190,7 +199,7 @@ __global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_
         }
         const f32x4 s = half[0] + half[1];
         const float v[4] = {s[0], s[1], s[2], s[3]};
-        y[hh] = fold_four(v, bit2, bit3);
+        y[hh] = fold_four<(G < 4 ? G : 4)>(v, bit2, bit3);
       }
       // pieces 0..3 and 4..7 sit in lanes with bit 4 clear and set: two row groups at a time
 #pragma unroll
@@ -232,6 +241,44 @@ __global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_
   }
 }
 
+// Tokens per wavefront and who shares them.  Measured, us, as split 8 / split 16 / own 16 / own 32:
+//   channels tokens     4 groups                     8 groups                     16 groups
+//   3584       1000    6.3/  8.1/ 21 / 34           8.1/ 11  / 28 / 51         12.2/ 16  / 51 / 88
+//              6000   13.4/ 13.6/ 21 / 35          19.0/ 20.4/ 29 / 51         34  / 32  / 51 / 89
+//             12000   23  / 19  / 21 / 34          34  / 29.8/ 29 / 51         65  / 47  / 51 / 89
+//             24000   40  / 33  / 40 / 35          59  / 56  / 52 / 51        126  / 92  / 89 / 90
+//             32768   56  / 45  / 42 / 38          83  / 78  / 55 / 54        170  /125  / 92 / 92
+//        64 x   576   62  / 51  / 61 / 69          91  / 86  / 81 / 87        191  /140  /131 /152
+//             65536  120  / 95  / 92 / 87         166  /158  /132 /100        336  /253  /193 /167
+//            524288  883  /698  /676 /642        1218  /1202 /906 /790       2644  /1972 /1387/1220
+//   1024       6000    5.5/  5.7/7.8/ 12           7.7/  8.8/ 10 / 17         14.2/ 12.7/ 17 / 29
+//             12000    8.8/  7.7/8.4/ 12          13.5/ 12.6/ 11 / 17         26  / 18.5/ 18 / 29
+//             24000   17  / 15  / 14 / 13          26  / 25  / 17 / 18         49  / 37  / 29 / 29
+//    512      12000    7.8/  6.7/5.4/ 7.9         11.5/ 9.3/6.6/10.4           19  / 13.4/ 11 / 17
+// Few tokens are bound by the chain of chunks of a wavefront, which the split form cuts to an eighth
+// (the more chunks there are, the longer it wins); many by the weights' preparation per wavefront,
+// which more tokens share.  The last form's wavefronts fill a SIMD each (64 x 576 tokens are a second
+// round of an eighth).  A wavefront's tokens are of one batch element: elements of few tokens take the
+// form that they fill (1024 channels, 8 groups, elements of 1 token: 32768 of them 201 / 408 / 232 /
+// 545; of 13: 2048 of them 33 / 31 / 21 / 43; of 40: 3000 of them 116 / 132 / 72 / 117; of 65: 512 of
+// them 37 / 39 / 38 / 27).
+RouterForm router_form(int B, int N, int d_model, int G) {
+  const long long tokens = (long long)B * N;
+  const int chunks = d_model / 128;
+  if (tokens < 3000 || N <= 8) return kSplit8;
+  const int split_max = G <= 4 ? min(24000, 1600 * chunks)
+                               : min(12000, 4000 + (G == 8 ? 600 : 1200) * chunks);
+  if (tokens < split_max) return kSplit16;
+  constexpr int kSimds = 1024;
+  const long long waves = (long long)B * ((N + 31) / 32);  // of the last form
+  const bool many = waves >= kSimds * 4 / 3;               // no short second round
+  if (G <= 4) {
+    if (N >= 64 && tokens >= 24000 && waves <= kSimds) return kOwn32;
+    if (N >= 64 && chunks >= 16 && waves < kSimds * 7 / 4) return kSplit16;
+  }
+  return N >= 64 && many ? kOwn32 : kOwn16;
+}
+
 int launch_router_logits(const void* h, const void* W, const float* bias, int bias_stride,
                          float* logits, int B, int Hkv, int N, int d_model, int G,
                          hipStream_t st) {
@@ -242,26 +289,13 @@ int launch_router_logits(const void* h, const void* W, const float* bias, int bi
          RouterCfg<GG, TG, SPLIT>::WAVES * 64, 0, st>>>(                                        \
           (const router_u32x4*)h, (const router_u32x4*)W, bias, logits, N, d_model, Hkv,        \
           bias_stride)
-  // Tokens per wavefront and who shares them (measured at 3584 and 4096 channels, us):
-  //   tokens    8 groups: split 1 / split 2 / 2 / 4    4 groups            16 groups (1 and 2)
-  //     2000        8.6 /  10.8 /   - /   -            7.5 /  9.2          13.5 / 18.6
-  //     4000       13.4 /  11.2 /  29 /  50           11.4 /  9.7 / 27     24.8 / 19.1 / 57
-  //     8000       24.3 /  21.9 /  29 /  50           19.1 / 16.6 / 29     49.3 / 37.2 / 57
-  //    16000       43.6 /  41.2 /  31 /  51           33.7 / 28.1 / 33     94.6 / 71.5 / 58
-  //    64000      151   / 150   / 106 /  91          117   / 90   / 109    363  / 274  / 190
-  //   524288          -       -   839 / 683             -       -  623/616      -      - / 1289
-  // Few tokens are bound by the chain of chunks of a wavefront, which the split form cuts to an
-  // eighth; many by the weights' preparation per wavefront, which more tokens share.
-  const long long tokens = (long long)B * N;
-  const bool split1 = tokens < 3000;
-  const bool split2 = tokens < (G <= 4 ? 131072 : 12000);
-  const bool two = tokens < 24000 || G == 16;
+  const RouterForm form = router_form(B, N, d_model, G);
 #define STC_ROUTER_CASE(GG)                                                                     \
   case GG:                                                                                      \
-    if (split1) STC_ROUTER_GO(GG, 1, true);                                                     \
-    else if (split2) STC_ROUTER_GO(GG, 2, true);                                                \
-    else if (two) STC_ROUTER_GO(GG, 2, false);                                                  \
-    else STC_ROUTER_GO(GG, (GG == 16 ? 2 : 4), false);                                          \
+    if (form == kSplit8) STC_ROUTER_GO(GG, 1, true);                                            \
+    else if (form == kSplit16) STC_ROUTER_GO(GG, 2, true);                                      \
+    else if (form == kOwn16) STC_ROUTER_GO(GG, 2, false);                                       \
+    else STC_ROUTER_GO(GG, 4, false);                                                           \
     break;
   switch (G) {
     STC_ROUTER_CASE(1)

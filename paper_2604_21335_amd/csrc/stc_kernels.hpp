@@ -80,6 +80,10 @@ int launch_flush_tail(const stc_shape_t& s, void* K_tail, void* V_tail, int n, i
 int launch_append_tail(const stc_shape_t& s, const void* k_new, const void* v_new, void* K_tail,
                        void* V_tail, int n_tail, int tail_cap, hipStream_t st);
 
+// How the router's tokens are shared out: the wavefronts of a workgroup on the same 8 or 16
+// tokens, or 16 or 32 tokens of its own for every wavefront.
+enum RouterForm { kSplit8, kSplit16, kOwn16, kOwn32 };
+RouterForm router_form(int B, int N, int d_model, int G);
 int launch_router_logits(const void* h, const void* W, const float* bias, int bias_stride,
                          float* logits, int B, int Hkv, int N, int d_model, int G, hipStream_t st);
 

@@ -6,13 +6,14 @@ import torch
 import paper_2604_21335_amd as stc
 from oracle import stc_oracle as O
 from tests import parity as PT
+from tests import routes
 from tests.helpers import randn_bf16
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# wavefronts that share tokens (up to 3000, then up to 12000 or 131072 tokens), wavefronts of their own
+# wavefronts that share 8 tokens (up to 3000, or elements of up to 8) or 16, wavefronts of their own
 # with 16 and with 32 tokens; token counts that fill no wavefront; more than 64 chunks, whose
 # sums meet in two rounds; fewer chunks than wavefronts
 @pytest.mark.parametrize("B,N,dm,G", [
@@ -35,3 +36,31 @@ def test_router_logits_on_both_sides_of_every_rule(B, N, dm, G):
     for b in range(B):
         want = O.router_logits(h[b], Wr, bias)
         assert np.array_equal(got[b, 0].view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("B,N,dm,G,form", [
+    (3001, 1, 128, 8, routes.SPLIT8), (400, 8, 256, 4, routes.SPLIT8), (400, 9, 256, 4, routes.OWN16),
+    (600, 9, 256, 16, routes.SPLIT16), (300, 33, 128, 8, routes.OWN16), (300, 63, 256, 2, routes.OWN16),
+    (454, 65, 128, 8, routes.OWN16), (455, 65, 128, 8, routes.OWN32), (455, 65, 128, 16, routes.OWN32),
+    (1, 23999, 128, 4, routes.OWN16), (1, 24000, 128, 4, routes.OWN32), (1, 32769, 128, 2, routes.OWN16),
+    (1, 43649, 128, 1, routes.OWN32), (1, 32769, 2048, 4, routes.SPLIT16), (1, 57313, 2048, 1, routes.OWN32),
+    (1, 43681, 256, 16, routes.OWN32), (7, 6241, 128, 16, routes.OWN32)])
+def test_router_logits_of_many_elements_and_of_every_form(B, N, dm, G, form):
+    """Elements that end inside a wavefront or leave wavefronts of a workgroup without tokens, and both
+    sides of the lines between the forms: the first, last and some other tokens bit for bit, every
+    logit written."""
+    assert routes.router_form(B, N, dm, G) == form
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + dm)
+    h = torch.randn(B, N, dm, device=DEV, generator=g).bfloat16()
+    Wr = torch.randn(G, dm, device=DEV, generator=g).bfloat16()
+    bias = torch.randn(B, G, device=DEV, generator=g)
+    logits = torch.full((B, 2, N, G), float("nan"), dtype=torch.float32, device=DEV)
+    stc.stc_router_logits(h, Wr, bias, logits, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(logits[:, 0], logits[:, 1]) and bool(torch.isfinite(logits).all())
+    rng = np.random.default_rng(N)
+    for b in sorted({0, B // 2, B - 1}):
+        at = sorted({*range(min(N, 40)), *range(max(0, N - 40), N), *rng.integers(0, N, 100).tolist()})
+        want = O.router_logits(PT.host_bf16(h[b, at]), PT.host_bf16(Wr), bias[b].cpu().numpy())
+        assert np.array_equal(logits[b, 0, at].cpu().numpy().view(np.uint32), want.view(np.uint32))

@@ -1,0 +1,24 @@
+"""Dispatch rules that depend on more than one size, on the CPU."""
+import pytest
+
+from tests import routes
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("dm", [128, 512, 1024, 3584, 8192])
+def test_router_form_fits_the_tokens_of_a_batch_element(G, dm):
+    """A wavefront's tokens lie in one batch element.  The token slots that a launch computes are never
+    more than those of workgroups of 64 tokens, whatever the number of elements."""
+    tokens_of = {routes.SPLIT8: 8, routes.SPLIT16: 16, routes.OWN16: 16, routes.OWN32: 32}
+    for N in [*range(1, 70), 95, 97, 129, 208, 576, 4097]:
+        for B in (1, 3, 64, 500, 2048, 32768, 65535):
+            if B * N > 1 << 27:
+                continue
+            t = tokens_of[routes.router_form(B, N, dm, G)]
+            assert (N + t - 1) // t * t <= (N + 63) // 64 * 64, (B, N)
+
+
+def test_router_forms_are_all_reached():
+    for G in (1, 2, 4, 8, 16):
+        assert {routes.router_form(B, N, 1024, G) for B, N in [(1, 100), (1, 4000), (1, 23000), (4, 32768)]} == {
+            routes.SPLIT8, routes.SPLIT16, routes.OWN16, routes.OWN32}
