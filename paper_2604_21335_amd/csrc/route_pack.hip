@@ -302,6 +302,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     const float* __restrict__ logits, uint16_t* __restrict__ mask,
     uint32_t* __restrict__ chunk_sum, int N, int nchunks, int Ncap, uint32_t budget, int share) {
   constexpr int TPT = KPT / G;  // tokens per thread: tid, tid + 1024, ...
+  static_assert(TPT * kGlobalThreads <= kSmallTokens, "masks and chunk counters in LDS");
   __shared__ uint32_t hist[kGlobalBins];
   __shared__ uint32_t waves[kGlobalThreads / 64];
   __shared__ uint32_t s_pick[3];  // digit, rank inside it, keys that have it
@@ -680,13 +681,14 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
       // long as there are CUs for them: one CU takes long to write many streams' masks
       const int parts = max(1, min(share, 256 / sets));
 #define STC_GLOBAL_SMALL(GG, KPT)                                                             \
+  if constexpr (KPT / GG * kGlobalThreads <= kSmallTokens)                                    \
   global_small_kernel<GG, KPT><<<dim3(sets, parts), kGlobalThreads, 0, st>>>(                 \
       logits, mask, chunk, s.N, nchunks, Ncap, budget, share)
 #define STC_GLOBAL_SMALL_CASE(GG)                                                             \
   case GG:                                                                                    \
-    if (n <= 16u * kGlobalThreads) STC_GLOBAL_SMALL(GG, 16);                                  \
-    else if (n <= 32u * kGlobalThreads) STC_GLOBAL_SMALL(GG, 32);                             \
-    else STC_GLOBAL_SMALL(GG, 64);                                                            \
+    if (n <= 16u * kGlobalThreads) { STC_GLOBAL_SMALL(GG, 16); }                              \
+    else if (n <= 32u * kGlobalThreads) { STC_GLOBAL_SMALL(GG, 32); }                         \
+    else { STC_GLOBAL_SMALL(GG, 64); }                                                        \
     break;
       switch (s.G) {
         STC_GLOBAL_SMALL_CASE(1)
@@ -700,7 +702,7 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
 #undef STC_GLOBAL_SMALL_CASE
 #undef STC_GLOBAL_SMALL
     } else {
-  global_init_kernel<<<(sets * kGlobalBins + 255) / 256, 256, 0, st>>>(hist, state, sets,
+      global_init_kernel<<<(sets * kGlobalBins + 255) / 256, 256, 0, st>>>(hist, state, sets,
                                                                            budget);
       if (budget > 0) {
         dim3 hgrid((unsigned)(((unsigned long long)n + kHistSlice - 1) / kHistSlice), sets);
