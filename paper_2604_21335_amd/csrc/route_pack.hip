@@ -290,12 +290,29 @@ __global__ __launch_bounds__(kChunk) void global_mask_kernel(
 }
 
 // The whole selection of one set of logits, masks and chunk sums of every gridDim.y-th stream of
-// the set included, by one workgroup with the keys in registers: thread i owns the tokens i, i + 1024, ...  Same
-// digits and same order among equal keys as the kernels above.  Bound by latency (histograms
-// in LDS, three block scans).  Routing and packing of 8 x 32 streams of 4096 tokens with one set of
-// 32768 logits per batch element: 26 us less than with the nine launches above, all of which
-// went over a copy of the selection per stream.
+// the set included, by one workgroup with the keys in registers: thread i owns the tokens i,
+// i + 1024, ...  Same order among equal keys as the kernels above.
+//
+// Bins of equal width between the smallest and the largest logit, and the keys of the wanted one's bin
+// ranked one by one.  Logits that crowd a few bins cost more, because their atomics wait for each
+// other and the bin holds too many keys: a wavefront that sees a crowd counts it by ballots, and the
+// bin's own smallest and largest key end the search (one value) or give a second set of bins.  What
+// crowds those too differs in scale and goes digit by digit, as do ranges that float cannot divide.
+// Bound by latency (histograms in LDS, block scans) and by instruction issue of the one CU.
+// Routing and packing, us, as one selection per stream in nine launches over the chip / in this form
+// with digits wherever the first bins fail and every key an atomic / now:
+//                            normal       halves       all equal      1 in 10 at -1e9  outliers x 1e4
+//   8 sets of 32768, 32 x   87/56/56     98/91/73     151/131/46     85/85/66         87/89/65
+//   4 sets of 65536         45/27/27     48/97/62      75/196/27     45/85/47         45/90/50
+//   8 sets of 1200          32/11/11     33/19/19      34/20/12      32/18/16         32/43/16
+// So sets of 65536 logits with ties or outliers are the one case that the launches over the chip do
+// faster; logits of a linear map have neither.
 constexpr int kSmallTokens = 16384;
+// Of the first keys of a wavefront, this many in one bin are a crowd (normal logits: 0.05 expected).
+constexpr int kGlobalCrowd = 6;
+// Keys of a bin that are ranked one by one: more are slower that way than in further bins (1199 of
+// 1200 logits: 43 us, 16 with further bins) or by digits (900 of 65536: 74 us, 57 by digits).
+constexpr uint32_t kGlobalRanked = 256;
 
 template <int G, int KPT>
 __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
@@ -306,7 +323,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   __shared__ uint32_t hist[kGlobalBins];
   __shared__ uint32_t waves[kGlobalThreads / 64];
   __shared__ uint32_t s_pick[3];  // digit, rank inside it, keys that have it
-  __shared__ uint32_t s_count;
+  __shared__ uint32_t s_count, s_crowd;
   __shared__ __align__(4) uint16_t s_mask[kSmallTokens];
   __shared__ uint32_t s_chunk[kSmallTokens / kChunk];
   const int tid = threadIdx.x;
@@ -323,15 +340,50 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   for (int i = tid; i < kSmallTokens / kChunk; i += kGlobalThreads) s_chunk[i] = 0u;
   uint32_t prefix = 0u, decided = 0u, remaining = budget;
   bool take_all = false, found = false;
-  // Bins of equal width between the smallest and the largest logit spread the keys over the
-  // histogram (a digit of the key's bits puts logits that share sign and exponent into a few
-  // bins, whose atomics then wait for each other).  The bin is monotone in the logit.
+  // Bins of equal width spread the keys over the histogram (a digit of the key's bits puts logits
+  // that share sign and exponent into a few bins).  The bin is monotone in the logit.
   float lo = 0.f, scale = 0.f;
   uint32_t bin_of_kth = 0u;
   auto bin = [&](uint32_t k) -> uint32_t {
     const float f = __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
     return min((uint32_t)((f - lo) * scale), (uint32_t)(kGlobalBins - 1));
   };
+  // The bin that holds the key of rank `remaining` among those in the histogram, that rank in the
+  // bin, and its number of keys -> s_pick.  Thread t owns the 4 adjacent bins 4095-4t .. 4092-4t
+  // (descending order).
+  auto pick = [&]() __attribute__((always_inline)) {
+    uint32_t c[4], own = 0, tot;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) own += c[j] = hist[kGlobalBins - 1 - (4 * tid + j)];
+    uint32_t above = block_exscan_1024(own, waves, &tot);  // keys in larger bins
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (above < remaining && remaining <= above + c[j]) {
+        s_pick[0] = (uint32_t)(kGlobalBins - 1 - (4 * tid + j));
+        s_pick[1] = remaining - above;
+        s_pick[2] = c[j];
+      }
+      above += c[j];
+    }
+    __syncthreads();
+  };
+  // The wanted key among the `cnt` keys listed in hist, one per thread.
+  auto rank = [&](uint32_t cnt) __attribute__((always_inline)) {
+    __syncthreads();
+    if (tid < (int)cnt) {
+      const uint32_t mine = hist[tid];
+      uint32_t gt = 0, ge = 0;
+      for (uint32_t j = 0; j < cnt; ++j) gt += hist[j] > mine, ge += hist[j] >= mine;
+      if (gt < remaining && remaining <= ge)  // equal keys agree
+        s_pick[0] = mine, s_pick[1] = remaining - gt, s_pick[2] = ge - gt;
+    }
+    __syncthreads();
+    prefix = s_pick[0];
+    remaining = s_pick[1];
+    take_all = s_pick[1] == s_pick[2];
+    found = true;
+  };
+  auto value = [](uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); };
   if (budget > 0) {
     uint32_t kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
@@ -347,64 +399,128 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     for (int w = 0; w < kGlobalThreads / 64; ++w)
       kmin = min(kmin, hist[w]), kmax = max(kmax, hist[64 + w]);
     __syncthreads();
-    lo = __uint_as_float((kmin & 0x80000000u) ? kmin & 0x7fffffffu : ~kmin);
-    const float hi = __uint_as_float((kmax & 0x80000000u) ? kmax & 0x7fffffffu : ~kmax);
+    lo = value(kmin);
+    const float hi = value(kmax);
     scale = (float)(kGlobalBins - 1) / (hi - lo);
-    // one value everywhere, or a range that float cannot divide: every key is in bin 0
+    if (kmin == kmax) {  // one value everywhere
+      prefix = kmin;
+      take_all = remaining == (uint32_t)N * G;
+      found = true;
+    }
+    // a range that float cannot divide: every key is in bin 0
     if (!(hi > lo) || !(hi - lo < 3.0e38f) || !(scale < 3.0e38f)) lo = 0.f, scale = 0.f;
   }
   if (budget > 0 && scale > 0.f) {
 #pragma unroll
     for (int j = 0; j < kGlobalBins / kGlobalThreads; ++j) hist[j * kGlobalThreads + tid] = 0u;
-    if (tid == 0) s_count = 0u;
+    if (tid == 0) s_count = 0u, s_crowd = 0u;
     __syncthreads();
+    // A wavefront in which many of the first keys share a bin counts its keys in it without atomics.
+    const int first = token(0) < N ? (int)bin(key[0][0]) : -1;
+    const int crowd = __builtin_amdgcn_readfirstlane(first);
+    if (__builtin_expect(crowd >= 0 && __popcll(__ballot(first == crowd)) >= kGlobalCrowd, 0)) {
+      uint32_t crowded = 0;
 #pragma unroll
-    for (int i = 0; i < TPT; ++i)
+      for (int i = 0; i < TPT; ++i)
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-        if (token(i) < N) atomicAdd(&hist[bin(key[i][g])], 1u);
-    __syncthreads();
-    uint32_t c[4], own = 0, tot;  // descending bins, as below
+        for (int g = 0; g < G; ++g) {
+          const int b = token(i) < N ? (int)bin(key[i][g]) : -1;
+          crowded += __popcll(__ballot(b == crowd));
+          if (b >= 0 && b != crowd) atomicAdd(&hist[b], 1u);
+        }
+      if ((tid & 63) == 0) atomicAdd(&hist[crowd], crowded);
+    } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) own += c[j] = hist[kGlobalBins - 1 - (4 * tid + j)];
-    uint32_t above = block_exscan_1024(own, waves, &tot);
+      for (int i = 0; i < TPT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (above < remaining && remaining <= above + c[j]) {
-        s_pick[0] = (uint32_t)(kGlobalBins - 1 - (4 * tid + j));
-        s_pick[1] = remaining - above;
-        s_pick[2] = c[j];
-      }
-      above += c[j];
+        for (int g = 0; g < G; ++g)
+          if (token(i) < N) atomicAdd(&hist[bin(key[i][g])], 1u);
     }
     __syncthreads();
+    pick();
     bin_of_kth = s_pick[0];
     remaining = s_pick[1];
     const uint32_t cnt = s_pick[2];
-    if (cnt <= (uint32_t)kGlobalThreads) {  // list the bin's keys and rank them, one per thread
+    if (cnt <= kGlobalRanked) {
 #pragma unroll
       for (int i = 0; i < TPT; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g)
           if (token(i) < N && bin(key[i][g]) == bin_of_kth)
             hist[atomicAdd(&s_count, 1u)] = key[i][g];
-      __syncthreads();
-      if (tid < (int)cnt) {
-        const uint32_t mine = hist[tid];
-        uint32_t gt = 0, ge = 0;
-        for (uint32_t j = 0; j < cnt; ++j) gt += hist[j] > mine, ge += hist[j] >= mine;
-        if (gt < remaining && remaining <= ge)  // equal keys agree
-          s_pick[0] = mine, s_pick[1] = remaining - gt, s_pick[2] = ge - gt;
-      }
-      __syncthreads();
-      prefix = s_pick[0];
-      remaining = s_pick[1];
-      take_all = s_pick[1] == s_pick[2];
-      found = true;
+      rank(cnt);
     }
   }
-  if (budget > 0 && !found) {  // digit by digit, within the bin
-    for (int pass = 0; pass < 3; ++pass) {
+  if (__builtin_expect(budget > 0 && !found, 0)) {
+    uint32_t klo = 0u, khi = 0xffffffffu;  // the wanted key is in [klo, khi]
+    if (scale > 0.f) {
+      // The smallest and the largest key of the bin: it may be one value, and if not, bins between
+      // these two spread its keys.
+      klo = 0xffffffffu, khi = 0u;
+#pragma unroll
+      for (int i = 0; i < TPT; ++i)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          if (token(i) < N && bin(key[i][g]) == bin_of_kth)
+            klo = min(klo, key[i][g]), khi = max(khi, key[i][g]);
+      for (int d = 32; d >= 1; d >>= 1) {
+        klo = min(klo, (uint32_t)__shfl_xor((int)klo, d));
+        khi = max(khi, (uint32_t)__shfl_xor((int)khi, d));
+      }
+      if ((tid & 63) == 0) hist[tid >> 6] = klo, hist[64 + (tid >> 6)] = khi;
+      __syncthreads();
+      for (int w = 0; w < kGlobalThreads / 64; ++w)
+        klo = min(klo, hist[w]), khi = max(khi, hist[64 + w]);
+      __syncthreads();
+      if (klo == khi) {
+        prefix = klo;
+        take_all = remaining == s_pick[2];
+        found = true;
+      }
+      const float lo2 = value(klo), scale2 = (float)(kGlobalBins - 1) / (value(khi) - lo2);
+      auto in_bin = [&](int i, int g) {
+        return token(i) < N && key[i][g] >= klo && key[i][g] <= khi;
+      };
+      auto bin2 = [&](uint32_t k) -> uint32_t {  // of such a key
+        return min((uint32_t)((value(k) - lo2) * scale2), (uint32_t)(kGlobalBins - 1));
+      };
+      bool spread = !found && scale2 < 3.0e38f;
+      if (spread) {
+#pragma unroll
+        for (int j = 0; j < kGlobalBins / kGlobalThreads; ++j) hist[j * kGlobalThreads + tid] = 0u;
+        // where a wavefront's keys crowd a bin again, the logits differ in scale: digits spread them
+        const int first = in_bin(0, 0) ? (int)bin2(key[0][0]) : -1;
+        const uint64_t any = __ballot(first >= 0);
+        const int crowd = __builtin_amdgcn_readlane(first, any ? __ffsll((long long)any) - 1 : 0);
+        if (any && __popcll(__ballot(first == crowd)) >= kGlobalCrowd) s_crowd = 1u;
+        __syncthreads();
+        spread = s_crowd == 0u;
+      }
+      if (spread) {
+        const uint32_t rank_in_bin = remaining;
+#pragma unroll
+        for (int i = 0; i < TPT; ++i)
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            if (in_bin(i, g)) atomicAdd(&hist[bin2(key[i][g])], 1u);
+        __syncthreads();
+        pick();
+        const uint32_t b = s_pick[0], cnt = s_pick[2];
+        remaining = s_pick[1];
+        if (cnt <= kGlobalRanked) {
+#pragma unroll
+          for (int i = 0; i < TPT; ++i)
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+              if (in_bin(i, g) && bin2(key[i][g]) == b)
+                hist[atomicAdd(&s_count, 1u)] = key[i][g];
+          rank(cnt);
+        } else {
+          remaining = rank_in_bin;
+        }
+      }
+    }
+    for (int pass = 0; pass < 3 && !found; ++pass) {
       const int shift = global_shift(pass);
       const uint32_t bins = global_bins(pass);
 #pragma unroll
@@ -414,25 +530,11 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
       for (int i = 0; i < TPT; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          if (token(i) < N && (key[i][g] & decided) == prefix && bin(key[i][g]) == bin_of_kth)
+          if (token(i) < N && (key[i][g] & decided) == prefix && key[i][g] >= klo &&
+              key[i][g] <= khi)
             atomicAdd(&hist[(key[i][g] >> shift) & (bins - 1)], 1u);
       __syncthreads();
-      // thread t owns the 4 adjacent digits 4095-4t .. 4092-4t (bins past `bins` are empty)
-      uint32_t c[4], own = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) own += c[j] = hist[kGlobalBins - 1 - (4 * tid + j)];
-      uint32_t tot;
-      uint32_t above = block_exscan_1024(own, waves, &tot);  // keys with a larger digit
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (above < remaining && remaining <= above + c[j]) {
-          s_pick[0] = (uint32_t)(kGlobalBins - 1 - (4 * tid + j));
-          s_pick[1] = remaining - above;
-          s_pick[2] = c[j];
-        }
-        above += c[j];
-      }
-      __syncthreads();
+      pick();  // (bins past `bins` are empty)
       prefix |= s_pick[0] << shift;
       decided |= (bins - 1) << shift;
       remaining = s_pick[1];

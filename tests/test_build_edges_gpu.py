@@ -111,6 +111,60 @@ def test_global_budget_at_the_limits_of_its_one_workgroup_form(N, G, room, share
                                       O.token_offsets(m, G))
 
 
+def _uneven(rng, shape, kind):
+    """Logits that a selection by bins or digits has to work for."""
+    x = rng.standard_normal(shape).astype(np.float32)
+    tok = rng.random(shape[:-1] + (1,))
+    if kind == "equal":
+        x[:] = -0.25
+    elif kind == "two values":
+        x = np.where(x > 0.5, np.float32(1.5), np.float32(-0.0)).astype(np.float32)
+    elif kind == "halves":
+        x = np.round(2 * x) / 2
+    elif kind == "masked":                                 # tokens at a large negative number
+        x = np.where(tok < 0.3, np.float32(-1e9), x)
+    elif kind == "mostly masked":
+        x = np.where(tok < 0.9, np.float32(-1e9), x)
+    elif kind == "outliers":
+        x = np.where(rng.random(shape) < 0.002, x * np.float32(1e4), x)
+    elif kind == "nested":                                 # every round of bins leaves most in one
+        e = rng.integers(0, 9, size=shape)
+        x = x * np.float32(10.0) ** (4 * e - 30)
+    elif kind == "lowest":
+        x = np.where(tok < 0.3, np.finfo(np.float32).min, x)
+    elif kind == "wide":                                   # a range beyond the largest float
+        x = np.where(tok < 0.1, np.float32(3.2e38), np.where(tok > 0.9, np.float32(-3.2e38), x))
+    elif kind == "infinite":
+        x = np.where(tok < 0.1, np.float32(np.inf), np.where(tok > 0.8, np.float32(-np.inf), x))
+    elif kind == "subnormal":
+        x = (x * np.float32(1e-41)).astype(np.float32)
+    return np.ascontiguousarray(x, dtype=np.float32)
+
+
+@pytest.mark.parametrize("N,G", [(8192, 8), (4096, 8), (1500, 4), (4096, 16), (16384, 2), (16384, 4), (3000, 1),
+                                 (20000, 8)])
+@pytest.mark.parametrize("kind", ["equal", "two values", "halves", "masked", "mostly masked", "outliers", "nested",
+                                  "lowest", "wide", "infinite", "subnormal"])
+def test_global_budget_of_uneven_logits(N, G, kind):
+    """Ties, logits far from the others, ranges that cannot be divided: masks and offsets equal the
+    oracle's in the one-workgroup form (and in the passes over the chip, last size)."""
+    B, Hkv, D = 2, 2, 128
+    rng = np.random.default_rng(3 * N + G)
+    logits = _uneven(rng, (B, Hkv, N, G), kind)
+    V = torch.zeros(B, Hkv, N, D, dtype=torch.bfloat16, device=DEV)
+    c = stc.RoutedCache(B, Hkv, Hkv, D, N, G, 1, device=DEV)
+    dl = torch.from_numpy(logits).to(DEV)
+    for gk in sorted({1, (G + 1) // 2, max(1, G - 1)}):
+        stc.stc_route_and_pack_values(c.shape, stc.STC_ROUTE_GLOBAL, V, dl, None, gk, None, c.mask, c.tok_off,
+                                      c.vpacked, c.dev_status, c._ws_route)
+        torch.cuda.synchronize()
+        for b in range(B):
+            for h in range(Hkv):
+                m = O.route_mask_global(logits[b, h], N * gk)
+                assert np.array_equal(PT.host_u16(c.mask)[b, h], m), (b, h, gk)
+                assert np.array_equal(c.tok_off.cpu().numpy().view(np.uint32)[b, h], O.token_offsets(m, G))
+
+
 @pytest.mark.parametrize("N", [524288, 524289, 524289 + 700])
 def test_packed_copy_on_both_sides_of_the_scan_launch(N):
     """Up to 2048 chunks of 256 tokens the packed copy adds up the chunk sums itself, beyond a launch
