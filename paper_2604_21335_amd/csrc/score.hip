@@ -111,19 +111,18 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
 #undef STC_SCORE_GO
 }
 
-// One workgroup of 8 wavefronts scores a whole stream (NP <= 512) into LDS and then selects the
+// One workgroup of 8 wavefronts scores a whole stream (NP <= PAGES) into LDS and then selects the
 // stream's k pages itself (`score` is an optional copy of the scores): the form for many streams
 // of few pages each, where a stream per workgroup still fills the chip and the selection needs
 // no launch of its own.  RM: at most this many query heads per KV head.
-constexpr int kScoreSelectPages = 512;
-template <int D, int RM>
+template <int D, int RM, int PAGES>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void score_select_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restrict__ q,
                          float* __restrict__ score, int NP, int Hq, int Hkv, int tiles_cap,
                          int32_t* __restrict__ page_idx, int k_pages) {
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
   __shared__ __align__(16) unsigned char s_q[score_q_lds_bytes<D, RM>()];
-  __shared__ __align__(16) float s_score[kScoreSelectPages];
+  __shared__ __align__(16) float s_score[PAGES];
   const int stream = blockIdx.x;
   const int b = stream / Hkv, kvh = stream % Hkv, heads = Hq / Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -140,7 +139,7 @@ void score_select_kernel(const u32x4* __restrict__ tiles, const uint16_t* __rest
   if (score)
     for (int i = threadIdx.x; i < NP; i += 64 * WAVES) score[(size_t)stream * NP + i] = s_score[i];
   int32_t* list = page_idx + (size_t)stream * k_pages;
-  topk_block<kScoreSelectPages / (64 * WAVES), 64 * WAVES>(
+  topk_block<PAGES / (64 * WAVES), 64 * WAVES>(
       s_score, NP, k_pages, [list](int pos, int page) { list[pos] = page; });
 }
 
@@ -150,28 +149,42 @@ static int launch_score_select_d(const stc_shape_t& s, const void* q, const void
                                  hipStream_t st) {
   const int streams = s.B * s.Hkv, R = s.Hq / s.Hkv;
   const int tcap = bounds_tiles(token_cap(s));
-#define STC_SCORE_SELECT(RM)                                                                   \
-  score_select_kernel<D, RM><<<streams, 512, 0, st>>>((const u32x4*)bounds, (const uint16_t*)q, \
-                                                      score, NP, s.Hq, s.Hkv, tcap, page_idx,  \
-                                                      k_pages)
-  if (R == 1) STC_SCORE_SELECT(1);
-  else if (R == 2) STC_SCORE_SELECT(2);
-  else if (R <= 4) STC_SCORE_SELECT(4);
-  else if (R <= 8) STC_SCORE_SELECT(8);
+#define STC_SCORE_SELECT(RM, PAGES)                                                            \
+  score_select_kernel<D, RM, PAGES><<<streams, 512, 0, st>>>(                                  \
+      (const u32x4*)bounds, (const uint16_t*)q, score, NP, s.Hq, s.Hkv, tcap, page_idx, k_pages)
+#define STC_SCORE_SELECT_PAGES(RM)                                                             \
+  if (NP <= 512) STC_SCORE_SELECT(RM, 512);                                                    \
+  else STC_SCORE_SELECT(RM, 1024);
+  if (R == 1) { STC_SCORE_SELECT_PAGES(1) }
+  else if (R == 2) { STC_SCORE_SELECT_PAGES(2) }
+  else if (R <= 4) { STC_SCORE_SELECT_PAGES(4) }
+  else if (R <= 8) STC_SCORE_SELECT(8, 512);  // (score_can_select: at most 256 pages)
   else return -1;
+#undef STC_SCORE_SELECT_PAGES
 #undef STC_SCORE_SELECT
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Where the single workgroup per stream wins: on short streams, where both forms are bound by
-// their launches, and up to 512 pages with few heads per KV head where the streams just fill the
-// chip (us, against scoring and selection as two launches: 256 streams of 256 pages 10.0 / 10.8;
-// 128 of 512 at 4 heads 11.3 / 12; 256 of 512 16.7 / 15.8; 256 of 2048 at 7 heads 53 / 28).
+// Where the single workgroup per stream wins: on short streams, where both forms are bound by their
+// launches, and on longer ones with few heads per KV head while the streams fill the chip without
+// many rounds (two of the workgroups fit a CU at D = 128, four at D = 64).  Its time over that of
+// scoring and selection as two launches, bounds in the caches / out of them, 4 heads:
+//   D   pages    128 streams    192         256         320         512         1024
+//   128   257    0.81 / 0.88  0.73 / 0.81 0.74 / 0.83 0.90 / 0.89 0.97 / 0.95 0.93 / 1.02
+//         512    1.01 / 1.06  1.01 / 0.92 0.91 / 0.98 0.94 / 1.01 0.99 / 1.02 0.94 / 1.06
+//        1024    0.97 / 1.13  0.87 / 1.04 0.94 / 1.02 0.92 / 1.09 0.97 / 1.10 1.10 / 1.09
+//    64   512    0.98 / 0.97  0.87 / 0.89 0.87 / 0.94 0.88 / 0.86 0.94 / 0.95 0.91 / 0.96
+//        1024    1.07 / 1.18  1.00 / 0.96 0.83 / 0.96 0.87 / 0.99 0.94 / 1.02 0.91 / 1.01
+// 64 streams of 512 pages 1.09 / 1.15; with 7 heads 128 streams of 512 pages 1.11 / 1.18, 320 of 384
+// 1.04 / 1.07.  (256 streams of 257 pages: 8.1 us for 11.2.)  Whole steps of 512 streams: 300 pages
+// 57.6 / 60.5 us for 58.4 / 59.0, 500 pages 88.1 / 94.1 for 90.6 / 90.1.
 bool score_can_select(const stc_shape_t& s, int k_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
   const int R = s.Hq / s.Hkv, streams = s.B * s.Hkv;
   if (k_pages >= NP || R > 8) return false;
-  return NP <= 256 || (NP <= 512 && R <= 4 && streams >= 128 && streams < 256);
+  if (NP <= 256) return true;
+  if (R > 4 || streams < 128) return false;
+  return NP <= 640 && streams <= (s.D == 128 ? 384 : 1024);
 }
 
 int launch_score_select(const stc_shape_t& s, const void* q, const void* bounds, float* score,

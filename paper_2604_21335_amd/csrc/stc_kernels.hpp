@@ -45,7 +45,7 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
 int launch_score(const stc_shape_t& s, const void* q, const void* bounds, float* score,
                  bool per_head, hipStream_t st);
 // One workgroup per stream scores the stream and selects its pages (many streams of at most
-// 512 pages); `score` may be nullptr.  Only if score_can_select().
+// 640 pages); `score` may be nullptr.  Only if score_can_select().
 bool score_can_select(const stc_shape_t& s, int k_pages);
 int launch_score_select(const stc_shape_t& s, const void* q, const void* bounds, float* score,
                         int32_t* page_idx, int k_pages, hipStream_t st);

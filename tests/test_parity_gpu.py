@@ -9,6 +9,7 @@ import paper_2604_21335_amd as stc
 from oracle import stc_oracle as O
 from paper_2604_21335_amd import workloads as W
 from tests import parity as PT
+from tests import routes
 from tests.helpers import f32_to_bf16_bits, ints_bf16, randn_bf16
 
 pytestmark = pytest.mark.gpu
@@ -181,34 +182,40 @@ def test_decode_step_is_the_two_calls_in_one(B, Hkv, R, N, k):
     assert np.array_equal(idx[b, h].cpu().numpy(), O.select_pages(sc, k))
 
 
-def test_many_streams_of_2048_pages_select_in_the_scoring_workgroup():
-    """192 streams of exactly 2048 pages (the most a scoring workgroup orders by itself) and of
-    2049 (one more: separate launches): lists against the oracle on sampled streams, and the
-    scores bit for bit."""
+# streams, heads per KV head, D, pages: both sides of every line of the rule
+@pytest.mark.parametrize("B,Hkv,R,D,NP,one", [
+    (48, 4, 2, 64, 2048, False), (48, 4, 2, 64, 2049, False),
+    (1, 2, 8, 128, 256, True), (1, 2, 8, 128, 257, False), (1, 3, 1, 64, 256, True), (2, 1, 9, 64, 200, False),
+    (32, 4, 4, 128, 257, True), (32, 4, 4, 128, 511, True), (32, 4, 1, 128, 512, True), (32, 4, 4, 128, 513, True),
+    (32, 4, 3, 128, 640, True), (32, 4, 3, 128, 641, False), (127, 1, 4, 128, 300, False), (128, 1, 5, 128, 300, False),
+    (128, 3, 2, 128, 290, True), (385, 1, 2, 128, 290, False), (32, 4, 4, 64, 640, True), (32, 4, 2, 64, 641, False),
+    (256, 4, 1, 64, 260, True), (1025, 1, 1, 64, 260, False)])
+def test_selection_by_the_scoring_workgroup_and_by_a_launch_of_its_own(B, Hkv, R, D, NP, one):
+    """Lists against the oracle on sampled streams and the scores bit for bit, whichever launches make
+    them, with the scores returned and in the workspace; last pages are ragged."""
     dev = "cuda:0"
-    for N in (32768, 32769):
-        B, Hq, Hkv, D, G, k = 48, 8, 4, 64, 2, 100
-        g = torch.Generator(device=dev)
-        g.manual_seed(N)
-        K = torch.randn(B, Hkv, N, D, device=dev, generator=g).bfloat16()
-        q = torch.randn(B, Hq, D, device=dev, generator=g).bfloat16()
-        shape = stc.make_shape(B, Hq, Hkv, D, N, G, N * G)
-        bounds = torch.empty(stc.stc_bounds_bytes(shape) // 2, dtype=torch.bfloat16, device=dev)
-        stc.stc_build_page_bounds(shape, K, bounds)
-        NP = (N + 15) // 16
-        idx = torch.full((B, Hkv, k), -1, dtype=torch.int32, device=dev)
-        score = torch.full((B, Hkv, NP), float("nan"), dtype=torch.float32, device=dev)
-        stc.stc_select_pages(shape, q, bounds, k, idx, score, None)
-        idx2 = torch.full_like(idx, -1)
-        ws = torch.empty(stc.stc_workspace_bytes(shape, stc.STC_WS_SELECT, k), dtype=torch.uint8,
-                         device=dev)
-        stc.stc_select_pages(shape, q, bounds, k, idx2, None, ws)      # scores in the workspace
-        torch.cuda.synchronize()
-        assert torch.equal(idx, idx2)
-        for (b, h) in ((0, 0), (47, 3), (20, 1)):
-            sc = O.page_scores(W.bf16_bits(q[b, 2 * h:2 * h + 2]), O.page_bounds(W.bf16_bits(K[b, h])))
-            assert np.array_equal(score[b, h].cpu().numpy().view(np.uint32), sc.view(np.uint32))
-            assert np.array_equal(idx[b, h].cpu().numpy(), O.select_pages(sc, k))
+    N, G, k, Hq = 16 * NP - 7, 2, min(100, NP - 1), Hkv * R
+    assert routes.selects_with_scores(B, Hq, Hkv, D, N, k) == one
+    g = torch.Generator(device=dev)
+    g.manual_seed(N)
+    K = torch.randn(B, Hkv, N, D, device=dev, generator=g, dtype=torch.bfloat16)
+    q = torch.randn(B, Hq, D, device=dev, generator=g).bfloat16()
+    shape = stc.make_shape(B, Hq, Hkv, D, N, G, N * G)
+    bounds = torch.empty(stc.stc_bounds_bytes(shape) // 2, dtype=torch.bfloat16, device=dev)
+    stc.stc_build_page_bounds(shape, K, bounds)
+    idx = torch.full((B, Hkv, k), -1, dtype=torch.int32, device=dev)
+    score = torch.full((B, Hkv, NP), float("nan"), dtype=torch.float32, device=dev)
+    stc.stc_select_pages(shape, q, bounds, k, idx, score, None)
+    idx2 = torch.full_like(idx, -1)
+    ws = torch.empty(stc.stc_workspace_bytes(shape, stc.STC_WS_SELECT, k), dtype=torch.uint8,
+                     device=dev)
+    stc.stc_select_pages(shape, q, bounds, k, idx2, None, ws)      # scores in the workspace
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx2)
+    for (b, h) in {(0, 0), (B - 1, Hkv - 1), (B // 2, Hkv // 2)}:
+        sc = O.page_scores(W.bf16_bits(q[b, R * h:R * h + R]), O.page_bounds(W.bf16_bits(K[b, h])))
+        assert np.array_equal(score[b, h].cpu().numpy().view(np.uint32), sc.view(np.uint32))
+        assert np.array_equal(idx[b, h].cpu().numpy(), O.select_pages(sc, k))
 
 
 def test_parity_very_long_stream():
