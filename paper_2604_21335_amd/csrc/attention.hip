@@ -67,6 +67,11 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
 //   of a CU with one workgroup at D = 128, two at D = 64, so more streams than that run in
 //   rounds (320 streams of 48 pages: 41.3 / 34.4), and with fewer the chip is not full (128
 //   streams of 48 pages: 23.4 / 23.1).
+//   Lists of the query heads of one KV head share pages, which come from the caches after the first
+//   head: such launches are bound by latency more than by bandwidth and gain from several pairs
+//   only up to 3 (224 streams of 7 heads, us, against one pair per wavefront: 40 pages 14.3 / 15.8,
+//   64: 18.7 / 19.0, 128: 32.3 / 28.1; 256 streams of 4 heads, 24 pages 9.8 / 11.5, 64: 21.8 / 20.6,
+//   128: 35.3 / 31.7; of 16 heads, 32 pages 12.2 / 12.8, 64: 20.3 / 18.4).
 //   Otherwise 8 wavefronts with a pair each, which beats 4 with a pair each also where that
 //   leaves CUs idle (8 streams of 90 pages: 13.5 / 14.7).
 struct AttnPlan {
@@ -85,17 +90,21 @@ static bool long_select_shape(const stc_shape_t& s, int k_pages) {
 // one at D = 128, two at D = 64).
 static int resident_streams(const stc_shape_t& s) { return s.D == 128 ? 256 : 512; }
 
-static AttnPlan attention_plan(const stc_shape_t& s, int k_pages) {
+// kv_div query heads per KV head with page lists of their own (each of them a stream here).
+static AttnPlan attention_plan(const stc_shape_t& s, int k_pages, int kv_div = 1) {
   const int streams = s.B * s.Hkv;
   AttnPlan p{k_pages <= 8 ? 4 : 8, 1, 0};
-  if (k_pages > 16 && k_pages <= 16 * kMaxPairs && streams >= 192 &&
+  const int max_pairs = kv_div > 1 ? kMaxPairsShared : kMaxPairs;
+  if (k_pages > 16 && k_pages <= 16 * max_pairs && streams >= 192 &&
       streams <= resident_streams(s))
     p.pairs = (k_pages + 15) / 16;
   p.splits = (k_pages + p.waves * 2 * p.pairs - 1) / (p.waves * 2 * p.pairs);
   return p;
 }
 
-int attention_splits(const stc_shape_t& s, int k_pages) { return attention_plan(s, k_pages).splits; }
+int attention_splits(const stc_shape_t& s, int k_pages, int kv_div) {
+  return attention_plan(s, k_pages, kv_div).splits;
+}
 
 // The per-query-head form is the ordinary launch on a shape with one KV head per query head
 // (the kernel then maps kv_div of those onto one cache).
@@ -221,7 +230,8 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
   const int NP = (s.N + kPage - 1) / kPage;
   const int streams = s.B * s.Hkv;
   const int tail_pages = (n_tail + kPage - 1) / kPage;
-  const AttnPlan plan = attention_plan(s, k_pages + tail_pages);
+  const int kv_div = s.Hkv / s0.Hkv;
+  const AttnPlan plan = attention_plan(s, k_pages + tail_pages, kv_div);
   AttnLaunch a{attn_params(s, s0, plan, q, K, vpacked, mask, tok_off, page_idx, k_pages, K_tail,
                            V_tail, n_tail, tail_cap, page_heads, sel_score, sel_list, out, ws),
                dim3(plan.splits, streams), st};
@@ -233,7 +243,7 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
     a.p.nx = kXcds;
     a.grid = dim3(plan.splits * streams, 1);
   }
-  const bool stream_loads = streaming_loads(s, k_pages, tail_pages, s.Hkv / s0.Hkv);
+  const bool stream_loads = streaming_loads(s, k_pages, tail_pages, kv_div);
   const bool tail = tail_pages > 0, select = sel_score != nullptr;
   const int rc = s.D == 128 ? attn_dispatch<128>(a, plan, tail, select, stream_loads)
                             : attn_dispatch<64>(a, plan, tail, select, stream_loads);

@@ -35,6 +35,7 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;  // "no token seen yet" running maximum
 constexpr int kMaxPairs = 8;         // pairs of pages per wavefront at most
+constexpr int kMaxPairsShared = 3;   // the same where heads of a KV head have lists of their own
 constexpr int kTailPage = 1 << 30;   // flag of a page slot that lies in the uncompressed tail
 
 // Partial result of one (query head, split): [0] running max (base-2 logits),

@@ -22,3 +22,15 @@ def test_router_forms_are_all_reached():
     for G in (1, 2, 4, 8, 16):
         assert {routes.router_form(B, N, 1024, G) for B, N in [(1, 100), (1, 4000), (1, 23000), (4, 32768)]} == {
             routes.SPLIT8, routes.SPLIT16, routes.OWN16, routes.OWN32}
+
+
+@pytest.mark.parametrize("D,streams", [(128, 192), (128, 224), (128, 256), (64, 192), (64, 512)])
+def test_several_pairs_of_pages_per_wavefront(D, streams):
+    """Up to 8 where a stream's pages are its own, up to 3 where heads of a KV head share pages; one
+    where the streams do not fill the chip or do not all fit on it."""
+    for k in (16, 17, 48, 49, 64, 128, 129):
+        full = (k + 15) // 16
+        assert routes.pairs(streams, 1, 1, D, 4096, k) == (full if k <= 128 else 1)
+        assert routes.pairs(streams // 4, 4, 4, D, 4096, k, kv_div=4) == (full if k <= 48 else 1)
+        assert routes.pairs(191, 1, 1, D, 4096, k) == 1
+        assert routes.pairs(513, 1, 1, D, 4096, k) == 1
