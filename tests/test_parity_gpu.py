@@ -37,11 +37,11 @@ CASES = [
     (1, 8, 1, 128, 777, 16, 13),       # GQA 8:1, G = 16 (8-wide groups)
     (3, 6, 3, 64, 530, 8, 9),          # GQA 2:1, D = 64 with 8-wide groups
     (1, 4, 1, 128, 4096, 1, 64),       # G = 1
-    (1, 3, 1, 64, 300, 2, 5),          # group size 3: generic score kernel
+    (1, 3, 1, 64, 300, 2, 5),          # group size 3: the scoring table has an unused head
     (2, 2, 2, 128, 16, 8, 1),          # a single page
     (1, 1, 1, 64, 5, 4, 1),            # fewer tokens than a page
     (1, 16, 1, 128, 640, 4, 12),       # 16 query heads on one KV head
-    (48, 4, 4, 64, 600, 4, 9),         # 192 streams: a workgroup scores and selects a stream
+    (48, 4, 4, 64, 600, 4, 9),         # 192 streams: a workgroup does a stream's whole step
     (49, 28, 4, 128, 1000, 8, 20),     # the same with 7 heads per KV head
     (64, 6, 3, 128, 20, 8, 1),         # 192 streams of two pages
     (2, 10, 2, 128, 1300, 8, 17),      # GQA 5:1 at D = 128: query operands in shared memory
@@ -145,18 +145,23 @@ def test_missing_page_list_means_leading_pages():
     assert np.array_equal(o.cpu().numpy(), hip["out"])
 
 
-@pytest.mark.parametrize("B,Hkv,R,N,k", [
-    (16, 4, 2, 32768, 128),     # 64 streams x 8 workgroups: selection inside the attention kernel
-    (16, 4, 2, 32768, 144),     # 9 workgroups per stream: selection launch + attention launch
-    (2, 2, 7, 32784, 128),      # 2049 pages: one too many for the keys held in registers
-    (3, 1, 4, 4000, 7),         # workgroups of 4 wavefronts, ragged last page
-    (1, 2, 1, 3333, 100),       # 7 workgroups of 8 wavefronts, ragged list end
+@pytest.mark.parametrize("B,Hkv,R,N,k,launches", [
+    (16, 4, 2, 32768, 128, "in attention"),     # 64 streams x 8 workgroups: selection inside the attention kernel
+    (16, 4, 2, 32768, 144, "three"),            # 9 workgroups per stream: selection launch + attention launch
+    (2, 2, 7, 32784, 128, "in attention"),      # 2049 pages: 16 keys per thread, four streams
+    (16, 4, 2, 32784, 128, "three"),            # too many workgroups for that
+    (2, 2, 7, 131072, 200, "in attention"),     # 8192 pages
+    (2, 2, 7, 131088, 200, "three"),            # 8193: more than it orders
+    (3, 1, 4, 4000, 7, "one"),                  # 250 pages: one launch, ragged last page
+    (3, 1, 4, 4500, 7, "in attention"),         # 282 pages: workgroups of 4 wavefronts
+    (1, 2, 1, 3333, 100, "in attention"),       # 7 workgroups of 8 wavefronts, ragged list end
 ])
-def test_decode_step_is_the_two_calls_in_one(B, Hkv, R, N, k):
+def test_decode_step_is_the_two_calls_in_one(B, Hkv, R, N, k, launches):
     """stc_decode_step through the C ABI with a workspace of its own, used twice without
     clearing: page list and output bit for bit those of stc_select_pages followed by
-    stc_decode_attention, on both sides of every switch between its two launch plans."""
+    stc_decode_attention, on both sides of the switches between its launch plans."""
     Hq, D, G = Hkv * R, 128, 8
+    assert routes.step(B, Hq, Hkv, D, N, k) == launches
     dev = "cuda:0"
     g = torch.Generator(device=dev)
     g.manual_seed(N + k)
@@ -273,8 +278,8 @@ def test_selection_ties_and_signed_zero():
 @pytest.mark.parametrize("Hq,Hkv,D", [(3, 1, 128), (5, 1, 64), (12, 2, 128), (6, 1, 64), (9, 1, 64),
                                       (16, 1, 128)])
 def test_scores_for_every_head_group_size(Hq, Hkv, D):
-    """Page scores bit for bit for group sizes served by the matrix-core kernel (1..8 heads
-    per KV head) and by the general one (9..16); N leaves a ragged last page and tile."""
+    """Page scores bit for bit for group sizes that have a scoring kernel of their own (1..8 heads per
+    KV head) and for those that share one (9..16); N leaves a ragged last page and tile."""
     B, N, G = 2, 16 * 37 + 5, 4
     K, V, q, logits, kcount = _rand_case(40 + Hq, B, Hq, Hkv, D, N, G, outliers=True)
     hip = PT.run_hip(K, V, q, G, 9, logits=logits, kcount=kcount)
@@ -613,7 +618,7 @@ def _plant_subnormals(rng, bits, frac=0.12):
                                        (2, 128, 2.0 ** -70)])
 def test_subnormal_inputs_count_as_zero_in_page_scores(R, D, scale):
     """Keys and queries that are subnormal as bf16 are zeros for the page scores (bounds keep
-    their bit patterns): matrix-core kernel and the one-head-at-a-time kernel against the
+    their bit patterns): the kernels of up to 8 heads per KV head and the one of 9..16 against the
     oracle, bit for bit.  With large queries the products of subnormal inputs would be ordinary
     floats, so a kernel that multiplied them would differ in many bits; with tiny queries the
     products of normal inputs lie in the subnormal float range and must come out exact."""
@@ -933,12 +938,17 @@ def test_workload_full_size_every_stream_selection(name):
     assert worst <= PT.TIGHT
 
 
-@pytest.mark.parametrize("B,k_pages,tail_cap", [(8, 108, 128), (2, 60, 96)])
-def test_tail_decode_across_the_launch_plan_switch(B, k_pages, tail_cap):
-    """Buffers sized once for the full tail must serve every tail length: with few streams the
-    attention launch changes its plan (wavefronts per workgroup, hence splits) while the tail
-    grows.  The step is run at tail lengths on both sides of the switch, with one workspace."""
+# (a workgroup more per stream while the tail grows; from one launch to attention that selects,
+# from one launch and 8 pairs of pages per wavefront to splits; from 4 wavefronts to 8)
+@pytest.mark.parametrize("B,k_pages,tail_cap,plans", [(8, 108, 128, 1), (2, 60, 96, 1), (1, 12, 128, 2), (48, 124, 128, 2),
+                                                      (1, 7, 48, 1)])
+def test_tail_decode_across_the_launch_plan_switch(B, k_pages, tail_cap, plans):
+    """Buffers sized once for the full tail must serve every tail length: the launches and the
+    workgroups per stream change while the tail grows.  The step is run at tail lengths on both
+    sides of the switch, with one workspace."""
     Hq, Hkv, D, G, N = 28, 4, 128, 8, 16 * 140
+    lengths = sorted(n for n in {0, 1, 40, 64, 65, tail_cap} if n <= tail_cap)
+    assert len({routes.step(B, Hq, Hkv, D, N, k_pages, n) for n in lengths}) == plans
     K, V, q, logits, kcount = _rand_case(300 + B, B, Hq, Hkv, D, N, G)
     rng = np.random.default_rng(301)
     Kt, Vt = randn_bf16(rng, (B, Hkv, tail_cap, D)), randn_bf16(rng, (B, Hkv, tail_cap, D))
@@ -949,7 +959,7 @@ def test_tail_decode_across_the_launch_plan_switch(B, k_pages, tail_cap):
     c.K_tail.copy_(PT.to_dev_bf16(Kt))
     c.V_tail.copy_(PT.to_dev_bf16(Vt))
     R = Hq // Hkv
-    for n_tail in (0, 1, 40, 64, 65, tail_cap):
+    for n_tail in lengths:
         c.n_tail = n_tail
         for one_call in (True, False):
             c.out.fill_(float("nan"))
