@@ -4,8 +4,11 @@
 
 namespace stc {
 
+// No bound on the registers: several pairs at D = 64 held to 128 of them, for two workgroups per CU,
+// spill 2 to 11 and are slower at every number of streams (512 streams of 40 pages 15.1 us, 14.1
+// without; 256 streams of 64 pages and a tail 16.3, 13.3; 512 of 128 pages 37.8, 36.8).
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
-__global__ __launch_bounds__(64 * WAVES, MULTI && D == 64 ? 4 : 1) void attn_mfma_kernel(const AttnParams P) {
+__global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams P) {
   extern __shared__ __align__(16) unsigned char lds[];  // WAVES * AttnCfg<D>::WAVE_LDS bytes
   int stream = blockIdx.y, split = blockIdx.x;
   if (P.nx > 0) {

@@ -12,6 +12,9 @@ namespace stc {
 // RM: query heads per KV head are at most this; `heads` = their number.
 // Bound by memory while many workgroups are in different parts, by the chain of dependent
 // accesses of one stream where there are few.
+// At D = 64 two workgroups share a CU, with 128 registers each; without a tail one register is
+// spilled for it (512 streams of 512 pages, 64 kept 36.5 us, 39.2 with one workgroup per CU; of 250
+// pages, 30 kept 19.6, 22.5; but 256 streams of 512 pages 20.3, 19.6).
 template <int D, int RM, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnParams P,
                                                    const score_u32x4* __restrict__ tiles,
