@@ -90,7 +90,8 @@ static bool long_select_shape(const stc_shape_t& s, int k_pages) {
 }
 
 // Workgroups that take a whole stream each and are resident at once (the registers of a CU hold
-// one at D = 128, two at D = 64).
+// one at D = 128, two at D = 64 without a tail; with one the two halves of 512 streams follow
+// each other, which is no slower than splits: 26.2 us for 30.2 at 64 pages).
 static int resident_streams(const stc_shape_t& s) { return s.D == 128 ? 256 : 512; }
 
 // kv_div query heads per KV head with page lists of their own (each of them a stream here).
@@ -208,12 +209,20 @@ static AttnParams attn_params(const stc_shape_t& s, const stc_shape_t& s0, const
                     s.Hkv / s0.Hkv, page_heads, token_cap(s), sel_score, sel_list, plan.pairs, 0};
 }
 
-// K rows and value runs are read once per step.  Where the keys and bounds of a step are a good
-// part of what the last-level cache holds (256 MB), they are read with streaming loads, which leave
-// the caches alone (256 streams of 64 pages, 104 MB of keys and values: 20.9 against 23.2 us;
-// 2048 streams of 13 pages, 172 MB: 30.1 against 32.7; 64 of 128 pages, 50 MB, beside 67 MB of
-// bounds: 16.2 against 17.1).  Smaller steps may find them in that cache, and there streaming
-// loads cost 5 % (128 streams of 40 pages, 21 MB of keys: 21.1 us per step against 19.8).
+// K rows and value runs are read once per step.  What a launch cannot know is whether they still lie
+// in the last-level cache (256 MB): behind the other layers of a decoder they do not, where one
+// cache is stepped by itself they do.  us per step with ordinary / streaming loads of them:
+//   keys + bounds, MiB             out of the cache     in it
+//    8 + 15   40 streams of  751    18.5 / 18.5        14.8 / 15.0
+//   20 + 16  128 of  250            22.5 / 22.0        19.8 / 19.0
+//   16 + 32   32 of 2048            22.9 / 22.5        20.8 / 21.0
+//   38 + 31  160 of  400            30.8 / 30.2        25.9 / 26.8
+//   64 + 32  256 of  256            32.4 / 29.4        26.8 / 28.6
+//   32 + 64   64 of 2048            32.8 / 31.9        30.7 / 30.1
+//   75 + 47  320 of  300            44.4 / 42.7        37.2 / 39.8
+//   64 + 64  256 of  512            37.8 / 34.2        32.0 / 32.7
+// Below 80 MiB the two differ by 2 % out of the cache and by 4 % either way in it; above, streaming
+// loads gain 3 to 10 % out of the cache, for which a step of one cache by itself pays up to 7 %.
 // Pages that several query heads of a KV head select (kv_div > 1) count once: they come from the
 // caches after the first.
 static bool streaming_loads(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
@@ -273,7 +282,7 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
 // page), or enough streams that the chip is full either way.  Step in us, one launch / several:
 // 8 streams of 64 pages 8.0 / 9.5; 32 of 125 pages, 16 kept 10.1 / 11.1; 256 of 256 pages, 64 kept
 // 29.4 / 30.9; D = 64, 256 of 256 pages, 32 kept 13.6 / 16.2; 256 of 1024 pages with 7 heads, 96
-// kept 54.2 / 54.  Not: 8 streams of 500 pages 12.6 / 11.0; 64 of 250 pages with 7 heads 13.7 /
+// kept 54.2 / 54 is where the two meet.  Not: 8 streams of 500 pages 12.6 / 11.0; 64 of 250 pages with 7 heads 13.7 /
 // 13.3; 512 of 250 pages at D = 128 (two rounds) 31.8 / 27.3.
 bool step_is_one_kernel(const stc_shape_t& s, int k_pages, int tail_pages) {
   const int NP = (s.N + kPage - 1) / kPage, streams = s.B * s.Hkv, R = s.Hq / s.Hkv;

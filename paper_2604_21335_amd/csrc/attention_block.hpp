@@ -77,8 +77,9 @@ struct AttnCfg {
 static __device__ u32x4 stc_zero16 = {0u, 0u, 0u, 0u};  // never written
 
 
-// One wavefront takes one pair of page slots of one stream; the WAVES wavefronts of a workgroup
-// then merge their partial results in LDS.
+// One wavefront takes one pair of page slots of one stream, or, with MULTI, P.pairs adjacent pairs
+// one after the other (up to kMaxPairs), each a partial result of its own; the WAVES wavefronts of
+// a workgroup then merge their partial results in LDS.
 // Page slots are the selected pages of the compressed cache followed, with TAIL, by the pages
 // of the uncompressed tail; kv_div query-head streams may share one KV head's cache.
 //

@@ -35,16 +35,18 @@ constexpr int kBoundsStreamWaves = 7;  // streams of at most this many wavefront
 // on packed 16-bit integers, first over a lane's own rows, then across lanes by swapping halves
 // of register pairs, which leaves every lane with the minimum and maximum of two channels.
 // Bound by memory (K is read once, 1/8 of it written).  K is read with streaming loads, which
-// leave the caches alone, also where it was written just before (2048 streams of 208 tokens,
-// 122 MB, behind their compaction: 23.5 us, 30.3 with ordinary loads).  Measured on 64
+// leave the caches alone.  Where K was written just before, ordinary loads would be faster for this
+// launch (2048 streams of 208 tokens, 109 MB, behind their copy 19.9 us, 21.5), but they push out
+// values written beside the keys: compaction of both, bounds and packing of that shape 137.8 us,
+// 129.5 with streaming loads.  Measured on 64
 // streams of 32768 tokens (604 MB): 95.8 us (6.3 TB/s) against 106.5 with ordinary loads, 113
 // with 4 pages per wavefront, 124-137 with wavefronts that walk a run of pages, and 131 for
 // the form before, in which a thread walked the 16 rows of a page four loads at a time (a request
 // was four pieces of 256 bytes in four pages).
 // A workgroup is 4 wavefronts.  A stream of up to 7 is one workgroup that has no wavefronts for the
 // padding pages of its last tile: the one with the last page writes their zeros (2048 streams of
-// 130 tokens, 9 pages in two tiles: 16.2 us, 19.4 with wavefronts for the padding; at 8 wavefronts two workgroups are as
-// good, 24.4 us, and one of 8 is slower, 25.9).
+// 130 tokens, 9 pages in two tiles: 16.2 us, 19.4 with wavefronts for the padding; 8 wavefronts are
+// better as two workgroups, 24.4 us, than as one, 25.9).
 template <int D>
 __global__ __launch_bounds__(64 * kBoundsStreamWaves) void bounds_kernel(
     const bounds_u32x4* __restrict__ K, uint32_t* __restrict__ bounds, int N, int NP, int Ncap) {

@@ -70,14 +70,23 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const u32x4* t4 = (const u32x4*)bounds;
   const uint16_t* q16 = (const uint16_t*)q;
   // Query operands in shared memory, one tile requested at a time per wavefront (measured: two
-  // requested ahead is slower at every grid), about 1024 workgroups.  Bounds of 64 MiB and more are
-  // read with streaming loads (64 streams of 2048 pages, 67 MB: 12.4 us; 13.2 with 2048
-  // workgroups, 13.9 with ordinary loads).  Smaller ones may still lie in the last-level cache,
-  // where ordinary loads are faster (4 streams of 8192 pages, 17 MB: 5.4 us against 6.1; with
-  // 2048 workgroups 256 streams of 256 pages take 7.3 us instead of 6.5).
+  // requested ahead is slower at every grid), about 4096 wavefronts (512 workgroups of 8 or 1024 of
+  // 4).  Streaming loads from 64 MiB of bounds on.  us, bounds in the caches / out of them:
+  //                                    ordinary loads, wavefronts           streaming loads
+  //    MiB  streams x pages, heads    2048         4096         8192              4096
+  //     16   128 x  250, 4          4.0 /  5.9   3.6 /  5.5   3.6 /  5.6       4.2 /  5.8
+  //     32   256 x  256, 4          5.3 /  8.7   4.8 /  7.6   5.1 /  8.1       6.8 /  7.5
+  //     32    32 x 2048, 7          6.6 /  9.1   6.2 /  7.8   6.2 /  8.5       7.7 /  8.2
+  //     64    64 x 2048, 7         12.5 / 15.8  12.2 / 13.4  12.3 / 13.3      12.3 / 12.8
+  //     64   256 x 1024, 1, D = 64 11.5 / 16.9  11.5 / 14.9  11.2 / 14.0      12.5 / 13.1
+  //    128   256 x 1024, 4         20.7 / 25.6  20.3 / 25.1  20.4 / 25.5      20.9 / 21.9
+  // So up to 32 MiB ordinary loads are no slower even where nothing is cached, and much faster
+  // where it is; from 64 MiB on streaming ones gain 5 to 13 % where a decoder's other layers have
+  // pushed the bounds out, and lose 1 to 8 % where a single cache is stepped by itself.
   const bool stream_loads = (long long)streams * ntiles * T16 * 16 >= (64ll << 20);
   // Up to 4 heads per KV head, whose tiles take half as long, half as many workgroups of twice the
-  // size start sooner (128 streams of 250 pages: 19.9 against 20.4 us per step).
+  // size start sooner (128 streams of 250 pages: 19.9 against 20.4 us per step; the figures of 4
+  // heads above are of this form).
   const int waves = R <= 4 ? 8 : 4;
   const int want = max(1, 4096 / waves / streams);
   int tp = (ntiles + want - 1) / want;
