@@ -113,8 +113,6 @@ __global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_
   const bool bit2 = lane & 4, bit3 = lane & 8;
   const int t_first = blockIdx.x * C::BLOCK_TOKENS + (SPLIT ? 0 : wave * C::WAVE_TOKENS) +
                       4 * tq + j;
-  if constexpr (!SPLIT)  // a wavefront behind the last token (no barriers in this form)
-    if (blockIdx.x * C::BLOCK_TOKENS + wave * C::WAVE_TOKENS >= N) return;
   const int nc = d_model / 128;
   const int row16 = d_model / 8;  // 16-byte pieces per row
 
@@ -243,50 +241,62 @@ __global__ __launch_bounds__((RouterCfg<G, TG, SPLIT>::WAVES * 64)) void router_
 
 // Tokens per wavefront and who shares them.  Measured, us, as split 8 / split 16 / own 16 / own 32:
 //   channels tokens     4 groups                     8 groups                     16 groups
-//   3584       1000    6.3/  8.1/ 21 / 34           8.1/ 11  / 28 / 51         12.2/ 16  / 51 / 88
-//              6000   13.4/ 13.6/ 21 / 35          19.0/ 20.4/ 29 / 51         34  / 32  / 51 / 89
-//             12000   23  / 19  / 21 / 34          34  / 29.8/ 29 / 51         65  / 47  / 51 / 89
-//             24000   40  / 33  / 40 / 35          59  / 56  / 52 / 51        126  / 92  / 89 / 90
-//             32768   56  / 45  / 42 / 38          83  / 78  / 55 / 54        170  /125  / 92 / 92
-//        64 x   576   62  / 51  / 61 / 69          91  / 86  / 81 / 87        191  /140  /131 /152
-//             65536  120  / 95  / 92 / 87         166  /158  /132 /100        336  /253  /193 /167
+//   3584       4096   10.7/  9.4/ 22 / 35          14.5/ 12.2/ 29 / 51         25.1/ 18.9/ 52 / 90
+//             12000   24  / 20  / 22 / 35          35  / 31  / 30 / 51         67  / 49  / 52 / 90
+//             20000   36  / 29  / 40 / 35          53  / 49  / 52 / 51        109  / 78  / 88 / 90
+//             32768   56  / 45  / 42 / 38          81  / 78  / 55 / 55        171  /124  / 92 / 93
+//             40000   69  / 57  / 64 / 71         103  / 98  / 82 / 88        212  /160  /132 /154
+//             65536  118  / 92  / 92 / 87         164  /159  /134 / 99        340  /254  /184 /161
 //            524288  883  /698  /676 /642        1218  /1202 /906 /790       2644  /1972 /1387/1220
-//   1024       6000    5.5/  5.7/7.8/ 12           7.7/  8.8/ 10 / 17         14.2/ 12.7/ 17 / 29
-//             12000    8.8/  7.7/8.4/ 12          13.5/ 12.6/ 11 / 17         26  / 18.5/ 18 / 29
-//             24000   17  / 15  / 14 / 13          26  / 25  / 17 / 18         49  / 37  / 29 / 29
-//    512      12000    7.8/  6.7/5.4/ 7.9         11.5/ 9.3/6.6/10.4           19  / 13.4/ 11 / 17
-// Few tokens are bound by the chain of chunks of a wavefront, which the split form cuts to an eighth
-// (the more chunks there are, the longer it wins); many by the weights' preparation per wavefront,
-// which more tokens share.  The last form's wavefronts fill a SIMD each (64 x 576 tokens are a second
-// round of an eighth).  A wavefront's tokens are of one batch element: elements of few tokens take the
-// form that they fill (1024 channels, 8 groups, elements of 1 token: 32768 of them 201 / 408 / 232 /
-// 545; of 13: 2048 of them 33 / 31 / 21 / 43; of 40: 3000 of them 116 / 132 / 72 / 117; of 65: 512 of
-// them 37 / 39 / 38 / 27).
+//   1024       4096    5.1/  4.9/8.4/ 13           6.3/  6.0/ 11 / 18         10.6/  7.9/ 18 / 29
+//              8000    7.1/  6.3/8.8/ 13          10.1/  9.7/ 11 / 18         19.0/ 13.7/ 18 / 29
+//             16384   12.4/ 10.4/9.2/ 13          18.3/ 17.4/ 12 / 18           35  / 26  / 19 / 30
+//             40000   25  / 23  / 20 / 23          42  / 40  / 27 / 29          82  / 60  / 44 / 50
+//         500 x  40   14.7/ 14.7/ 12 / 17          23  / 25  / 16 / 26          42  / 37  / 29 / 45
+//        5000 x   1   18.9/ 29  / 24 / 36          31  / 63  / 33 / 60          76  /103  / 63 /104
+// The time goes in rounds of one workgroup to a CU (a wavefront that has its workgroup for itself: to
+// a SIMD).  Of the first round the split forms see next to nothing, being bound by latency there: the
+// chain of chunks of a wavefront is an eighth of the other two forms'.  Later rounds cost the chunks
+// times a constant of form and groups, which falls with the tokens that share a preparation of the
+// weights.  The switch is where these lines cross: over 792 sizes (700 to 140000 tokens in elements of
+// 1 to 98304, 256 to 8192 channels, 1 to 16 groups) the form taken is 1 % above the best in the mean,
+// and 10 % and more above it in 19.
 RouterForm router_form(int B, int N, int d_model, int G) {
-  const long long tokens = (long long)B * N;
-  const int chunks = d_model / 128;
-  if (tokens < 3000 || N <= 8) return kSplit8;
-  const int split_max = G <= 4 ? min(24000, 1600 * chunks)
-                               : min(12000, 4000 + (G == 8 ? 600 : 1200) * chunks);
-  if (tokens < split_max) return kSplit16;
-  constexpr int kSimds = 1024;
-  const long long waves = (long long)B * ((N + 31) / 32);  // of the last form
-  const bool many = waves >= kSimds * 4 / 3;               // no short second round
-  if (G <= 4) {
-    if (N >= 64 && tokens >= 24000 && waves <= kSimds) return kOwn32;
-    if (N >= 64 && chunks >= 16 && waves < kSimds * 7 / 4) return kSplit16;
-  }
-  return N >= 64 && many ? kOwn32 : kOwn16;
+  // per round and chunk: G <= 4, 8, 16
+  static constexpr int kCost[4][3] = {{58, 90, 183}, {94, 188, 307}, {55, 72, 138}, {98, 132, 235}};
+  const int chunks = d_model / 128, groups = G <= 4 ? 0 : G == 8 ? 1 : 2;
+  auto blocks = [&](int tokens) { return (long long)B * ((N + tokens - 1) / tokens); };
+  auto rounds = [](long long n, int at_once) { return (n + at_once - 1) / at_once; };
+  auto split = [&](RouterForm f, int tokens) {
+    return 10 * (max(chunks, 8) + 10) * kCost[f][groups] * (rounds(blocks(tokens), 256) - 1);
+  };
+  auto own = [&](RouterForm f, int tokens, int tenths) {
+    const long long n = N <= tokens ? rounds(B, 1024) : rounds(blocks(4 * tokens), 256);
+    return 8 * (chunks + 3) * kCost[f][groups] * (10 * n - tenths);
+  };
+  RouterForm form = kSplit8;
+  long long cost = split(kSplit8, 8);
+  auto take = [&](RouterForm f, long long c) {
+    if (c < cost) form = f, cost = c;
+  };
+  take(kSplit16, split(kSplit16, 16));
+  take(kOwn16, own(kOwn16, 16, 3));
+  // (few groups of long rows are bound by the reads: 64 chunks of 4 groups, 131072 tokens: 477 / 392 /
+  // 437 / 493)
+  if (G > 4 || chunks <= 32) take(kOwn32, own(kOwn32, 32, 0));
+  return form;
 }
 
 int launch_router_logits(const void* h, const void* W, const float* bias, int bias_stride,
                          float* logits, int B, int Hkv, int N, int d_model, int G,
                          hipStream_t st) {
+  // a batch element of fewer tokens than a workgroup's has no wavefronts behind its last token
+  auto waves = [&](int tokens) { return min(4, (N + tokens - 1) / tokens); };
 #define STC_ROUTER_GO(GG, TG, SPLIT)                                                            \
   router_logits_kernel<GG, TG, SPLIT>                                                           \
       <<<dim3((N + RouterCfg<GG, TG, SPLIT>::BLOCK_TOKENS - 1) /                                \
                   RouterCfg<GG, TG, SPLIT>::BLOCK_TOKENS, B),                                   \
-         RouterCfg<GG, TG, SPLIT>::WAVES * 64, 0, st>>>(                                        \
+         (SPLIT ? kSplitWaves : waves(RouterCfg<GG, TG, SPLIT>::WAVE_TOKENS)) * 64, 0, st>>>(  \
           (const router_u32x4*)h, (const router_u32x4*)W, bias, logits, N, d_model, Hkv,        \
           bias_stride)
   const RouterForm form = router_form(B, N, d_model, G);

@@ -39,12 +39,14 @@ def test_router_logits_on_both_sides_of_every_rule(B, N, dm, G):
 
 
 @pytest.mark.parametrize("B,N,dm,G,form", [
-    (3001, 1, 128, 8, routes.SPLIT8), (400, 8, 256, 4, routes.SPLIT8), (400, 9, 256, 4, routes.OWN16),
-    (600, 9, 256, 16, routes.SPLIT16), (300, 33, 128, 8, routes.OWN16), (300, 63, 256, 2, routes.OWN16),
-    (454, 65, 128, 8, routes.OWN16), (455, 65, 128, 8, routes.OWN32), (455, 65, 128, 16, routes.OWN32),
-    (1, 23999, 128, 4, routes.OWN16), (1, 24000, 128, 4, routes.OWN32), (1, 32769, 128, 2, routes.OWN16),
-    (1, 43649, 128, 1, routes.OWN32), (1, 32769, 2048, 4, routes.SPLIT16), (1, 57313, 2048, 1, routes.OWN32),
-    (1, 43681, 256, 16, routes.OWN32), (7, 6241, 128, 16, routes.OWN32)])
+    (3001, 1, 128, 8, routes.OWN16), (3001, 1, 1024, 8, routes.OWN16), (400, 8, 256, 4, routes.SPLIT8),
+    (1, 2048, 128, 4, routes.SPLIT8), (1, 2049, 128, 4, routes.SPLIT16), (2049, 1, 1024, 16, routes.SPLIT8),
+    (600, 9, 256, 16, routes.OWN16), (300, 17, 128, 8, routes.OWN16), (300, 33, 128, 8, routes.OWN16),
+    (300, 63, 256, 2, routes.OWN16), (455, 65, 128, 16, routes.OWN32), (400, 97, 128, 4, routes.OWN32),
+    (3001, 1, 3584, 8, routes.SPLIT8),
+    (1, 24001, 128, 4, routes.OWN16), (1, 32769, 128, 2, routes.OWN16), (1, 32769, 2048, 4, routes.SPLIT16),
+    (1, 57313, 2048, 1, routes.OWN32), (1, 43681, 256, 16, routes.OWN16), (7, 6241, 128, 16, routes.OWN16),
+    (1, 65535, 128, 8, routes.OWN32)])
 def test_router_logits_of_many_elements_and_of_every_form(B, N, dm, G, form):
     """Elements that end inside a wavefront or leave wavefronts of a workgroup without tokens, and both
     sides of the lines between the forms: the first, last and some other tokens bit for bit, every

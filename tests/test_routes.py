@@ -20,7 +20,7 @@ def test_router_form_fits_the_tokens_of_a_batch_element(G, dm):
 
 def test_router_forms_are_all_reached():
     for G in (1, 2, 4, 8, 16):
-        assert {routes.router_form(B, N, 1024, G) for B, N in [(1, 100), (1, 4000), (1, 23000), (4, 32768)]} == {
+        assert {routes.router_form(B, N, 1024, G) for B, N in [(1, 100), (1, 4000), (1, 16384), (4, 32768)]} == {
             routes.SPLIT8, routes.SPLIT16, routes.OWN16, routes.OWN32}
 
 
