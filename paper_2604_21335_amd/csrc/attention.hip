@@ -19,7 +19,8 @@ __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams 
     split = slot % P.splits;
   }
   attn_block<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>(
-      P, stream, split, lds, SELECT_IPT > 0 ? P.sel_score + (size_t)stream * P.NP : nullptr);
+      P, stream, split, lds, SELECT_IPT > 0 ? P.sel_score + (size_t)stream * P.NP : nullptr,
+      (TopkLds<SELECT_IPT, 64 * WAVES>*)lds);
 }
 
 // Merge the split partials of one query head in ascending split order.  Each
@@ -140,6 +141,8 @@ template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
 int attn_go(const AttnLaunch& a) {
   // workgroups of 8 wavefronts at D = 128 need more than the default 64 KiB of LDS
   constexpr int lds_bytes = WAVES * AttnCfg<D>::WAVE_LDS;
+  static_assert(SELECT_IPT == 0 || lds_bytes >= (int)sizeof(TopkLds<SELECT_IPT, 64 * WAVES>),
+                "the selection uses the same memory");
   static std::atomic<uint64_t> allowed{0};
   if (!allow_dynamic_lds((const void*)attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>,
                          lds_bytes, allowed))

@@ -49,12 +49,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // round to nearest even
 }
 
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int D>
 struct AttnCfg {
   static constexpr int KC = D / 32;         // QK MFMAs per page (32 channels each)
@@ -135,11 +129,12 @@ int launch_step_kernel(const AttnParams& p, int D, int streams, const void* boun
                        float* score, bool tail, bool stream_loads, hipStream_t st);
 
 // The work of one workgroup: split `split` of stream `stream`.  `lds` = WAVES * WAVE_LDS bytes
-// of shared memory.  sel_score (SELECT_IPT > 0) = the stream's page scores; they may lie in
-// `lds`, which is written only after they have been read.
+// of shared memory.  sel_score (SELECT_IPT > 0) = the stream's page scores; they and the memory
+// of the selection, sel_lds, may lie in `lds`, which is written only after the selection.
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
 __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream, const int split,
-                                           unsigned char* lds, const float* sel_score) {
+                                           unsigned char* lds, const float* sel_score,
+                                           TopkLds<SELECT_IPT, 64 * WAVES>* sel_lds) {
   using C = AttnCfg<D>;
   const int ppw = MULTI ? 2 * P.pairs : 2;  // pages per wavefront
   const uint16_t* __restrict__ q = P.q;
@@ -204,20 +199,18 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     }
   }
   // (a workgroup whose page slots all lie in the uncompressed tail needs no list)
-  if constexpr (SELECT_IPT > 0) if (split * WAVES * ppw < k_pages) {
-    __shared__ int32_t s_pages[WAVES * 2 * (MULTI ? kMaxPairs : 1)];
+  const int lo = split * WAVES * ppw;  // first list position of this workgroup
+  __shared__ int32_t s_pages[SELECT_IPT > 0 ? WAVES * 2 * (MULTI ? kMaxPairs : 1) : 1];
+  if constexpr (SELECT_IPT > 0) if (lo < k_pages) {
     if ((int)threadIdx.x < WAVES * ppw) s_pages[threadIdx.x] = -1;
     __syncthreads();
-    const int lo = split * WAVES * ppw;  // first list position of this workgroup
-    int32_t* list = sel_list + (size_t)stream * k_pages;
-    topk_block<SELECT_IPT, 64 * WAVES>(sel_score, NP, k_pages,
-                                       [&](int pos, int page) {
-                                         const unsigned r = (unsigned)(pos - lo);
-                                         if (r < (unsigned)(WAVES * ppw)) {
-                                           s_pages[r] = page;
-                                           list[pos] = page;
-                                         }
-                                       });
+    topk_block<SELECT_IPT, 64 * WAVES>(sel_score, NP, k_pages, *sel_lds, [&](int pos, int page) {
+      const unsigned r = (unsigned)(pos - lo);
+      if (r < (unsigned)(WAVES * ppw)) {
+        s_pages[r] = page;
+        if (MULTI) sel_list[(size_t)stream * k_pages + pos] = page;
+      }
+    });
     __syncthreads();
     if (lane < npages && pi0 + lane < k_pages) my_pg = s_pages[wave * ppw + lane];
   }
@@ -559,6 +552,12 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
         pr[1] = lsum;
       }
     }
+  }
+  // One pair per wavefront: the list is written behind all loads, with which a store in front of
+  // them would be waited for.
+  if constexpr (SELECT_IPT > 0 && !MULTI) {
+    if ((int)threadIdx.x < WAVES * ppw && lo + (int)threadIdx.x < k_pages)
+      sel_list[(size_t)stream * k_pages + lo + threadIdx.x] = s_pages[threadIdx.x];
   }
 }
 

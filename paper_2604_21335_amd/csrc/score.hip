@@ -132,6 +132,7 @@ void score_select_kernel(const u32x4* __restrict__ tiles, const uint16_t* __rest
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
   __shared__ __align__(16) unsigned char s_q[score_q_lds_bytes<D, RM>()];
   __shared__ __align__(16) float s_score[PAGES];
+  __shared__ TopkLds<PAGES / 512, 512> s_topk;
   const int stream = blockIdx.x;
   const int b = stream / Hkv, kvh = stream % Hkv, heads = Hq / Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -149,7 +150,7 @@ void score_select_kernel(const u32x4* __restrict__ tiles, const uint16_t* __rest
     for (int i = threadIdx.x; i < NP; i += 64 * WAVES) score[(size_t)stream * NP + i] = s_score[i];
   int32_t* list = page_idx + (size_t)stream * k_pages;
   topk_block<PAGES / (64 * WAVES), 64 * WAVES>(
-      s_score, NP, k_pages, [list](int pos, int page) { list[pos] = page; });
+      s_score, NP, k_pages, s_topk, [list](int pos, int page) { list[pos] = page; });
 }
 
 template <int D>

@@ -80,8 +80,9 @@ template <int IPT, int THREADS>
 __global__ __launch_bounds__(THREADS) void topk_reg_kernel(const float* __restrict__ score,
                                                            int32_t* __restrict__ page_idx, int NP,
                                                            int k) {
+  __shared__ TopkLds<IPT, THREADS> s_topk;
   int32_t* out = page_idx + (size_t)blockIdx.x * k;
-  topk_block<IPT, THREADS>(score + (size_t)blockIdx.x * NP, NP, k,
+  topk_block<IPT, THREADS>(score + (size_t)blockIdx.x * NP, NP, k, s_topk,
                            [out](int pos, int page) { out[pos] = page; });
 }
 

@@ -84,4 +84,11 @@ __device__ __forceinline__ uint32_t bf16_unorder(int k) {
   return ((uint32_t)s) >> 16;
 }
 
+// Orders a wavefront's own accesses to shared memory across its lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace stc

@@ -15,6 +15,12 @@ namespace stc {
 // At D = 64 two workgroups share a CU, with 128 registers each; without a tail one register is
 // spilled for it (512 streams of 512 pages, 64 kept 36.5 us, 39.2 with one workgroup per CU; of 250
 // pages, 30 kept 19.6, 22.5; but 256 streams of 512 pages 20.3, 19.6).
+// Bytes of shared memory in front of the selection's: query operands and page scores.
+template <int D, int RM>
+constexpr int step_score_lds() {
+  return score_q_lds_bytes<D, RM>() + kStepKeys * 4;
+}
+
 template <int D, int RM, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnParams P,
                                                    const score_u32x4* __restrict__ tiles,
@@ -36,14 +42,15 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnPa
       heads);
   __syncthreads();
   for (int i = threadIdx.x; i < P.NP; i += 64 * WAVES) score[(size_t)stream * P.NP + i] = s_score[i];
-  attn_block<D, WAVES, TAIL, kStepKeys / (64 * WAVES), STREAM, true>(P, stream, 0, lds, s_score);
+  attn_block<D, WAVES, TAIL, kStepKeys / (64 * WAVES), STREAM, true>(
+      P, stream, 0, lds, s_score, (TopkLds<kStepKeys / 512, 512>*)(lds + step_score_lds<D, RM>()));
 }
 
 template <int D, int RM, bool TAIL, bool STREAM>
 static int step_go(const AttnParams& p, int streams, const void* bounds, int tiles_cap,
                    float* score, hipStream_t st) {
   constexpr int attn_lds = 8 * AttnCfg<D>::WAVE_LDS;
-  constexpr int score_lds = score_q_lds_bytes<D, RM>() + kStepKeys * 4;
+  constexpr int score_lds = step_score_lds<D, RM>() + (int)sizeof(TopkLds<kStepKeys / 512, 512>);
   constexpr int lds_bytes = attn_lds > score_lds ? attn_lds : score_lds;
   static std::atomic<uint64_t> allowed{0};
   if (!allow_dynamic_lds((const void*)step_kernel<D, RM, TAIL, STREAM>, lds_bytes, allowed))

@@ -83,27 +83,308 @@ __device__ __forceinline__ uint32_t block_exscan_once(uint32_t v, uint32_t* lds_
   return base + inc - v;
 }
 
-// Top-k pages of a stream by one workgroup of THREADS threads with the keys held in
-// registers: thread t owns the IPT adjacent pages t*IPT .. (NP <= THREADS * IPT <= 65535).
-// The selected pages are handed to emit(position in the ascending list, page).  Each radix
+constexpr int kTopkBins = 1024;  // bins of the first histogram, of bf16 resolution, used in a circle
+constexpr int kTopkFine = 256;   // bins of the second one, between the first threshold and the maximum
+
+// Shared memory of a selection by THREADS threads (512 at most) with IPT keys each.
+template <int IPT, int THREADS>
+struct TopkLds {
+  // keys above the first threshold that a wavefront can hold: all of its own up to 8 per thread
+  static constexpr int OWN = IPT > 2 ? (IPT < 8 ? IPT : 8) * 64 : 1;
+  alignas(16) int hist[kTopkBins];
+  alignas(16) int fine[kTopkFine];
+  alignas(16) uint32_t wmin[8], wmax[8];
+  int tot[8];
+  int cand[64], cand_page[64];
+  int gt[64], ge[64];
+  int ncand, full;
+  int key[THREADS / 64][OWN];
+  uint16_t page[THREADS / 64][OWN];
+};
+
+__device__ __forceinline__ int lanes_below(uint64_t m) {  // set bits of m below this lane
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Of the 256 counts whose largest bins lane l holds four of (h4, lane 0 the topmost): the bin that holds
+// the key of rank `rank`, if it is among them (uniform over the wavefront).  `above` = counts in front
+// of it (of all, if it is not there), `cnt` = its own; returns its offset from the top or -1.
+__device__ __forceinline__ int rank_bin(int4 h4, int rank, int& above, int& cnt) {
+  const int cd[4] = {h4.w, h4.z, h4.y, h4.x};
+  const int mine = (h4.w + h4.z) + (h4.y + h4.x);
+  const int incl = (int)wave_scan((uint32_t)mine, OpAdd{}, 0u);
+  int at = above + incl - mine, f_bin = 0, f_above = 0, f_cnt = 0;
+  const uint64_t hit = __ballot(at < rank && rank <= at + mine);
+  if (hit == 0) {
+    above += __builtin_amdgcn_readlane(incl, 63);
+    return -1;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (at < rank) f_bin = j, f_above = at, f_cnt = cd[j];
+    at += cd[j];
+  }
+  const int src = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
+  above = __builtin_amdgcn_readlane(f_above, src);
+  cnt = __builtin_amdgcn_readlane(f_cnt, src);
+  return 4 * src + __builtin_amdgcn_readlane(f_bin, src);
+}
+
+// a[j] by selects.  An array that is indexed at run time would be put into memory, which is also what
+// the compiler makes of selects between two elements unless it cannot see that they are.
+template <int N>
+__device__ __forceinline__ int pick(const int (&a)[N], int j) {
+  if constexpr (N == 1) {
+    return a[0];
+  } else {
+    int half[N / 2];
+    static_for<0, N / 2>([&](auto i) {
+      int even = a[2 * i], odd = a[2 * i + 1];
+      asm("" : "+v"(even), "+v"(odd));
+      half[i] = (j & 1) ? odd : even;
+    });
+    return pick(half, j >> 1);
+  }
+}
+
+// Top-k pages of a stream by one workgroup of THREADS threads, NP <= THREADS * IPT pages.
+// The selected pages are handed to emit(position in the ascending list, page).  Returns false,
+// with nothing emitted, if the scores are not of the kind that it is made for (below).
+//
+// Bound by latency: a chain of barriers and of dependent instructions, in which a step over all keys
+// of a thread, or a branch per key, costs as much as a barrier.  So no phase goes through a thread's
+// keys one by one, and few keys are left after the first:
+//  - Scores are compared as the integers that their bits are, which is their order wherever
+//    they are positive.
+//  - The digits of the first histogram are the upper 16 bits (bf16 resolution, 128 bins per
+//    octave), taken in a circle of 1024 bins, so that the range of the keys need not be known
+//    before they are counted.
+//  - Up to 2 keys per thread: all of them are counted, and the bin of the k-th largest is found.
+//  - More: only the maxima of groups of 4 adjacent keys are counted.  k maxima at or above a bin's
+//    lower edge are k keys at or above it, so the pages below it are out.  Every wavefront gathers
+//    those that are left of its own, few more than k in all, and only these are counted in finer
+//    bins between that edge and the maximum.
+//  - The keys of the wanted bin are ranked one by one, and positions come from ballots.
+// Made for streams whose k-th largest score is positive and within 8 octaves of the maximum; NaN and
+// infinities are outside.
+// Time from the scores' arrival to the list, inside the attention launch, against topk_any: 8192 keys of
+// which 256 are kept 5.3 -> 3.6 us, 2048 of which 128 are kept 3.0 -> 2.4 (a step over 28 caches of
+// 131072 tokens 604 -> 543 us, over 64 streams of 2048 pages 30.4 -> 30.0, over 8 streams of 64
+// pages 7.4 -> 7.0).  Scores that it gives up on cost its first phases on top, 0.5 to 1.5 us.
+template <int IPT, int THREADS, class Emit>
+__device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int NP, int k,
+                                              TopkLds<IPT, THREADS>& S, Emit emit) {
+  constexpr int NW = THREADS / 64;
+  constexpr bool ALL = IPT <= 2;
+  constexpr int VEC = IPT < 4 ? IPT : 4, NQ = IPT / VEC;
+  constexpr int NE = ALL ? VEC : TopkLds<IPT, THREADS>::OWN / 64;  // keys per lane that are left, at most
+  typedef int keyvec __attribute__((ext_vector_type(VEC == 1 ? 2 : VEC), aligned(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (NP < VEC || (!ALL && k > (NP / VEC) / 8 * 7)) return false;
+
+  // A wavefront owns 64 * IPT adjacent pages, a lane VEC adjacent ones of each of their NQ parts:
+  // key[q * VEC + i] is page first(q) + i.  The lanes behind the last page read the last VEC pages,
+  // of which they own those from their own first page on.
+  int key[NQ * VEC];
+  auto own = [&](int q) { return ((wave * NQ + q) * 64 + lane) * VEC; };
+  auto first = [&](int q) { return min(own(q), NP - VEC); };
+  static_for<0, NQ>([&](auto q) {
+    const float* p = sc + first(q);
+    if constexpr (VEC == 1) {
+      key[q] = __float_as_int(*p);
+    } else {
+      const keyvec v = *(const keyvec*)p;
+      static_for<0, VEC>([&](auto i) { key[q * VEC + i] = v[(int)i]; });
+    }
+  });
+  for (int i = tid; i < kTopkBins / 4; i += THREADS) ((int4*)S.hist)[i] = int4{0, 0, 0, 0};
+  if (!ALL && tid < kTopkFine / 4) ((int4*)S.fine)[tid] = int4{0, 0, 0, 0};
+  if (tid == 0) S.ncand = 0, S.full = 0;
+  __syncthreads();
+  if ((wave + 1) * 64 * IPT > NP)
+    static_for<0, NQ>([&](auto q) {
+      static_for<0, VEC>([&](auto i) {
+        if (first(q) + i < own(q)) key[q * VEC + i] = INT32_MIN;
+      });
+    });
+
+  // What is counted, and the range of it.
+  uint32_t vmax = 0u, vmin = 0xffffffffu;
+  auto count = [&](int v) {
+    if (v > 0) atomicAdd(&S.hist[(v >> 16) & (kTopkBins - 1)], 1);
+    vmax = max(vmax, (uint32_t)max(v, 0));
+    vmin = min(vmin, v > 0 ? (uint32_t)v : 0xffffffffu);
+  };
+  static_for<0, NQ>([&](auto q) {
+    if constexpr (ALL) {
+      static_for<0, VEC>([&](auto i) { count(key[i]); });
+    } else {
+      count(max(max(key[4 * q], key[4 * q + 1]), max(key[4 * q + 2], key[4 * q + 3])));
+    }
+  });
+  vmax = wave_reduce(vmax, OpMax{}, 0u);
+  vmin = wave_reduce(vmin, OpMin{}, 0xffffffffu);
+  if (lane == 0) S.wmax[wave] = vmax, S.wmin[wave] = vmin;
+  __syncthreads();
+
+  // The bin in which the count from above reaches k; every wavefront finds it for itself.
+#pragma unroll
+  for (int w = 0; w < NW; ++w) vmax = max(vmax, S.wmax[w]), vmin = min(vmin, S.wmin[w]);
+  if (vmax == 0u) return false;
+  const int top = (int)(vmax >> 16) | 3, bins = top - (int)(vmin >> 16) + 1;
+  if (bins > kTopkBins) return false;
+  int above = 0, cnt = 0, bin = -1;
+  for (int c0 = 0; bin < 0; c0 += 256) {
+    if (c0 >= bins) return false;  // fewer than k of them are positive
+    const int o = rank_bin(*(const int4*)&S.hist[(top - 3 - c0 - 4 * lane) & (kTopkBins - 1)], k,
+                           above, cnt);
+    if (o >= 0) bin = top - c0 - o;
+  }
+  if (bin <= 0) return false;  // zeros would lie in it, which are not counted
+  int edge = bin << 16;        // of the wanted bin, which has `cnt` keys
+
+  // left[e], page[e]: the keys at or above the edge that this wavefront gathers from its own, in page
+  // order: number 64*e + lane.  (ALL: its own keys, number 64*e + lane is key e of the lane.)
+  int left[NE], page[NE];
+  int n = 64;  // their number in this wavefront
+  auto each = [&](auto f) {  // more than one per lane are rare
+    f(IC<0>{});
+    if constexpr (NE > 1) {
+      if (ALL || n > 64)
+        static_for<1, NE>([&](auto e) {
+          if (ALL || 64 * e < n) f(e);
+        });
+    }
+  };
+  int shift = 16;  // binary digits of the keys below those of the bin
+  if constexpr (ALL) {
+    static_for<0, NE>([&](auto e) { left[e] = key[e], page[e] = first(0) + e; });
+  } else {
+    uint32_t has = 0u;
+    static_for<0, IPT>([&](auto j) { has |= key[j] >= edge ? 1u << j : 0u; });
+    int start[NQ];
+    n = 0;
+    static_for<0, (NQ + 1) / 2>([&](auto h) {  // counts of two parts in the halves of a word
+      const uint32_t c = (uint32_t)__popc(has >> (8 * h) & 0xfu) |
+                         (uint32_t)__popc(has >> (8 * h) & 0xf0u) << 16;
+      const uint32_t incl = wave_scan(c, OpAdd{}, 0u);
+      const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      start[2 * h] = n + (int)((incl - c) & 0xffffu);
+      n += (int)(all & 0xffffu);
+      if constexpr (2 * h + 1 < NQ) {
+        start[2 * h + 1] = n + (int)((incl - c) >> 16);
+        n += (int)(all >> 16);
+      }
+    });
+    if (n <= TopkLds<IPT, THREADS>::OWN) {
+      for (uint32_t m = has; m; m &= m - 1u) {
+        const int j = __ffs((int)m) - 1, q = j >> 2;
+        const int at = pick(start, q) + __popc(has & (0xfu << (4 * q)) & ((1u << j) - 1u));
+        S.key[wave][at] = pick(key, j);
+        S.page[wave][at] = (uint16_t)(first(q) + (j & 3));
+      }
+    } else {
+      n = 0;
+      S.full = 1;
+    }
+    wave_lds_sync();
+    shift = max(0, 24 - __clz((int)(vmax - (uint32_t)edge) | 1));
+    each([&](auto e) {
+      const int at = max(min(64 * e + lane, n - 1), 0);
+      const int v = S.key[wave][at];
+      page[e] = S.page[wave][at];
+      left[e] = 64 * e + lane < n ? v : INT32_MIN;
+      if (64 * e + lane < n) atomicAdd(&S.fine[(v - edge) >> shift], 1);
+    });
+    __syncthreads();
+    if (S.full) return false;  // a wavefront has more than it can hold
+    above = 0;
+    const int o = rank_bin(*(const int4*)&S.fine[kTopkFine - 4 - 4 * lane], k, above, cnt);
+    edge += (kTopkFine - 1 - o) << shift;
+  }
+
+  // The least key that is taken: the edge, or a key of the wanted bin.
+  int least = edge;
+  const int rank = k - above;  // in the wanted bin
+  if (rank < cnt) {
+    if (cnt > 64) return false;
+    each([&](auto e) {
+      if ((uint32_t)(left[e] - edge) >> shift == 0u) {
+        const int c = atomicAdd(&S.ncand, 1);
+        S.cand[c] = left[e];
+        S.cand_page[c] = page[e];
+      }
+    });
+    __syncthreads();
+    const int mine = lane < cnt ? S.cand[lane] : INT32_MIN;
+    int gt = 0;
+#pragma unroll 4
+    for (int i = 0; i < cnt; ++i) gt += __builtin_amdgcn_readlane(mine, i) > mine;
+    int larger = rank - 1;  // keys of the bin above the wanted one
+    uint64_t eq;            // the candidates with its value
+    while ((eq = __ballot(lane < cnt && gt == larger)) == 0) --larger;
+    least = __builtin_amdgcn_readlane(
+        mine, __builtin_amdgcn_readfirstlane(__ffsll((long long)eq) - 1));
+    if (rank - larger < __popcll(eq)) {  // equal keys: those of the lowest pages are taken
+      const int pg = (eq >> lane) & 1u ? S.cand_page[lane] : INT32_MAX;
+      int lower = 0;
+      for (int i = 0; i < cnt; ++i) lower += __builtin_amdgcn_readlane(pg, i) < pg;
+      const uint64_t last = __ballot(pg != INT32_MAX && lower == rank - larger - 1);
+      const int limit = __builtin_amdgcn_readlane(
+          pg, __builtin_amdgcn_readfirstlane(__ffsll((long long)last) - 1));
+      each([&](auto e) {
+        if (left[e] == least && page[e] > limit) left[e] = INT32_MIN;
+      });
+    }
+  }
+
+  // Positions: a count per wavefront, and the wavefronts in front of it.
+  uint64_t taken[NE] = {};
+  int sum = 0;
+  each([&](auto e) {
+    taken[e] = __ballot(left[e] >= least);
+    sum += __popcll(taken[e]);
+  });
+  if (lane == 0) S.tot[wave] = sum;
+  __syncthreads();
+  const uint32_t t = lane < NW ? (uint32_t)S.tot[lane] : 0u;
+  int pos = __builtin_amdgcn_readlane((int)(wave_scan(t, OpAdd{}, 0u) - t), wave);
+  if constexpr (ALL) {
+    static_for<0, NE>([&](auto e) { pos += lanes_below(taken[e]); });
+    static_for<0, NE>([&](auto e) {
+      if (left[e] >= least) emit(pos++, page[e]);
+    });
+  } else {
+    each([&](auto e) {
+      if (left[e] >= least) emit(pos + lanes_below(taken[e]), page[e]);
+      pos += __popcll(taken[e]);
+    });
+  }
+  return true;
+}
+
+// The same for any scores, with the keys held in registers: thread t owns the IPT adjacent pages t*IPT .. (NP <= THREADS * IPT <= 65535).
+// Each radix
 // pass is a shared-memory histogram of one key digit, which every wavefront then scans for
 // itself (digits in descending order) to find the digit that holds the k-th largest key: no
 // broadcast and no second barrier.  The usual case (one pass, then at most 64 candidates
 // ranked directly) crosses five workgroup barriers.
 template <int IPT, int THREADS, class Emit>
-__device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP, int k,
-                                           Emit emit) {
+__device__ __forceinline__ void topk_any(const float* __restrict__ sc, int NP, int k,
+                                         TopkLds<IPT, THREADS>& S, Emit emit) {
   constexpr int NW = THREADS / 64;
   // Digit width: 8 bits, 10 from 4096 keys on, where a digit of 8 bits leaves more keys beside
   // the k-th than are ranked directly, which costs a second pass.
   constexpr int HB = THREADS * IPT > 2048 ? 10 : 8;
   constexpr int BINS = 1 << HB, PER = BINS / 64;  // digits per lane of a wavefront's scan
-  __shared__ __align__(16) int hist[BINS];
-  __shared__ uint32_t waves[NW];  // per-wavefront sums of the final scan
-  __shared__ uint32_t s_min[NW], s_max[NW];
-  __shared__ int s_ncand;
-  __shared__ uint32_t cand[64];
-  __shared__ int s_gt[64], s_ge[64];  // per candidate: candidates above it / not below it
+  int* const hist = S.hist;
+  uint32_t* const waves = (uint32_t*)S.tot;  // per-wavefront sums of the final scan
+  uint32_t *const s_min = S.wmin, *const s_max = S.wmax;
+  int& s_ncand = S.ncand;
+  uint32_t* const cand = (uint32_t*)S.cand;
+  int *const s_gt = S.gt, *const s_ge = S.ge;  // per candidate: candidates above it / not below it
+  static_assert(BINS <= kTopkBins && NW <= 8, "shared memory");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int i0 = tid * IPT;
@@ -247,6 +528,17 @@ __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP,
       if (t && pos < k) emit(pos++, i0 + j);
     }
   }
+}
+
+// Top-k pages of a stream by one workgroup of THREADS threads, NP <= THREADS * IPT <= 65535: ties to
+// the lowest page, emit(position in the ascending list, page) for every selected one.  `sc` must not
+// lie in `S`.
+template <int IPT, int THREADS, class Emit>
+__device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP, int k,
+                                           TopkLds<IPT, THREADS>& S, Emit emit) {
+  if (topk_positive<IPT, THREADS>(sc, NP, k, S, emit)) return;
+  __syncthreads();
+  topk_any<IPT, THREADS>(sc, NP, k, S, emit);
 }
 
 }  // namespace stc
