@@ -11,12 +11,11 @@ template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
 __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams P) {
   extern __shared__ __align__(16) unsigned char lds[];  // WAVES * AttnCfg<D>::WAVE_LDS bytes
   int stream = blockIdx.y, split = blockIdx.x;
-  if (P.nx > 0) {
-    // Workgroup i of a launch runs on XCD i % 8: all workgroups of a stream get the same i % nx,
+  if (P.by_xcd) {
+    // Workgroup i of a launch runs on XCD i % 8: all workgroups of a stream get the same i % 8,
     // so that what they share (the stream's page scores, its query) passes through one L2
-    const int x = blockIdx.x % P.nx, slot = blockIdx.x / P.nx;
-    stream = (slot / P.splits) * P.nx + x;
-    split = slot % P.splits;
+    stream = blockIdx.z * kXcds + blockIdx.x;
+    split = blockIdx.y;
   }
   attn_block<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>(
       P, stream, split, lds, SELECT_IPT > 0 ? P.sel_score + (size_t)stream * P.NP : nullptr,
@@ -206,10 +205,10 @@ static AttnParams attn_params(const stc_shape_t& s, const stc_shape_t& s0, const
                               int32_t* sel_list, float* out, void* ws) {
   if (n_tail == 0) K_tail = V_tail = K;  // any valid address: never read
   return AttnParams{(const uint16_t*)q, (const uint16_t*)K, (const unsigned char*)vpacked, mask,
-                    tok_off, page_idx, (float*)ws, out, s.Hq, s.Hkv, s.N,
+                    tok_off, page_idx, (float*)ws, out, s.Hq / s.Hkv, s.N,
                     (s.N + kPage - 1) / kPage, s.G, (uint32_t)s.v_cap_groups, k_pages, plan.splits,
                     (const uint16_t*)K_tail, (const uint16_t*)V_tail, n_tail, tail_cap,
-                    s.Hkv / s0.Hkv, page_heads, token_cap(s), sel_score, sel_list, plan.pairs, 0};
+                    s.Hkv / s0.Hkv, page_heads, token_cap(s), sel_score, sel_list, plan.pairs, false};
 }
 
 // K rows and value runs are read once per step.  What a launch cannot know is whether they still lie
@@ -253,10 +252,9 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
   if (sel_score && (NP > 8192 || per_head || page_heads)) return -1;
   // with the selection inside, the workgroups of a stream all read the stream's scores: keep
   // them on one XCD (measured on the headline shape: 34.2 against 34.6 us per step)
-  constexpr int kXcds = 8;
   if (sel_score && plan.splits > 1 && streams % kXcds == 0) {
-    a.p.nx = kXcds;
-    a.grid = dim3(plan.splits * streams, 1);
+    a.p.by_xcd = true;
+    a.grid = dim3(kXcds, plan.splits, streams / kXcds);
   }
   const bool stream_loads = streaming_loads(s, k_pages, tail_pages, kv_div);
   const bool tail = tail_pages > 0, select = sel_score != nullptr;

@@ -36,6 +36,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;  // "no token seen yet" running maximum
 constexpr int kMaxPairs = 8;         // pairs of pages per wavefront at most
 constexpr int kMaxPairsShared = 3;   // the same where heads of a KV head have lists of their own
+constexpr int kXcds = 8;
 constexpr int kTailPage = 1 << 30;   // flag of a page slot that lies in the uncompressed tail
 
 // Partial result of one (query head, split): [0] running max (base-2 logits),
@@ -106,7 +107,7 @@ struct AttnParams {
   const uint32_t* tok_off;
   const int32_t* page_idx;
   float *partial, *out;
-  int Hq, Hkv, N, NP, G;
+  int R, N, NP, G;  // R: query heads per stream (KV head)
   uint32_t cap;
   int k_pages, splits;
   const uint16_t *K_tail, *V_tail;
@@ -115,8 +116,8 @@ struct AttnParams {
   int Ncap;
   const float* sel_score;
   int32_t* sel_list;
-  int pairs;  // pairs of pages per wavefront (MULTI kernels)
-  int nx;  // > 0: one-dimensional grid, stream s on the workgroups i with i % nx == s % nx
+  int pairs;    // pairs of pages per wavefront (MULTI kernels)
+  bool by_xcd;  // grid (kXcds, splits, streams / kXcds): a stream's workgroups on one XCD
 };
 
 // Keys that the selection inside a step kernel holds (pages per stream at most), and the bounds
@@ -145,7 +146,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   const int32_t* __restrict__ page_idx = P.page_idx;
   float* __restrict__ partial = P.partial;
   float* __restrict__ out = P.out;
-  const int Hq = P.Hq, Hkv = P.Hkv, N = P.N, NP = P.NP, G = P.G;
+  const int R = P.R, N = P.N, NP = P.NP, G = P.G;
   const uint32_t cap = P.cap;
   const int k_pages = P.k_pages, splits = P.splits;
   const uint16_t* __restrict__ K_tail = P.K_tail;
@@ -154,13 +155,11 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   const uint16_t* __restrict__ page_heads = P.page_heads;
   const int Ncap = P.Ncap;
   int32_t* __restrict__ sel_list = P.sel_list;
-  const int b = stream / Hkv, kvh = stream % Hkv;
-  const int R = Hq / Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;  // MFMA row/column and k-group of this lane
-  const int gd = D / G;
-  const uint32_t gbytes = gd * 2;
-  const int lg_upg = 31 - __clz(gd / 8);  // log2(16-byte units per group)
+  const int lg_g = 31 - __clz(G);                 // G is a power of two
+  const uint32_t gbytes = (D * 2) >> lg_g;
+  const int lg_upg = 31 - __clz(D / 8) - lg_g;  // log2(16-byte units per group)
   const float scale = kLog2e / sqrtf((float)D);
 
   unsigned char* wl = lds + wave * C::WAVE_LDS;
@@ -168,7 +167,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   // per-stream bases (wave-uniform); everything below is addressed with 32-bit byte offsets.
   // kv_div > 1: the launch has one "stream" (page list, query, output) per query head and
   // kv_div of them share the cache of one KV head.
-  const int kvs = stream / kv_div;
+  const int kvs = kv_div == 1 ? stream : stream / kv_div;
   const unsigned char* Ks = (const unsigned char*)K + (size_t)kvs * Ncap * D * 2;
   const unsigned char* mask_s = (const unsigned char*)mask + (size_t)kvs * Ncap * 2;
   const unsigned char* off_s = (const unsigned char*)tok_off + (size_t)kvs * (Ncap + 1) * 4;
@@ -338,7 +337,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   // B operand of the QK product: this lane's 8 channels of head r16 for every 32-channel step
   u32x4 qreg[C::KC];
   {
-    const unsigned char* qs = (const unsigned char*)q + ((size_t)b * Hq + kvh * R) * D * 2;
+    const unsigned char* qs = (const unsigned char*)q + (size_t)stream * R * D * 2;
     const uint32_t qo = ((r16 < R ? r16 : 0) * D + 8 * kg) * 2;
 #pragma unroll
     for (int j = 0; j < C::KC; ++j)
@@ -541,7 +540,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
       lsum = fmaf(wgt, ((const float*)(lds + w * C::WAVE_LDS + C::MML))[head * 2 + 1], lsum);
       a = fmaf(wgt, ((const float*)(lds + w * C::WAVE_LDS))[head * C::MROW + c], a);
     }
-    const size_t hf = (size_t)b * Hq + kvh * R + head;
+    const size_t hf = (size_t)stream * R + head;
     if (splits == 1) {
       out[hf * D + c] = lsum > 0.f ? a / lsum : 0.f;
     } else {

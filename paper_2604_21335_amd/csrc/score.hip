@@ -37,23 +37,23 @@ typedef score_u32x4 u32x4;
 template <int D, int R, bool PER_HEAD, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void score_lds_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restrict__ q,
-                      float* __restrict__ score, int NP, int Hq, int Hkv, int tiles_per_block,
+                      float* __restrict__ score, int NP, int group, int tiles_per_block,
                       int tiles_cap) {
   constexpr int T16 = (D / 32) * 64;
   __shared__ __align__(16) unsigned char s_q[score_q_lds_bytes<D, R>()];
   const int stream = blockIdx.y;
-  const int b = stream / Hkv, kvh = stream % Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
   const int t0 = blockIdx.x * tiles_per_block;
   const int t1 = min(t0 + tiles_per_block, ntiles);
-  const int heads = R > 8 ? Hq / Hkv : R;  // groups of more than 8 heads share one instance
-  const uint16_t* qs = q + ((size_t)b * Hq + kvh * heads) * D;
+  const int heads = R > 8 ? group : R;  // groups of more than 8 heads share one instance
+  ScoreQuery<D, R, 64 * WAVES> sq;
+  sq.load(q + (size_t)stream * heads * D, heads);  // [B, Hkv, heads, D]
   score_tile_range<D, R, PER_HEAD, WAVES, 1, STREAM>(
       (const score_u32x4*)tiles + (size_t)stream * tiles_cap * T16 + lane,
       score + (size_t)stream * (PER_HEAD ? heads : 1) * NP, NP, t0, t1, s_q, wave, lane,
       [&] {
-        score_fill_q<D, R, 64 * WAVES>(qs, s_q, heads);
+        sq.store(s_q, heads);
         __syncthreads();
       },
       heads);
@@ -94,7 +94,7 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
   const dim3 grid((ntiles + tp - 1) / tp, streams);
 #define STC_SCORE_GO(RR, PH, STREAM)                                                              \
   score_lds_kernel<D, RR, PH, (RR <= 4 ? 8 : 4), STREAM><<<grid, 64 * waves, 0, st>>>(            \
-      t4, q16, score, NP, s.Hq, s.Hkv, tp, tcap)
+      t4, q16, score, NP, R, tp, tcap)
 #define STC_SCORE_CASE(RR)                                                                        \
   case RR:                                                                                        \
     if (per_head) {                                                                               \
@@ -127,21 +127,21 @@ static void launch_score_d(const stc_shape_t& s, const void* q, const void* boun
 template <int D, int RM, int PAGES>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void score_select_kernel(const u32x4* __restrict__ tiles, const uint16_t* __restrict__ q,
-                         float* __restrict__ score, int NP, int Hq, int Hkv, int tiles_cap,
+                         float* __restrict__ score, int NP, int heads, int tiles_cap,
                          int32_t* __restrict__ page_idx, int k_pages) {
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
   __shared__ __align__(16) unsigned char s_q[score_q_lds_bytes<D, RM>()];
   __shared__ __align__(16) float s_score[PAGES];
   __shared__ TopkLds<PAGES / 512, 512> s_topk;
   const int stream = blockIdx.x;
-  const int b = stream / Hkv, kvh = stream % Hkv, heads = Hq / Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int ntiles = (NP + kBoundsTilePages - 1) / kBoundsTilePages;
-  const uint16_t* qs = q + ((size_t)b * Hq + kvh * heads) * D;
+  ScoreQuery<D, RM, 64 * WAVES> sq;
+  sq.load(q + (size_t)stream * heads * D, heads);
   score_tile_range<D, RM, false, WAVES, 2>(
       tiles + (size_t)stream * tiles_cap * T16 + lane, s_score, NP, 0, ntiles, s_q, wave, lane,
       [&] {
-        score_fill_q<D, RM, 64 * WAVES>(qs, s_q, heads);
+        sq.store(s_q, heads);
         __syncthreads();
       },
       heads);
@@ -161,7 +161,7 @@ static int launch_score_select_d(const stc_shape_t& s, const void* q, const void
   const int tcap = bounds_tiles(token_cap(s));
 #define STC_SCORE_SELECT(RM, PAGES)                                                            \
   score_select_kernel<D, RM, PAGES><<<streams, 512, 0, st>>>(                                  \
-      (const u32x4*)bounds, (const uint16_t*)q, score, NP, s.Hq, s.Hkv, tcap, page_idx, k_pages)
+      (const u32x4*)bounds, (const uint16_t*)q, score, NP, R, tcap, page_idx, k_pages)
 #define STC_SCORE_SELECT_PAGES(RM)                                                             \
   if (NP <= 512) STC_SCORE_SELECT(RM, 512);                                                    \
   else STC_SCORE_SELECT(RM, 1024);

@@ -19,40 +19,55 @@ __host__ __device__ constexpr int score_q_lds_bytes() {
   return ((R + 3) / 4) * (D / 8) * 64 * 8;
 }
 
-// Fills the operand table for the first `heads` of R heads at `qs` ([R][D] bf16).  Entry (g, c, lane) is the A
+// The operand table of the first `heads` of R heads at `qs` ([R][D] bf16).  Entry (g, c, lane) is the A
 // operand of lane `lane` for channel c of its chunk and head 4g + lane%4: the query value in
 // the k-slot of the channel's minimum when it is negative, of its maximum otherwise, zeros in
 // the three other slots (the channel pair of a B operand occupies two slots each).  All
-// threads of the workgroup call it; the caller synchronises before the table is read.
+// threads of the workgroup load and store it; the caller synchronises before the table is read.
+// The loads go out in front of the tiles', so that the table is written while the tiles travel: behind
+// them they would return last, since loads return in order.
 template <int D, int R, int THREADS>
-__device__ __forceinline__ void score_fill_q(const uint16_t* __restrict__ qs, unsigned char* qlds,
-                                             int heads = R) {
-  constexpr int CH = D / 8, NG = (R + 3) / 4, PIECES = CH / 8;  // 16-byte pieces per chunk
+struct ScoreQuery {
   // one work item = 8 adjacent channels of one (head group, lane): a single 16-byte load
-  for (int it = threadIdx.x; it < NG * PIECES * 64; it += THREADS) {
-    const int l = it & 63, piece = (it >> 6) % PIECES, g = it / (64 * PIECES);
-    const int head = 4 * g + (l & 3), e = (l >> 2) & 7;
-    score_u32x4 v = {0u, 0u, 0u, 0u};
-    if (head < heads) v = *(const score_u32x4*)(qs + head * D + e * CH + piece * 8);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t lo = w[i] & 0xffffu, hi = w[i] >> 16;  // channels 2i and 2i+1 of the piece
-      const uint32_t qa0 = (lo & 0x8000u) ? lo : lo << 16;
-      const uint32_t qa1 = (hi & 0x8000u) ? hi : hi << 16;
-      const int c = piece * 8 + 2 * i;
-      *(score_u32x2*)(qlds + (size_t)((g * CH + c) * 64 + l) * 8) = score_u32x2{qa0, 0u};
-      *(score_u32x2*)(qlds + (size_t)((g * CH + c + 1) * 64 + l) * 8) = score_u32x2{0u, qa1};
-    }
+  static constexpr int CH = D / 8, NG = (R + 3) / 4, PIECES = CH / 8;  // 16-byte pieces per chunk
+  static constexpr int ITEMS = NG * PIECES * 64, PER = (ITEMS + THREADS - 1) / THREADS;
+  score_u32x4 v[PER];
+
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ qs, int heads) {
+    static_for<0, PER>([&](auto n) {
+      const int it = min((int)threadIdx.x + n * THREADS, ITEMS - 1);
+      const int l = it & 63, piece = (it >> 6) % PIECES, g = it / (64 * PIECES);
+      const int head = 4 * g + (l & 3), e = (l >> 2) & 7;
+      v[n] = *(const score_u32x4*)(qs + min(head, heads - 1) * D + e * CH + piece * 8);
+    });
   }
-}
+
+  __device__ __forceinline__ void store(unsigned char* qlds, int heads) const {
+    static_for<0, PER>([&](auto n) {
+      const int it = threadIdx.x + n * THREADS;
+      const int l = it & 63, piece = (it >> 6) % PIECES, g = it / (64 * PIECES);
+      if (ITEMS % THREADS != 0 && it >= ITEMS) return;
+      const bool live = 4 * g + (l & 3) < heads;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = live ? v[n][i] : 0u;
+        const uint32_t lo = w & 0xffffu, hi = w >> 16;  // channels 2i and 2i+1 of the piece
+        const uint32_t qa0 = (lo & 0x8000u) ? lo : lo << 16;
+        const uint32_t qa1 = (hi & 0x8000u) ? hi : hi << 16;
+        const int c = piece * 8 + 2 * i;
+        *(score_u32x2*)(qlds + (size_t)((g * CH + c) * 64 + l) * 8) = score_u32x2{qa0, 0u};
+        *(score_u32x2*)(qlds + (size_t)((g * CH + c + 1) * 64 + l) * 8) = score_u32x2{0u, qa1};
+      }
+    });
+  }
+};
 
 // Scores tiles t0 + wave, t0 + wave + WAVES, ... < t1 of one stream.  `base` = the stream's
 // tiles + lane; out = the stream's score row(s).  DEPTH tiles of the wavefront are requested
 // ahead (DEPTH - 1 in flight behind the one being computed); STREAM: with loads that leave the
 // caches alone.  `prologue` is run by every thread
-// once the first tiles have been requested: it fills the operand table (score_fill_q) and
-// synchronises the workgroup, so that the latency of the query loads hides behind the tiles'.
+// once the first tiles have been requested: it stores the operand table (ScoreQuery, whose loads the
+// caller has made) and synchronises the workgroup.
 // Heads from `heads` on count for nothing.
 template <int D, int R, bool PER_HEAD, int WAVES, int DEPTH = 2, bool STREAM = false,
           class Prologue>
@@ -116,8 +131,9 @@ __device__ __forceinline__ void score_tile_range(const score_u32x4* __restrict__
   int t = t0 + wave;
   const bool any = t < t1;  // wave-uniform
   score_u32x4 d[DEPTH][NJ];
+  __builtin_amdgcn_sched_barrier(0);  // behind the query loads
   if (any) static_for<0, DEPTH>([&](auto k) { load_tile(d[k], t + k * WAVES); });
-  __builtin_amdgcn_sched_barrier(0);  // the tile requests go out first
+  __builtin_amdgcn_sched_barrier(0);  // the tile requests go out before anything is waited for
   prologue();
   if (!any) return;
   for (; t < t1; t += DEPTH * WAVES) {

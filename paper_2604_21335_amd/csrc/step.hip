@@ -28,15 +28,16 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnPa
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
   extern __shared__ __align__(16) unsigned char lds[];
   const int stream = blockIdx.x;
-  const int b = stream / P.Hkv, kvh = stream % P.Hkv, heads = P.Hq / P.Hkv;
+  const int heads = P.R;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint16_t* qs = P.q + ((size_t)b * P.Hq + kvh * heads) * D;
+  ScoreQuery<D, RM, 64 * WAVES> sq;
+  sq.load(P.q + (size_t)stream * heads * D, heads);
   float* s_score = (float*)(lds + score_q_lds_bytes<D, RM>());
   const int ntiles = (P.NP + kBoundsTilePages - 1) / kBoundsTilePages;
   score_tile_range<D, RM, false, WAVES, kStepTilesAhead, STREAM>(
       tiles + (size_t)stream * tiles_cap * T16 + lane, s_score, P.NP, 0, ntiles, lds, wave, lane,
       [&] {
-        score_fill_q<D, RM, 64 * WAVES>(qs, lds, heads);
+        sq.store(lds, heads);
         __syncthreads();
       },
       heads);
@@ -74,7 +75,7 @@ template <int D>
 static int step_dispatch_heads(const AttnParams& p, int streams, const void* bounds,
                                int tiles_cap, float* score, bool tail, bool stream_loads,
                                hipStream_t st) {
-  const int R = p.Hq / p.Hkv;
+  const int R = p.R;
   if (R == 1) return step_dispatch<D, 1>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
   if (R == 2) return step_dispatch<D, 2>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
   if (R <= 4) return step_dispatch<D, 4>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
