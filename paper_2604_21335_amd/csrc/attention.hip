@@ -8,17 +8,21 @@ namespace stc {
 // spill 2 to 11 and are slower at every number of streams (512 streams of 40 pages 15.1 us, 14.1
 // without; 256 streams of 64 pages and a tail 16.3, 13.3; 512 of 128 pages 37.8, 36.8).
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
-__global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(const AttnParams P) {
+__global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(
+    const void* list_or_score, const uint16_t* q, const uint16_t* K, const uint16_t* mask,
+    const uint32_t* tok_off, int NP, int k_pages, int Ncap, int R_by_xcd, const AttnParams rest) {
+  AttnParams P = AttnFirst{q, K, mask, tok_off, NP, k_pages, Ncap, R_by_xcd & 0xff}.with(rest);
+  P.page_idx = SELECT_IPT > 0 ? nullptr : (const int32_t*)list_or_score;
   extern __shared__ __align__(16) unsigned char lds[];  // WAVES * AttnCfg<D>::WAVE_LDS bytes
   int stream = blockIdx.y, split = blockIdx.x;
-  if (P.by_xcd) {
+  if (R_by_xcd >> 8) {
     // Workgroup i of a launch runs on XCD i % 8: all workgroups of a stream get the same i % 8,
     // so that what they share (the stream's page scores, its query) passes through one L2
     stream = blockIdx.z * kXcds + blockIdx.x;
     split = blockIdx.y;
   }
   attn_block<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>(
-      P, stream, split, lds, SELECT_IPT > 0 ? P.sel_score + (size_t)stream * P.NP : nullptr,
+      P, stream, split, lds, (const float*)list_or_score + (size_t)stream * NP,
       (TopkLds<SELECT_IPT, 64 * WAVES>*)lds);
 }
 
@@ -147,7 +151,9 @@ int attn_go(const AttnLaunch& a) {
                          lds_bytes, allowed))
     return -1;
   attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>
-      <<<a.grid, 64 * WAVES, lds_bytes, a.st>>>(a.p);
+      <<<a.grid, 64 * WAVES, lds_bytes, a.st>>>(
+          SELECT_IPT > 0 ? (const void*)a.p.sel_score : (const void*)a.p.page_idx, a.p.q, a.p.K,
+          a.p.mask, a.p.tok_off, a.p.NP, a.p.k_pages, a.p.Ncap, a.p.R | (int)a.p.by_xcd << 8, a.p);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -301,8 +307,8 @@ int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const v
   const AttnParams p =
       attn_params(s, s, plan, q, K, vpacked, mask, tok_off, nullptr, k_pages, K_tail, V_tail, n_tail,
                   tail_cap, nullptr, nullptr, list, out, nullptr);
-  return launch_step_kernel(p, s.D, s.B * s.Hkv, bounds, bounds_tiles(token_cap(s)), score,
-                            tail_pages > 0, streaming_loads(s, k_pages, tail_pages, 1), st);
+  return launch_step_kernel(p, s.D, s.B * s.Hkv, bounds, score, tail_pages > 0,
+                            streaming_loads(s, k_pages, tail_pages, 1), st);
 }
 
 // New token of every stream -> row n_tail of the stream's uncompressed tail (K and V).

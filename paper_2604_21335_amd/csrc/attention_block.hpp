@@ -120,14 +120,29 @@ struct AttnParams {
   bool by_xcd;  // grid (kXcds, splits, streams / kXcds): a stream's workgroups on one XCD
 };
 
+// The arguments that a workgroup needs first come in front of the struct, one by one: the first 14
+// words of a kernel's scalar arguments are in registers when it starts (a struct is not), the
+// others are a load from memory away.
+struct AttnFirst {
+  const uint16_t *q, *K, *mask;
+  const uint32_t* tok_off;
+  int NP, k_pages, Ncap, R;
+
+  __device__ __forceinline__ AttnParams with(AttnParams p) const {
+    p.q = q, p.K = K, p.mask = mask, p.tok_off = tok_off;
+    p.NP = NP, p.k_pages = k_pages, p.Ncap = Ncap, p.R = R;
+    return p;
+  }
+};
+
 // Keys that the selection inside a step kernel holds (pages per stream at most), and the bounds
 // tiles that a wavefront of it has in flight.
 constexpr int kStepKeys = 1024;
 constexpr int kStepTilesAhead = 2;
 
 // One launch for a whole step (step.hip): one workgroup of 8 wavefronts per stream, no splits.
-int launch_step_kernel(const AttnParams& p, int D, int streams, const void* bounds, int tiles_cap,
-                       float* score, bool tail, bool stream_loads, hipStream_t st);
+int launch_step_kernel(const AttnParams& p, int D, int streams, const void* bounds, float* score,
+                       bool tail, bool stream_loads, hipStream_t st);
 
 // The work of one workgroup: split `split` of stream `stream`.  `lds` = WAVES * WAVE_LDS bytes
 // of shared memory.  sel_score (SELECT_IPT > 0) = the stream's page scores; they and the memory

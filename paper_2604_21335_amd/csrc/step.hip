@@ -22,9 +22,12 @@ constexpr int step_score_lds() {
 }
 
 template <int D, int RM, bool TAIL, bool STREAM>
-__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnParams P,
-                                                   const score_u32x4* __restrict__ tiles,
-                                                   int tiles_cap, float* __restrict__ score) {
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(
+    const score_u32x4* __restrict__ tiles, float* __restrict__ score, const uint16_t* q,
+    const uint16_t* K, const uint32_t* tok_off, int NP, int k_pages, int Ncap, int R,
+    const AttnParams rest) {
+  const AttnParams P = AttnFirst{q, K, rest.mask, tok_off, NP, k_pages, Ncap, R}.with(rest);
+  const int tiles_cap = bounds_tiles(Ncap);
   constexpr int WAVES = 8, T16 = (D / 32) * 64;
   extern __shared__ __align__(16) unsigned char lds[];
   const int stream = blockIdx.x;
@@ -48,8 +51,8 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(const AttnPa
 }
 
 template <int D, int RM, bool TAIL, bool STREAM>
-static int step_go(const AttnParams& p, int streams, const void* bounds, int tiles_cap,
-                   float* score, hipStream_t st) {
+static int step_go(const AttnParams& p, int streams, const void* bounds, float* score,
+                   hipStream_t st) {
   constexpr int attn_lds = 8 * AttnCfg<D>::WAVE_LDS;
   constexpr int score_lds = step_score_lds<D, RM>() + (int)sizeof(TopkLds<kStepKeys / 512, 512>);
   constexpr int lds_bytes = attn_lds > score_lds ? attn_lds : score_lds;
@@ -57,37 +60,38 @@ static int step_go(const AttnParams& p, int streams, const void* bounds, int til
   if (!allow_dynamic_lds((const void*)step_kernel<D, RM, TAIL, STREAM>, lds_bytes, allowed))
     return -1;
   step_kernel<D, RM, TAIL, STREAM>
-      <<<streams, 512, lds_bytes, st>>>(p, (const score_u32x4*)bounds, tiles_cap, score);
+      <<<streams, 512, lds_bytes, st>>>((const score_u32x4*)bounds, score, p.q, p.K, p.tok_off, p.NP,
+                                        p.k_pages, p.Ncap, p.R, p);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 template <int D, int RM>
-static int step_dispatch(const AttnParams& p, int streams, const void* bounds, int tiles_cap,
-                         float* score, bool tail, bool stream_loads, hipStream_t st) {
+static int step_dispatch(const AttnParams& p, int streams, const void* bounds, float* score,
+                         bool tail, bool stream_loads, hipStream_t st) {
   if (stream_loads)
-    return tail ? step_go<D, RM, true, true>(p, streams, bounds, tiles_cap, score, st)
-                : step_go<D, RM, false, true>(p, streams, bounds, tiles_cap, score, st);
-  return tail ? step_go<D, RM, true, false>(p, streams, bounds, tiles_cap, score, st)
-              : step_go<D, RM, false, false>(p, streams, bounds, tiles_cap, score, st);
+    return tail ? step_go<D, RM, true, true>(p, streams, bounds, score, st)
+                : step_go<D, RM, false, true>(p, streams, bounds, score, st);
+  return tail ? step_go<D, RM, true, false>(p, streams, bounds, score, st)
+              : step_go<D, RM, false, false>(p, streams, bounds, score, st);
 }
 
 template <int D>
 static int step_dispatch_heads(const AttnParams& p, int streams, const void* bounds,
-                               int tiles_cap, float* score, bool tail, bool stream_loads,
+                               float* score, bool tail, bool stream_loads,
                                hipStream_t st) {
   const int R = p.R;
-  if (R == 1) return step_dispatch<D, 1>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
-  if (R == 2) return step_dispatch<D, 2>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
-  if (R <= 4) return step_dispatch<D, 4>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
-  if (R <= 8) return step_dispatch<D, 8>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
+  if (R == 1) return step_dispatch<D, 1>(p, streams, bounds, score, tail, stream_loads, st);
+  if (R == 2) return step_dispatch<D, 2>(p, streams, bounds, score, tail, stream_loads, st);
+  if (R <= 4) return step_dispatch<D, 4>(p, streams, bounds, score, tail, stream_loads, st);
+  if (R <= 8) return step_dispatch<D, 8>(p, streams, bounds, score, tail, stream_loads, st);
   return -1;
 }
 
-int launch_step_kernel(const AttnParams& p, int D, int streams, const void* bounds, int tiles_cap,
-                       float* score, bool tail, bool stream_loads, hipStream_t st) {
+int launch_step_kernel(const AttnParams& p, int D, int streams, const void* bounds, float* score,
+                       bool tail, bool stream_loads, hipStream_t st) {
   return D == 128
-             ? step_dispatch_heads<128>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st)
-             : step_dispatch_heads<64>(p, streams, bounds, tiles_cap, score, tail, stream_loads, st);
+             ? step_dispatch_heads<128>(p, streams, bounds, score, tail, stream_loads, st)
+             : step_dispatch_heads<64>(p, streams, bounds, score, tail, stream_loads, st);
 }
 
 }  // namespace stc

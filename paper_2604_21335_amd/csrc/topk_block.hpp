@@ -319,7 +319,6 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
     __syncthreads();
     const int mine = lane < cnt ? S.cand[lane] : INT32_MIN;
     int gt = 0;
-#pragma unroll 4
     for (int i = 0; i < cnt; ++i) gt += __builtin_amdgcn_readlane(mine, i) > mine;
     int larger = rank - 1;  // keys of the bin above the wanted one
     uint64_t eq;            // the candidates with its value
