@@ -68,9 +68,16 @@ struct AttnCfg {
   static_assert(MML + 16 * 2 * 4 <= 2 * TILE, "merge buffer fits the tiles");
 };
 
-// 16 zero bytes in device memory: where lanes beyond the end of a packed run read
-static __device__ u32x4 stc_zero16 = {0u, 0u, 0u, 0u};  // never written
-
+// Lanes that differ in lane bit 4 or 5 hold parts of the same sum or maximum: every lane gets op over
+// the four of them.  (Swaps of register halves; a shuffle would go through shared memory.)
+template <class Op>
+__device__ __forceinline__ float across_k_groups(float x, Op op) {
+  const uint32_t a = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const uint32_t b = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  const auto s = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
 
 // One wavefront takes one pair of page slots of one stream, or, with MULTI, P.pairs adjacent pairs
 // one after the other (up to kMaxPairs), each a partial result of its own; the WAVES wavefronts of
@@ -296,10 +303,8 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
       const unsigned char* kb = (pg >= 0 && is_tail(pg)) ? Kts : Ks;  // wave-uniform
 #pragma unroll
       for (int j = 0; j < C::NLD; ++j) {
-        const uint32_t tok = (j * 64 + lane) / C::LPR;
-        const bool tv = pg >= 0 && (t0 + tok < lim);
-        // rows of absent tokens read the store's first bytes: their logits are discarded
-        const uint32_t ko = tv ? t0 * (D * 2) + (j * 64 + lane) * 16 : 0;
+        // absent tokens read the end of the store's last row: their logits are discarded
+        const uint32_t ko = min(t0 * (D * 2) + (j * 64 + lane) * 16, lim * (D * 2) - 16);
         const u32x4* a = (const u32x4*)(kb + ko);
         kreg[x][j] = STREAM ? __builtin_nontemporal_load(a) : *a;
       }
@@ -313,18 +318,17 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     const uint32_t rg = r1 > r0 ? r1 - r0 : 0u;
     return min(rg, (uint32_t)(kPage * G));
   };
-  // Packed V runs of a pair, flat; lanes past the end of a run read the zero line.
+  // Packed V runs of a pair, flat; lanes past the end of a run read its last unit (of an empty run
+  // the store's first), which no token refers to.
 #define STC_ISSUE_V(vreg, M)                                                                   \
   static_for<0, 2>([&](auto x) {                                                               \
-    const uint32_t rbytes = run_groups(M, x) * gbytes + vgate;                                 \
-    const unsigned char* vrun =                                                                \
-        ((M.pgs[x] >= 0 && is_tail(M.pgs[x])) ? vts : vs) + (size_t)M.run0[x] * gbytes;        \
+    const uint32_t rbytes = run_groups(M, x) * gbytes;                                         \
+    const unsigned char* vrun = ((M.pgs[x] >= 0 && is_tail(M.pgs[x])) ? vts : vs) +            \
+                                (rbytes ? (size_t)M.run0[x] * gbytes : (size_t)0);             \
+    const uint32_t last = rbytes ? rbytes - 16u : 0u;                                          \
     static_for<0, C::NLD>([&](auto j) {                                                        \
-      const uint32_t bo = (j * 64 + lane) * 16;                                                \
-      /* one address computed with integer selects, so that it stays a single request */      \
-      const uintptr_t a = bo < rbytes ? (uintptr_t)vrun + bo : (uintptr_t)&stc_zero16;         \
-      const auto* ga = (const __attribute__((address_space(1))) u32x4*)a; /* not flat */       \
-      vreg[x][j] = STREAM ? __builtin_nontemporal_load(ga) : *ga;                              \
+      const u32x4* a = (const u32x4*)(vrun + min((uint32_t)((j * 64 + lane) * 16), last));     \
+      vreg[x][j] = STREAM ? __builtin_nontemporal_load(a) : *a;                                \
     });                                                                                        \
   })
 
@@ -395,8 +399,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
         mx = fmaxf(mx, s[x][i]);
       }
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = across_k_groups(mx, [](float a, float b) { return fmaxf(a, b); });
     const float m_pair = fmaxf(kNegBig, mx);
     float p[8];
     float psum = 0.f;
@@ -484,9 +487,6 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     // requested as soon as the current pair's K pages have left their registers.
     for (int pair = 0;; ++pair) {
       finish_meta(meta);
-      uint32_t vgate;
-      // 0, after they arrive
-      asm volatile("v_and_b32 %0, 0, %1" : "=v"(vgate) : "v"(meta.off ^ meta.mk));
       u32x4 vreg[2][C::NLD];
       STC_ISSUE_V(vreg, meta);
       __builtin_amdgcn_sched_barrier(0);
@@ -520,53 +520,68 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     for (int cb = 0; cb < C::CB; ++cb) acc[cb] = sum[cb];
   }
   // sum of weights of head r16 over this wavefront's tokens
-  float l = l_part + __shfl_xor(l_part, 16);
-  l += __shfl_xor(l, 32);
+  const float l = across_k_groups(l_part, [](float a, float b) { return a + b; });
 
   // ---- merge the workgroup's wavefronts: each leaves (m, l, acc[16][D]) in its own LDS region.
   // acc[cb][i] of lane (head r16, kg) is channel (4*kg + i)*CB + cb.
   float* macc = (float*)wl;             // [16][MROW]
   float* mml = (float*)(wl + C::MML);    // [16][2]
+  if (r16 < R) {  // the other columns are copies of head 0
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float* dst = macc + r16 * C::MROW + (4 * kg + i) * C::CB;
+    for (int i = 0; i < 4; ++i) {
+      float* dst = macc + r16 * C::MROW + (4 * kg + i) * C::CB;
 #pragma unroll
-    for (int c4 = 0; c4 < C::CB / 4; ++c4)
-      *(f32x4*)(dst + 4 * c4) = f32x4{acc[4 * c4][i], acc[4 * c4 + 1][i], acc[4 * c4 + 2][i],
-                                      acc[4 * c4 + 3][i]};
-  }
-  if (kg == 0) {
-    mml[r16 * 2] = m_run;
-    mml[r16 * 2 + 1] = l;
+      for (int c4 = 0; c4 < C::CB / 4; ++c4)
+        *(f32x4*)(dst + 4 * c4) = f32x4{acc[4 * c4][i], acc[4 * c4 + 1][i], acc[4 * c4 + 2][i],
+                                        acc[4 * c4 + 3][i]};
+    }
+    if (kg == 0) *(f32x2*)(mml + r16 * 2) = f32x2{m_run, l};
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < R * D; i += 64 * WAVES) {
-    const int head = i / D, c = i % D;
-    float mw[WAVES], m = kNegBig;
+  // A thread takes 4 adjacent channels of a head, or one where that still is one round and the
+  // channels are divided by the sum (divisions of a thread follow each other; one head of 64
+  // channels: 6.5 us per step with 4, 6.3 with one).
+  auto merge = [&](auto vec) {
+    constexpr int V = vec;
+    typedef __attribute__((ext_vector_type(V), aligned(4 * V))) float fvec;
+    typedef __attribute__((ext_vector_type(V), aligned(V > 1 ? 8 : 4))) float fvec_partial;
+    for (int i = threadIdx.x; i < R * (D / V); i += 64 * WAVES) {
+      const int head = i / (D / V), c = i % (D / V) * V;
+      f32x2 ml[WAVES];
+      fvec part[WAVES];
+      float m = kNegBig;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      mw[w] = ((const float*)(lds + w * C::WAVE_LDS + C::MML))[head * 2];
-      m = fmaxf(m, mw[w]);
-    }
-    float lsum = 0.f, a = 0.f;
+      for (int w = 0; w < WAVES; ++w) {
+        ml[w] = *(const f32x2*)(lds + w * C::WAVE_LDS + C::MML + head * 8);
+        part[w] = *(const fvec*)(lds + w * C::WAVE_LDS + (head * C::MROW + c) * 4);
+        m = fmaxf(m, ml[w].x);
+      }
+      float lsum = 0.f;
+      fvec a = 0.f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const float wgt = __builtin_amdgcn_exp2f(mw[w] - m);
-      lsum = fmaf(wgt, ((const float*)(lds + w * C::WAVE_LDS + C::MML))[head * 2 + 1], lsum);
-      a = fmaf(wgt, ((const float*)(lds + w * C::WAVE_LDS))[head * C::MROW + c], a);
-    }
-    const size_t hf = (size_t)stream * R + head;
-    if (splits == 1) {
-      out[hf * D + c] = lsum > 0.f ? a / lsum : 0.f;
-    } else {
-      float* pr = partial + (hf * splits + split) * partial_stride(D);
-      pr[2 + c] = a;
-      if (c == 0) {
-        pr[0] = m;
-        pr[1] = lsum;
+      for (int w = 0; w < WAVES; ++w) {
+        const float wgt = __builtin_amdgcn_exp2f(ml[w].x - m);
+        lsum = fmaf(wgt, ml[w].y, lsum);
+#pragma unroll
+        for (int e = 0; e < V; ++e) a[e] = fmaf(wgt, part[w][e], a[e]);
+      }
+      const size_t hf = (size_t)stream * R + head;
+      if (splits == 1) {
+        fvec o;
+#pragma unroll
+        for (int e = 0; e < V; ++e) o[e] = lsum > 0.f ? a[e] / lsum : 0.f;
+        *(fvec*)(out + hf * D + c) = o;
+      } else {
+        float* pr = partial + (hf * splits + split) * partial_stride(D);
+        *(fvec_partial*)(pr + 2 + c) = a;
+        if (c == 0) *(f32x2*)pr = f32x2{m, lsum};
       }
     }
-  }
+  };
+  if (splits == 1 && R * D <= 64 * WAVES)
+    merge(IC<1>{});
+  else
+    merge(IC<4>{});
   // One pair per wavefront: the list is written behind all loads, with which a store in front of
   // them would be waited for.
   if constexpr (SELECT_IPT > 0 && !MULTI) {
