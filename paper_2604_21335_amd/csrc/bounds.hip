@@ -1,30 +1,10 @@
 // Quest page summary: per-page, per-channel min and max of the cached keys
 // (token-level stage of the paper, Sec. 3.2; chunk size 16 from App. C.1).
+#include "build_helpers.hpp"
 #include "stc_common.hpp"
 #include "stc_kernels.hpp"
 
 namespace stc {
-
-typedef __attribute__((ext_vector_type(2))) short i16x2;
-typedef __attribute__((ext_vector_type(4))) uint32_t bounds_u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t bounds_u32x2;
-
-// Two bf16 patterns per dword <-> two signed 16-bit integers in the same order (-0 below +0);
-// the map is its own inverse.
-__device__ __forceinline__ i16x2 bf16_order2(i16x2 x) {
-  return x ^ ((x >> 15) & (i16x2){0x7fff, 0x7fff});
-}
-
-// Lanes that differ in lane bit 5 (SWAP 32) or bit 4 (SWAP 16) hold the same two quantities a
-// and b for different rows: the swap gives one half of the lanes both values of a, the other
-// half both values of b, so one min/max reduces both.
-template <int SWAP, class Op>
-__device__ __forceinline__ i16x2 fold_pair(i16x2 a, i16x2 b, Op op) {
-  const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-  const auto r = SWAP == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
-                            : __builtin_amdgcn_permlane16_swap(x, y, false, false);
-  return op(__builtin_bit_cast(i16x2, (uint32_t)r[0]), __builtin_bit_cast(i16x2, (uint32_t)r[1]));
-}
 
 constexpr int kBoundsWavePages = 2;  // adjacent pages per wavefront, all requested at once
 constexpr int kBoundsStreamWaves = 7;  // streams of at most this many wavefronts are one workgroup
@@ -70,41 +50,11 @@ __global__ __launch_bounds__(64 * kBoundsStreamWaves) void bounds_kernel(
       v[p][j] = __builtin_nontemporal_load(
           Ks + (size_t)min((p0 + p) * kPage + j * RPL + row, N - 1) * LPR);
   uint32_t* tiles = bounds + (size_t)stream * bounds_tiles(Ncap) * bounds_tile_dwords(D);
-  auto lo = [](i16x2 a, i16x2 b) { return __builtin_elementwise_min(a, b); };
-  auto hi = [](i16x2 a, i16x2 b) { return __builtin_elementwise_max(a, b); };
-  const int c = 8 * piece + 2 * (lane >> 4);
-  auto put = [&](int page, bounds_u32x2 w) {
-    if (D == 128 || (lane & 8) == 0)
-      *(bounds_u32x2*)(tiles + (size_t)(page / kBoundsTilePages) * bounds_tile_dwords(D) +
-                       bounds_tile_unit(D, page % kBoundsTilePages, c) * 4 + c % 4) = w;
-  };
 #pragma unroll
-  for (int p = 0; p < PW; ++p) {
-    i16x2 mn[4], mx[4];  // channels 8*piece + 2*d, +1
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-#pragma unroll
-      for (int j = 0; j < NLD; ++j) {
-        const i16x2 k = bf16_order2(__builtin_bit_cast(i16x2, (uint32_t)v[p][j][d]));
-        mn[d] = j ? lo(mn[d], k) : k;
-        mx[d] = j ? hi(mx[d], k) : k;
-      }
-    }
-    // lane bit 5 chooses between dwords d and d + 2, lane bit 4 between d and d + 1
-    i16x2 a = fold_pair<16>(fold_pair<32>(mn[0], mn[2], lo), fold_pair<32>(mn[1], mn[3], lo), lo);
-    i16x2 b = fold_pair<16>(fold_pair<32>(mx[0], mx[2], hi), fold_pair<32>(mx[1], mx[3], hi), hi);
-    if constexpr (D == 64) {  // rows also differ in lane bit 3
-      a = lo(a, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, a))));
-      b = hi(b, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, b))));
-    }
-    uint32_t mnw = __builtin_bit_cast(uint32_t, bf16_order2(a));
-    uint32_t mxw = __builtin_bit_cast(uint32_t, bf16_order2(b));
-    if (p0 + p >= NP) mnw = mxw = 0u;  // a padding page of the stream's last tile
-    // minimum in the low half, maximum in the high half of each channel's dword
-    put(p0 + p, bounds_u32x2{(mnw & 0xffffu) | (mxw << 16), (mnw >> 16) | (mxw & 0xffff0000u)});
-  }
+  for (int p = 0; p < PW; ++p) store_page_bounds<D>(tiles, p0 + p, p0 + p < NP, v[p], lane);
   if (gridDim.x == 1 && p0 + PW >= NP)  // the padding pages behind the last wavefront's own
-    for (int page = p0 + PW; page < ptile; ++page) put(page, bounds_u32x2{0u, 0u});
+    for (int page = p0 + PW; page < ptile; ++page)
+      put_page_bounds<D>(tiles, page, bounds_u32x2{0u, 0u}, lane);
 }
 
 int launch_bounds(const stc_shape_t& s, const void* K, void* bounds, hipStream_t st) {

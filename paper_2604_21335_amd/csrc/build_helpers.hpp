@@ -56,46 +56,73 @@ __device__ __forceinline__ uint32_t rank_mask(const float* __restrict__ lp, int 
   }
 }
 
-// Minimum and maximum of 8 adjacent channels over `ntok` token rows (row stride D*2 bytes,
-// `row` points at the 16-byte piece of the first row); w[i] = min | max << 16 as bf16 bits,
-// -0 ordered below +0.  ntok <= 0 gives zeros.
-template <int D>
-__device__ __forceinline__ void page_bounds_words(const uint4* row, int ntok,
-                                                  uint32_t (&w)[8]) {
-  constexpr int LPP = D / 8;
-  int mn[8], mx[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    mn[i] = 0x7fffffff;
-    mx[i] = (int)0x80000000;
-  }
-#pragma unroll 4
-  for (int t = 0; t < ntok; ++t, row += LPP) {
-    const uint4 v = *row;
-    const uint32_t x[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int a = bf16_order(x[i] & 0xffffu);
-      const int b = bf16_order(x[i] >> 16);
-      mn[2 * i] = min(mn[2 * i], a);
-      mx[2 * i] = max(mx[2 * i], a);
-      mn[2 * i + 1] = min(mn[2 * i + 1], b);
-      mx[2 * i + 1] = max(mx[2 * i + 1], b);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-    w[i] = ntok > 0 ? (bf16_unorder(mn[i]) | (bf16_unorder(mx[i]) << 16)) : 0u;
+typedef __attribute__((ext_vector_type(2))) short i16x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t bounds_u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t bounds_u32x2;
+
+// Two bf16 patterns per dword <-> two signed 16-bit integers in the same order (-0 below +0);
+// the map is its own inverse.
+__device__ __forceinline__ i16x2 bf16_order2(i16x2 x) {
+  return x ^ ((x >> 15) & (i16x2){0x7fff, 0x7fff});
 }
 
-// The two 16-byte units of channels 8*sub .. 8*sub+7 of page `page` in the tiled bounds layout.
+// Lanes that differ in lane bit 5 (SWAP 32) or bit 4 (SWAP 16) hold the same two quantities a
+// and b for different rows: the swap gives one half of the lanes both values of a, the other
+// half both values of b, so one min/max reduces both.
+template <int SWAP, class Op>
+__device__ __forceinline__ i16x2 fold_pair(i16x2 a, i16x2 b, Op op) {
+  const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+  const auto r = SWAP == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                            : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+  return op(__builtin_bit_cast(i16x2, (uint32_t)r[0]), __builtin_bit_cast(i16x2, (uint32_t)r[1]));
+}
+
+// A wavefront's part of a page's bounds in the tiled layout: the two channels 8*piece + 2*(lane/16), +1
+// of the lane's piece (lane % (D/8)), as (minimum | maximum << 16) each.
 template <int D>
-__device__ __forceinline__ void store_bounds_units(uint4* __restrict__ stream_tiles, int page,
-                                                   int sub, const uint32_t (&w)[8]) {
-  uint4* tile = stream_tiles + (size_t)(page / kBoundsTilePages) * (bounds_tile_dwords(D) / 4);
-  const int pt = page % kBoundsTilePages;
-  tile[bounds_tile_unit(D, pt, 8 * sub)] = make_uint4(w[0], w[1], w[2], w[3]);
-  tile[bounds_tile_unit(D, pt, 8 * sub + 4)] = make_uint4(w[4], w[5], w[6], w[7]);
+__device__ __forceinline__ void put_page_bounds(uint32_t* __restrict__ stream_tiles, int page,
+                                                bounds_u32x2 w, int lane) {
+  const int c = 8 * (lane % (D / 8)) + 2 * (lane >> 4);
+  if (D == 128 || (lane & 8) == 0)
+    *(bounds_u32x2*)(stream_tiles + (size_t)(page / kBoundsTilePages) * bounds_tile_dwords(D) +
+                     bounds_tile_unit(D, page % kBoundsTilePages, c) * 4 + c % 4) = w;
+}
+
+// The bounds of a page by one wavefront.  v[j]: the lane's 16-byte piece of row j*RPL + lane/LPR, with
+// LPR = D/8 lanes per token row and RPL = 64/LPR rows per request, so that lanes l + LPR*i hold
+// the same channels of different rows.  Minima and maxima are taken on packed 16-bit integers, first
+// over a lane's own rows, then across lanes by swapping halves of register pairs, which leaves
+// every lane with the minimum and maximum of two channels.  !present: a padding page, zeros.
+template <int D>
+__device__ __forceinline__ void store_page_bounds(uint32_t* __restrict__ stream_tiles, int page,
+                                                  bool present, const bounds_u32x4 (&v)[D / 32],
+                                                  int lane) {
+  auto lo = [](i16x2 a, i16x2 b) { return __builtin_elementwise_min(a, b); };
+  auto hi = [](i16x2 a, i16x2 b) { return __builtin_elementwise_max(a, b); };
+  i16x2 mn[4], mx[4];  // channels 8*piece + 2*d, +1
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j) {
+      const i16x2 k = bf16_order2(__builtin_bit_cast(i16x2, (uint32_t)v[j][d]));
+      mn[d] = j ? lo(mn[d], k) : k;
+      mx[d] = j ? hi(mx[d], k) : k;
+    }
+  }
+  // lane bit 5 chooses between dwords d and d + 2, lane bit 4 between d and d + 1
+  i16x2 a = fold_pair<16>(fold_pair<32>(mn[0], mn[2], lo), fold_pair<32>(mn[1], mn[3], lo), lo);
+  i16x2 b = fold_pair<16>(fold_pair<32>(mx[0], mx[2], hi), fold_pair<32>(mx[1], mx[3], hi), hi);
+  if constexpr (D == 64) {  // rows also differ in lane bit 3
+    a = lo(a, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, a))));
+    b = hi(b, __builtin_bit_cast(i16x2, dpp_f32<0x128>(__builtin_bit_cast(float, b))));
+  }
+  uint32_t mnw = __builtin_bit_cast(uint32_t, bf16_order2(a));
+  uint32_t mxw = __builtin_bit_cast(uint32_t, bf16_order2(b));
+  if (!present) mnw = mxw = 0u;
+  // minimum in the low half, maximum in the high half of each channel's dword
+  put_page_bounds<D>(
+      stream_tiles, page,
+      bounds_u32x2{(mnw & 0xffffu) | (mxw << 16), (mnw >> 16) | (mxw & 0xffff0000u)}, lane);
 }
 
 }  // namespace stc

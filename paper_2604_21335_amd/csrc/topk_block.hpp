@@ -5,41 +5,6 @@
 
 namespace stc {
 
-// One step of a wavefront scan on the data-parallel-primitive path (no LDS traffic): lanes
-// whose source lies outside the row, or whose row is masked off, combine with `ident`.
-#define STC_DPP_STEP(v, op, ident, ctrl, row_mask) \
-  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(ident), (int)(v), ctrl, row_mask, 0xf, false))
-
-struct OpAdd {
-  __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; }
-};
-struct OpMin {
-  __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return min(a, b); }
-};
-struct OpMax {
-  __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return max(a, b); }
-};
-
-// Inclusive scan over the 64 lanes: shifts by 1, 2, 4, 8 inside each row of 16 lanes, then
-// lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2 and 3.
-template <class Op>
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v, Op op, uint32_t ident) {
-  STC_DPP_STEP(v, op, ident, 0x111, 0xf);  // row_shr:1
-  STC_DPP_STEP(v, op, ident, 0x112, 0xf);  // row_shr:2
-  STC_DPP_STEP(v, op, ident, 0x114, 0xf);  // row_shr:4
-  STC_DPP_STEP(v, op, ident, 0x118, 0xf);  // row_shr:8
-  STC_DPP_STEP(v, op, ident, 0x142, 0xa);  // row_bcast:15 into rows 1 and 3
-  STC_DPP_STEP(v, op, ident, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-#undef STC_DPP_STEP
-
-// Reduction over the 64 lanes, in a scalar register.
-template <class Op>
-__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op, uint32_t ident) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(v, op, ident), 63);
-}
-
 __device__ __forceinline__ int wave_incl_scan(int v, int /*lane*/) {
   return (int)wave_scan((uint32_t)v, OpAdd{}, 0u);
 }
