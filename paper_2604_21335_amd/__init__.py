@@ -14,6 +14,7 @@ from . import workloads  # noqa: F401  (seeded synthetic inputs)
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libstc.so")
+BINDING_PATH = os.path.join(_PKG_DIR, "_binding.so")   # unpacks tensors for libstc.so
 
 STC_OK = 0
 STC_ERR_NULL, STC_ERR_SHAPE, STC_ERR_ALIGN, STC_ERR_WORKSPACE, STC_ERR_LAUNCH = -1, -2, -3, -4, -5
@@ -50,6 +51,7 @@ def make_shape(B, Hq, Hkv, D, N, G, v_cap_groups, P=16, N_cap=0):
 
 
 _lib = None
+_native = None
 
 
 def load_library():
@@ -58,7 +60,7 @@ def load_library():
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(BINDING_PATH):
         from .build import build_library
         build_library()
     lib = ctypes.CDLL(LIB_PATH)
@@ -120,42 +122,18 @@ def status_string(status):
     return load_library().stc_status_string(int(status)).decode()
 
 
-def _ptr(t, dtype=None, name="tensor"):
-    """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
-    if t is None:
-        return None
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise TypeError("%s must be a CUDA tensor" % name)
-    if not t.is_contiguous():
-        raise ValueError("%s must be contiguous" % name)
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
-        raise TypeError("%s has dtype %s" % (name, t.dtype))
-    return ctypes.c_void_p(t.data_ptr())
+def _current_stream():
+    return torch.cuda.current_stream().cuda_stream
 
 
-# The current stream's handle without building a torch.cuda.Stream object for it: 0.3 us per
-# call instead of 2.8, of about 12 that a small call takes to issue.  (A build of torch that
-# does not have the accessor is asked the long way.)
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
-def _stream():
-    if _raw_stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
-
-
-def _nbytes(t):
-    return 0 if t is None else t.numel() * t.element_size()
-
-
-def _check(status, where):
-    if status != STC_OK:
-        raise StcError(status, where)
-
-
-_U16 = (torch.int16, torch.uint16)
-_U32 = (torch.int32, torch.uint32)
+def _load_native():
+    """The module that unpacks the tensors of a call (csrc/binding.cpp)."""
+    global _native
+    if _native is None:
+        load_library()
+        from . import _binding
+        _native = _binding
+    return _native
 
 
 def stc_version():
@@ -185,99 +163,59 @@ def bounds_rows(bounds, shape):
 
 
 def stc_build_page_bounds(shape, K, bounds):
-    _check(load_library().stc_build_page_bounds(
-        ctypes.byref(shape), _ptr(K, torch.bfloat16, "K"), _ptr(bounds, torch.bfloat16, "bounds"),
-        _stream()), "stc_build_page_bounds")
+    (_native or _load_native()).build_page_bounds(shape, K, bounds)
 
 
 def stc_route_and_pack_values(shape, mode, V, logits, kcount, fixed_k, mask_in, mask, tok_off,
                               vpacked, dev_status, ws):
-    _check(load_library().stc_route_and_pack_values(
-        ctypes.byref(shape), mode, _ptr(V, torch.bfloat16, "V"),
-        _ptr(logits, torch.float32, "logits"), _ptr(kcount, torch.uint8, "kcount"), int(fixed_k),
-        _ptr(mask_in, _U16, "mask_in"), _ptr(mask, _U16, "mask"), _ptr(tok_off, _U32, "tok_off"),
-        _ptr(vpacked, torch.bfloat16, "vpacked"), _ptr(dev_status, torch.int32, "dev_status"),
-        _ptr(ws, None, "ws"), _nbytes(ws), _stream()), "stc_route_and_pack_values")
+    (_native or _load_native()).route_and_pack_values(
+        shape, mode, V, logits, kcount, fixed_k, mask_in, mask, tok_off, vpacked, dev_status, ws)
 
 
 def stc_select_pages(shape, q, bounds, k_pages, page_idx, page_score, ws):
-    _check(load_library().stc_select_pages(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        int(k_pages), _ptr(page_idx, torch.int32, "page_idx"),
-        _ptr(page_score, torch.float32, "page_score"), _ptr(ws, None, "ws"), _nbytes(ws),
-        _stream()), "stc_select_pages")
+    (_native or _load_native()).select_pages(shape, q, bounds, k_pages, page_idx, page_score, ws)
 
 
 def stc_score_pages(shape, q, bounds, page_score):
-    _check(load_library().stc_score_pages(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        _ptr(page_score, torch.float32, "page_score"), _stream()), "stc_score_pages")
+    (_native or _load_native()).score_pages(shape, q, bounds, page_score)
 
 
 def stc_decode_attention(shape, q, K, vpacked, mask, tok_off, page_idx, k_pages, out, ws):
-    _check(load_library().stc_decode_attention(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(K, torch.bfloat16, "K"),
-        _ptr(vpacked, torch.bfloat16, "vpacked"), _ptr(mask, _U16, "mask"),
-        _ptr(tok_off, _U32, "tok_off"), _ptr(page_idx, torch.int32, "page_idx"), int(k_pages),
-        _ptr(out, torch.float32, "out"), _ptr(ws, None, "ws"), _nbytes(ws), _stream()),
-        "stc_decode_attention")
+    (_native or _load_native()).decode_attention(shape, q, K, vpacked, mask, tok_off, page_idx,
+                                                 k_pages, out, ws)
 
 
 def stc_select_pages_per_head(shape, q, bounds, k_pages, page_idx, page_score, ws):
-    _check(load_library().stc_select_pages_per_head(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        int(k_pages), _ptr(page_idx, torch.int32, "page_idx"),
-        _ptr(page_score, torch.float32, "page_score"), _ptr(ws, None, "ws"), _nbytes(ws),
-        _stream()), "stc_select_pages_per_head")
+    (_native or _load_native()).select_pages_per_head(shape, q, bounds, k_pages, page_idx,
+                                                      page_score, ws)
 
 
 def stc_decode_attention_per_head(shape, q, K, vpacked, mask, tok_off, page_idx, k_pages, out, ws):
-    _check(load_library().stc_decode_attention_per_head(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(K, torch.bfloat16, "K"),
-        _ptr(vpacked, torch.bfloat16, "vpacked"), _ptr(mask, _U16, "mask"),
-        _ptr(tok_off, _U32, "tok_off"), _ptr(page_idx, torch.int32, "page_idx"), int(k_pages),
-        _ptr(out, torch.float32, "out"), _ptr(ws, None, "ws"), _nbytes(ws), _stream()),
-        "stc_decode_attention_per_head")
+    (_native or _load_native()).decode_attention_per_head(shape, q, K, vpacked, mask, tok_off,
+                                                          page_idx, k_pages, out, ws)
 
 
 def stc_flush_tail(shape, K_tail, V_tail, n_flush, n_tail, tail_cap, mode, logits, kcount, fixed_k, mask_in,
                    K, bounds, mask, tok_off, vpacked, dev_status):
-    _check(load_library().stc_flush_tail(
-        ctypes.byref(shape), _ptr(K_tail, torch.bfloat16, "K_tail"),
-        _ptr(V_tail, torch.bfloat16, "V_tail"), int(n_flush), int(n_tail), int(tail_cap), int(mode),
-        _ptr(logits, torch.float32, "logits"), _ptr(kcount, torch.uint8, "kcount"), int(fixed_k),
-        _ptr(mask_in, _U16, "mask_in"), _ptr(K, torch.bfloat16, "K"),
-        _ptr(bounds, torch.bfloat16, "bounds"), _ptr(mask, _U16, "mask"),
-        _ptr(tok_off, _U32, "tok_off"), _ptr(vpacked, torch.bfloat16, "vpacked"),
-        _ptr(dev_status, torch.int32, "dev_status"), _stream()), "stc_flush_tail")
+    (_native or _load_native()).flush_tail(
+        shape, K_tail, V_tail, n_flush, n_tail, tail_cap, mode, logits, kcount, fixed_k, mask_in, K,
+        bounds, mask, tok_off, vpacked, dev_status)
 
 
 def stc_union_pages(shape, page_idx_per_head, k_pages, union_idx, union_heads):
-    _check(load_library().stc_union_pages(
-        ctypes.byref(shape), _ptr(page_idx_per_head, torch.int32, "page_idx_per_head"),
-        int(k_pages), _ptr(union_idx, torch.int32, "union_idx"),
-        _ptr(union_heads, _U16, "union_heads"), int(union_idx.shape[-1]), _stream()),
-        "stc_union_pages")
+    (_native or _load_native()).union_pages(shape, page_idx_per_head, k_pages, union_idx,
+                                            union_heads, union_idx.shape[-1])
 
 
 def stc_decode_attention_union(shape, q, K, vpacked, mask, tok_off, union_idx, union_heads, out,
                                ws):
-    _check(load_library().stc_decode_attention_union(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(K, torch.bfloat16, "K"),
-        _ptr(vpacked, torch.bfloat16, "vpacked"), _ptr(mask, _U16, "mask"),
-        _ptr(tok_off, _U32, "tok_off"), _ptr(union_idx, torch.int32, "union_idx"),
-        _ptr(union_heads, _U16, "union_heads"), int(union_idx.shape[-1]),
-        _ptr(out, torch.float32, "out"), _ptr(ws, None, "ws"), _nbytes(ws), _stream()),
-        "stc_decode_attention_union")
+    (_native or _load_native()).decode_attention_union(
+        shape, q, K, vpacked, mask, tok_off, union_idx, union_heads, union_idx.shape[-1], out, ws)
 
 
 def stc_decode_step(shape, q, bounds, K, vpacked, mask, tok_off, k_pages, page_idx, out, ws):
-    _check(load_library().stc_decode_step(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        _ptr(K, torch.bfloat16, "K"), _ptr(vpacked, torch.bfloat16, "vpacked"),
-        _ptr(mask, _U16, "mask"), _ptr(tok_off, _U32, "tok_off"), int(k_pages),
-        _ptr(page_idx, torch.int32, "page_idx"), _ptr(out, torch.float32, "out"),
-        _ptr(ws, None, "ws"), _nbytes(ws), _stream()), "stc_decode_step")
+    (_native or _load_native()).decode_step(shape, q, bounds, K, vpacked, mask, tok_off, k_pages,
+                                            page_idx, out, ws)
 
 
 STC_STATIC_SCRATCH_BYTES = 8 * 1024 * 1024
@@ -285,43 +223,26 @@ STC_STATIC_SCRATCH_BYTES = 8 * 1024 * 1024
 
 def stc_decode_step_static(shape, q, bounds, K, vpacked, mask, tok_off, k_pages, page_idx, out):
     """stc_decode_step over the library's own static scratch array: no workspace argument."""
-    _check(load_library().stc_decode_step_static(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        _ptr(K, torch.bfloat16, "K"), _ptr(vpacked, torch.bfloat16, "vpacked"),
-        _ptr(mask, _U16, "mask"), _ptr(tok_off, _U32, "tok_off"), int(k_pages),
-        _ptr(page_idx, torch.int32, "page_idx"), _ptr(out, torch.float32, "out"), _stream()),
-        "stc_decode_step_static")
+    (_native or _load_native()).decode_step_static(shape, q, bounds, K, vpacked, mask, tok_off,
+                                                   k_pages, page_idx, out)
 
 
 def stc_decode_step_tail(shape, q, bounds, K, vpacked, mask, tok_off, k_pages, K_tail, V_tail,
                          n_tail, tail_cap, page_idx, out, ws):
-    _check(load_library().stc_decode_step_tail(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(bounds, torch.bfloat16, "bounds"),
-        _ptr(K, torch.bfloat16, "K"), _ptr(vpacked, torch.bfloat16, "vpacked"),
-        _ptr(mask, _U16, "mask"), _ptr(tok_off, _U32, "tok_off"), int(k_pages),
-        _ptr(K_tail, torch.bfloat16, "K_tail"), _ptr(V_tail, torch.bfloat16, "V_tail"),
-        int(n_tail), int(tail_cap), _ptr(page_idx, torch.int32, "page_idx"),
-        _ptr(out, torch.float32, "out"), _ptr(ws, None, "ws"), _nbytes(ws), _stream()),
-        "stc_decode_step_tail")
+    (_native or _load_native()).decode_step_tail(
+        shape, q, bounds, K, vpacked, mask, tok_off, k_pages, K_tail, V_tail, n_tail, tail_cap,
+        page_idx, out, ws)
 
 
 def stc_decode_attention_tail(shape, q, K, vpacked, mask, tok_off, page_idx, k_pages, K_tail,
                               V_tail, n_tail, tail_cap, out, ws):
-    _check(load_library().stc_decode_attention_tail(
-        ctypes.byref(shape), _ptr(q, torch.bfloat16, "q"), _ptr(K, torch.bfloat16, "K"),
-        _ptr(vpacked, torch.bfloat16, "vpacked"), _ptr(mask, _U16, "mask"),
-        _ptr(tok_off, _U32, "tok_off"), _ptr(page_idx, torch.int32, "page_idx"), int(k_pages),
-        _ptr(K_tail, torch.bfloat16, "K_tail"), _ptr(V_tail, torch.bfloat16, "V_tail"),
-        int(n_tail), int(tail_cap), _ptr(out, torch.float32, "out"), _ptr(ws, None, "ws"),
-        _nbytes(ws), _stream()), "stc_decode_attention_tail")
+    (_native or _load_native()).decode_attention_tail(
+        shape, q, K, vpacked, mask, tok_off, page_idx, k_pages, K_tail, V_tail, n_tail, tail_cap,
+        out, ws)
 
 
 def stc_append_tail(shape, k_new, v_new, K_tail, V_tail, n_tail, tail_cap):
-    _check(load_library().stc_append_tail(
-        ctypes.byref(shape), _ptr(k_new, torch.bfloat16, "k_new"),
-        _ptr(v_new, torch.bfloat16, "v_new"), _ptr(K_tail, torch.bfloat16, "K_tail"),
-        _ptr(V_tail, torch.bfloat16, "V_tail"), int(n_tail), int(tail_cap), _stream()),
-        "stc_append_tail")
+    (_native or _load_native()).append_tail(shape, k_new, v_new, K_tail, V_tail, n_tail, tail_cap)
 
 
 def stc_router_logits(h, W, bias, logits, Hkv):
@@ -335,17 +256,12 @@ def stc_router_logits(h, W, bias, logits, Hkv):
         if tuple(bias.shape) != (B, G):
             raise ValueError("a per-element bias must be [B, G]")
         per_batch = 1
-    _check(load_library().stc_router_logits(
-        B, Hkv, N, dm, G, _ptr(h, torch.bfloat16, "h"), _ptr(W, torch.bfloat16, "W"),
-        _ptr(bias, torch.float32, "bias"), per_batch, _ptr(logits, torch.float32, "logits"),
-        _stream()), "stc_router_logits")
+    (_native or _load_native()).router_logits(B, Hkv, N, dm, G, h, W, bias, per_batch, logits)
 
 
 def stc_compact_tokens(src, token_idx, dst, B, Hkv, N_src, n_keep, D, dev_status=None):
-    _check(load_library().stc_compact_tokens(
-        _ptr(src, torch.bfloat16, "src"), _ptr(token_idx, torch.int32, "token_idx"),
-        _ptr(dst, torch.bfloat16, "dst"), B, Hkv, N_src, n_keep, D,
-        _ptr(dev_status, torch.int32, "dev_status"), _stream()), "stc_compact_tokens")
+    (_native or _load_native()).compact_tokens(src, token_idx, dst, B, Hkv, N_src, n_keep, D,
+                                               dev_status)
 
 
 class RoutedCache:
@@ -409,7 +325,6 @@ class RoutedCache:
         self.page_idx = self._page_idx_buf[:B * Hkv * self.k_eff].view(B, Hkv, self.k_eff)
         if self.k_pages >= self.NP:      # every page is kept: the list is 0 .. NP-1
             stc_select_pages(self.shape, None, None, self.k_pages, self.page_idx, None, None)
-        self._step_cache = None
         # the page scores sit at the front of the workspace of stc_decode_step: page_score is a
         # view of them, so that both forms of step() leave the scores there
         self.page_score = None
@@ -431,7 +346,6 @@ class RoutedCache:
             self.K[:, :, :self.N].copy_(K)
         else:
             self.K = K
-        self._step_cache = None
         stc_build_page_bounds(self.shape, self.K, self.bounds)
         mode = STC_ROUTE_MASK if mask_in is not None else STC_ROUTE_TOPK
         if global_k is not None:
@@ -480,25 +394,6 @@ class RoutedCache:
         stc_decode_attention(self.shape, q, self.K, self.vpacked, self.mask, self.tok_off,
                              page_idx, self.k_eff, self.out, self._ws_attn)
 
-    def _step_args(self):
-        """C arguments of the one-call step for this cache's own tensors, validated once;
-        step() fills in the query, the tail length and the stream."""
-        if self._step_cache is None:
-            fixed = [ctypes.byref(self.shape), None, _ptr(self.bounds, torch.bfloat16, "bounds"),
-                     _ptr(self.K, torch.bfloat16, "K"), _ptr(self.vpacked, torch.bfloat16, "vpacked"),
-                     _ptr(self.mask, _U16, "mask"), _ptr(self.tok_off, _U32, "tok_off"),
-                     int(self.k_eff)]
-            if self.tail_cap:
-                fixed += [_ptr(self.K_tail, torch.bfloat16, "K_tail"),
-                          _ptr(self.V_tail, torch.bfloat16, "V_tail"), 0, int(self.tail_cap)]
-            fixed += [_ptr(self.page_idx, torch.int32, "page_idx"),
-                      _ptr(self.out, torch.float32, "out"), _ptr(self._ws_step, None, "ws"),
-                      _nbytes(self._ws_step), None]
-            lib = load_library()
-            self._step_cache = (lib.stc_decode_step_tail if self.tail_cap else lib.stc_decode_step,
-                                fixed)
-        return self._step_cache
-
     def step(self, q, one_call=True):
         """One decode step: page selection, then routed attention.  When every page is kept
         there is nothing to select: the attention call takes "all pages" as a missing list.
@@ -506,12 +401,15 @@ class RoutedCache:
         instead of stc_select_pages + stc_decode_attention."""
         if self.k_pages < self.NP:
             if one_call:
-                fn, args = self._step_args()
-                args[1] = _ptr(q, torch.bfloat16, "q")
                 if self.tail_cap:
-                    args[10] = int(self.n_tail)
-                args[-1] = _stream()
-                _check(fn(*args), "stc_decode_step")
+                    stc_decode_step_tail(self.shape, q, self.bounds, self.K, self.vpacked,
+                                         self.mask, self.tok_off, self.k_eff, self.K_tail,
+                                         self.V_tail, self.n_tail, self.tail_cap, self.page_idx,
+                                         self.out, self._ws_step)
+                else:
+                    stc_decode_step(self.shape, q, self.bounds, self.K, self.vpacked, self.mask,
+                                    self.tok_off, self.k_eff, self.page_idx, self.out,
+                                    self._ws_step)
                 return self.out
             self.select(q)
         self.attend(q)

@@ -2,12 +2,16 @@
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+
+import torch
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libstc.so")
 BENCH_LIB_PATH = os.path.join(PKG_DIR, "libstc_bench.so")   # benchmark-only helpers (bench.py)
+BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")         # Python's way into libstc.so
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 
 SOURCES = ["stc_api.hip", "bounds.hip", "router.hip", "route_pack.hip", "flush.hip",
@@ -36,6 +40,19 @@ def _hipcc():
     return "hipcc"
 
 
+def _binding_cmds(obj):
+    """Compiling and linking csrc/binding.cpp: host code against the headers of the installed torch."""
+    root, include = os.path.dirname(torch.__file__), sysconfig.get_path("include")
+    compile_ = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden",
+                "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                "-I" + os.path.join(root, "include"),
+                "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                "-I" + include, "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
+    link = ["g++", "-shared", obj, "-o", BINDING_PATH, "-L" + os.path.join(root, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-L" + PKG_DIR, "-lstc", "-Wl,-rpath,$ORIGIN"]
+    return compile_, link
+
+
 def _run(cmd):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
@@ -44,7 +61,7 @@ def _run(cmd):
 
 
 def build_library(verbose=False):
-    """Compile every source and link libstc.so; always recompiles."""
+    """Compile every source, link libstc.so and Python's way into it; always recompiles."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     hipcc = _hipcc()
     objs = [os.path.join(BUILD_DIR, s.replace(".hip", ".o")) for s in SOURCES]
@@ -56,11 +73,15 @@ def build_library(verbose=False):
         if verbose and out.strip():
             print(out)
 
+    compile_binding, link_binding = _binding_cmds(os.path.join(BUILD_DIR, "binding.o"))
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        binding = ex.submit(_run, compile_binding)
         list(ex.map(one, zip(SOURCES, objs)))
+        binding.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
     _run([hipcc, *HIPCC_FLAGS, "-shared", "-o", BENCH_LIB_PATH,
           os.path.join(CSRC, "bench_stream.hip")])
+    _run(link_binding)
     return LIB_PATH
 
 
