@@ -112,20 +112,15 @@ __device__ __forceinline__ uint32_t logit_key(float f) {
 // Exclusive prefix sum over a 1024-thread block (thread order); *total = block sum.
 __device__ __forceinline__ uint32_t block_exscan_1024(uint32_t v, uint32_t* lds16,
                                                       uint32_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t inc = v;
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  constexpr int NW = kGlobalThreads / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t inc = wave_scan(v, OpAdd{}, 0u);
   if (lane == 63) lds16[wave] = inc;
   __syncthreads();
-  uint32_t base = 0, tot = 0;
-  for (int w = 0; w < kGlobalThreads / 64; ++w) {
-    if (w < wave) base += lds16[w];
-    tot += lds16[w];
-  }
-  *total = tot;
+  const uint32_t w = lane < NW ? lds16[lane] : 0u;  // every wavefront scans the wavefronts' sums
+  const uint32_t winc = wave_scan(w, OpAdd{}, 0u);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)winc, NW - 1);
+  const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)(winc - w), wave);
   __syncthreads();
   return base + inc - v;
 }
@@ -300,13 +295,16 @@ __global__ __launch_bounds__(kChunk) void global_mask_kernel(
 // crowds those too differs in scale and goes digit by digit, as do ranges that float cannot divide.
 // Bound by latency (histograms in LDS, block scans) and by instruction issue of the one CU.
 // Routing and packing, us, as one selection per stream in nine launches over the chip / in this form
-// with digits wherever the first bins fail and every key an atomic / now:
-//                            normal       halves       all equal      1 in 10 at -1e9  outliers x 1e4
-//   8 sets of 32768, 32 x   87/56/56     98/91/73     151/131/46     85/85/66         87/89/65
-//   4 sets of 65536         45/27/27     48/97/62      75/196/27     45/85/47         45/90/50
-//   8 sets of 1200          32/11/11     33/19/19      34/20/12      32/18/16         32/43/16
-// So sets of 65536 logits with ties or outliers are the one case that the launches over the chip do
-// faster; logits of a linear map have neither.
+// with digits wherever the first bins fail and every key an atomic / with bins in the bin and crowds
+// counted / now, with scans and reductions on the DPP path and the wanted bin's keys found by a range
+// of keys instead of every key's bin once more:
+//                        normal       halves         all equal      1 in 10 at -1e9  outliers x 1e4
+//   8 sets of 32768,
+//   32 streams each   87/56/56/53  98/91/73/66   151/131/46/41   85/85/66/62      87/89/65/61
+//   4 sets of 65536   45/27/27/23  48/97/62/53    75/196/27/19   45/85/47/42      45/90/50/45
+//   8 sets of 1200    32/11/11/10  33/19/19/16    34/20/12/9     32/18/16/13      32/43/16/13
+// So sets of 65536 logits rounded to few values are the one case that the launches over the chip do
+// faster; logits of a linear map are not like that.
 constexpr int kSmallTokens = 16384;
 // Of the first keys of a wavefront, this many in one bin are a crowd (normal logits: 0.05 expected).
 constexpr int kGlobalCrowd = 6;
@@ -345,7 +343,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   float lo = 0.f, scale = 0.f;
   uint32_t bin_of_kth = 0u;
   auto bin = [&](uint32_t k) -> uint32_t {
-    const float f = __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k);
+    const float f = __uint_as_float(~(k ^ ((uint32_t)((int)k >> 31) >> 1)));  // value of the key
     return min((uint32_t)((f - lo) * scale), (uint32_t)(kGlobalBins - 1));
   };
   // The bin that holds the key of rank `remaining` among those in the histogram, that rank in the
@@ -370,7 +368,18 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
   // The wanted key among the `cnt` keys listed in hist, one per thread.
   auto rank = [&](uint32_t cnt) __attribute__((always_inline)) {
     __syncthreads();
-    if (tid < (int)cnt) {
+    found = true;
+    if (cnt <= 64 && tid < 64) {  // one wavefront, a key per lane
+      const uint32_t mine = hist[tid];
+      uint32_t gt = 0, ge = 0;
+      for (int j = 0; j < (int)cnt; ++j) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+        gt += o > mine, ge += o >= mine;
+      }
+      if (tid < (int)cnt && gt < remaining && remaining <= ge)  // equal keys agree
+        s_pick[0] = mine, s_pick[1] = remaining - gt, s_pick[2] = ge - gt;
+    }
+    if (cnt > 64 && tid < (int)cnt) {
       const uint32_t mine = hist[tid];
       uint32_t gt = 0, ge = 0;
       for (uint32_t j = 0; j < cnt; ++j) gt += hist[j] > mine, ge += hist[j] >= mine;
@@ -381,7 +390,18 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     prefix = s_pick[0];
     remaining = s_pick[1];
     take_all = s_pick[1] == s_pick[2];
-    found = true;
+  };
+  // Smallest of the threads' kmin and largest of their kmax, through hist.
+  auto block_range = [&](uint32_t& kmin, uint32_t& kmax) __attribute__((always_inline)) {
+    constexpr int NW = kGlobalThreads / 64;
+    const int lane = tid & 63;
+    kmin = wave_reduce(kmin, OpMin{}, 0xffffffffu);
+    kmax = wave_reduce(kmax, OpMax{}, 0u);
+    if (lane == 0) hist[tid >> 6] = kmin, hist[64 + (tid >> 6)] = kmax;
+    __syncthreads();
+    kmin = wave_reduce(hist[lane & (NW - 1)], OpMin{}, 0xffffffffu);
+    kmax = wave_reduce(hist[64 + (lane & (NW - 1))], OpMax{}, 0u);
+    __syncthreads();
   };
   auto value = [](uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); };
   if (budget > 0) {
@@ -390,15 +410,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     for (int i = 0; i < TPT; ++i)
 #pragma unroll
       for (int g = 0; g < G; ++g) kmin = min(kmin, key[i][g]), kmax = max(kmax, key[i][g]);
-    for (int d = 32; d >= 1; d >>= 1) {
-      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
-      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
-    }
-    if ((tid & 63) == 0) hist[tid >> 6] = kmin, hist[64 + (tid >> 6)] = kmax;
-    __syncthreads();
-    for (int w = 0; w < kGlobalThreads / 64; ++w)
-      kmin = min(kmin, hist[w]), kmax = max(kmax, hist[64 + w]);
-    __syncthreads();
+    block_range(kmin, kmax);
     lo = value(kmin);
     const float hi = value(kmax);
     scale = (float)(kGlobalBins - 1) / (hi - lo);
@@ -442,12 +454,21 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
     remaining = s_pick[1];
     const uint32_t cnt = s_pick[2];
     if (cnt <= kGlobalRanked) {
+      // Keys from a little below the wanted bin to a little above it: a superset of the bin's, as
+      // 1/64 is more than the rounding of a bin's number (below 2^-10), and rounding is monotone.
+      const float at = (float)bin_of_kth;
+      const uint32_t k0 = logit_key(lo + (at - 0.015625f) / scale);
+      const uint32_t near = logit_key(lo + (at + 1.015625f) / scale) - k0;
 #pragma unroll
-      for (int i = 0; i < TPT; ++i)
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (token(i) < N && bin(key[i][g]) == bin_of_kth)
-            hist[atomicAdd(&s_count, 1u)] = key[i][g];
+      for (int i = 0; i < TPT; ++i) {
+        uint32_t any = 0u;
+        static_for<0, G>([&](auto g) { any |= key[i][g] - k0 <= near ? 1u << g : 0u; });
+        if (token(i) >= N) any = 0u;
+        for (; any; any &= any - 1u) {
+          const uint32_t k = pick_of(key[i], __ffs((int)any) - 1);
+          if (bin(k) == bin_of_kth) hist[atomicAdd(&s_count, 1u)] = k;
+        }
+      }
       rank(cnt);
     }
   }
@@ -463,15 +484,7 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
         for (int g = 0; g < G; ++g)
           if (token(i) < N && bin(key[i][g]) == bin_of_kth)
             klo = min(klo, key[i][g]), khi = max(khi, key[i][g]);
-      for (int d = 32; d >= 1; d >>= 1) {
-        klo = min(klo, (uint32_t)__shfl_xor((int)klo, d));
-        khi = max(khi, (uint32_t)__shfl_xor((int)khi, d));
-      }
-      if ((tid & 63) == 0) hist[tid >> 6] = klo, hist[64 + (tid >> 6)] = khi;
-      __syncthreads();
-      for (int w = 0; w < kGlobalThreads / 64; ++w)
-        klo = min(klo, hist[w]), khi = max(khi, hist[64 + w]);
-      __syncthreads();
+      block_range(klo, khi);
       if (klo == khi) {
         prefix = klo;
         take_all = remaining == s_pick[2];
@@ -555,18 +568,22 @@ __global__ __launch_bounds__(kGlobalThreads) void global_small_kernel(
         e = before + block_exscan_1024(eq, waves, &tot);
         before += tot;
       }
-      if (t < N) {
+      if (take_all) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) m |= key[i][g] >= prefix ? 1u << g : 0u;
+        if (t >= N) m = 0;
+      } else if (t < N) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           if (key[i][g] > prefix) m |= 1u << g;
-          else if (key[i][g] == prefix && (take_all || e++ < remaining)) m |= 1u << g;
+          else if (key[i][g] == prefix && e++ < remaining) m |= 1u << g;
         }
       }
     }
     if (t < N) s_mask[t] = (uint16_t)m;
-    int kept = __popc(m);  // the 64 tokens of a wavefront lie in one chunk
-    for (int d = 32; d >= 1; d >>= 1) kept += __shfl_xor(kept, d);
-    if ((tid & 63) == 0 && kept) atomicAdd(&s_chunk[t / kChunk], (uint32_t)kept);
+    // the 64 tokens of a wavefront lie in one chunk
+    const uint32_t kept = wave_reduce((uint32_t)__popc(m), OpAdd{}, 0u);
+    if ((tid & 63) == 0 && kept) atomicAdd(&s_chunk[t / kChunk], kept);
   }
   __syncthreads();
   for (int r = blockIdx.y; r < share; r += gridDim.y) {

@@ -116,4 +116,21 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op, uint32_t iden
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(v, op, ident), 63);
 }
 
+// a[j] by selects.  An array that is indexed at run time would be put into memory, which is also what
+// the compiler makes of selects between two elements unless it cannot see that they are.
+template <class T, int N>
+__device__ __forceinline__ T pick_of(const T (&a)[N], int j) {
+  if constexpr (N == 1) {
+    return a[0];
+  } else {
+    T half[N / 2];
+    static_for<0, N / 2>([&](auto i) {
+      T even = a[2 * i], odd = a[2 * i + 1];
+      asm("" : "+v"(even), "+v"(odd));
+      half[i] = (j & 1) ? odd : even;
+    });
+    return pick_of(half, j >> 1);
+  }
+}
+
 }  // namespace stc

@@ -96,23 +96,6 @@ __device__ __forceinline__ int rank_bin(int4 h4, int rank, int& above, int& cnt)
   return 4 * src + __builtin_amdgcn_readlane(f_bin, src);
 }
 
-// a[j] by selects.  An array that is indexed at run time would be put into memory, which is also what
-// the compiler makes of selects between two elements unless it cannot see that they are.
-template <int N>
-__device__ __forceinline__ int pick(const int (&a)[N], int j) {
-  if constexpr (N == 1) {
-    return a[0];
-  } else {
-    int half[N / 2];
-    static_for<0, N / 2>([&](auto i) {
-      int even = a[2 * i], odd = a[2 * i + 1];
-      asm("" : "+v"(even), "+v"(odd));
-      half[i] = (j & 1) ? odd : even;
-    });
-    return pick(half, j >> 1);
-  }
-}
-
 // Top-k pages of a stream by one workgroup of THREADS threads, NP <= THREADS * IPT pages.
 // The selected pages are handed to emit(position in the ascending list, page).  Returns false,
 // with nothing emitted, if the scores are not of the kind that it is made for (below).
@@ -245,8 +228,8 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
     if (n <= TopkLds<IPT, THREADS>::OWN) {
       for (uint32_t m = has; m; m &= m - 1u) {
         const int j = __ffs((int)m) - 1, q = j >> 2;
-        const int at = pick(start, q) + __popc(has & (0xfu << (4 * q)) & ((1u << j) - 1u));
-        S.key[wave][at] = pick(key, j);
+        const int at = pick_of(start, q) + __popc(has & (0xfu << (4 * q)) & ((1u << j) - 1u));
+        S.key[wave][at] = pick_of(key, j);
         S.page[wave][at] = (uint16_t)(first(q) + (j & 3));
       }
     } else {
