@@ -7,7 +7,7 @@ namespace stc {
 // No bound on the registers: several pairs at D = 64 held to 128 of them, for two workgroups per CU,
 // spill 2 to 11 and are slower at every number of streams (512 streams of 40 pages 15.1 us, 14.1
 // without; 256 streams of 64 pages and a tail 16.3, 13.3; 512 of 128 pages 37.8, 36.8).
-template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
+template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI, int NX>
 __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(
     const void* list_or_score, const uint16_t* q, const uint16_t* K, const uint16_t* mask,
     const uint32_t* tok_off, int NP, int k_pages, int Ncap, int R_by_xcd, const AttnParams rest) {
@@ -21,44 +21,72 @@ __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(
     stream = blockIdx.z * kXcds + blockIdx.x;
     split = blockIdx.y;
   }
-  attn_block<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>(
+  attn_block<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI, NX>(
       P, stream, split, lds, (const float*)list_or_score + (size_t)stream * NP,
       (TopkLds<SELECT_IPT, 64 * WAVES>*)lds);
 }
 
-// Merge the split partials of one query head in ascending split order.  Each
-// thread owns one channel; partials are fetched BATCH splits at a time (one round of
-// loads for up to BATCH splits) and folded in with a running maximum.  Bound by latency: a launch
-// and a round trip to memory per batch (28 layers of 16 splits: 606 -> 603 us per step with
-// batches of 16 instead of 8).
-template <int D, int BATCH>
-__global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict__ partial,
-                                                         float* __restrict__ out, int splits) {
+constexpr int kCombineThreads = 256;
+
+// Merge the split partials of one query head, one workgroup per head.  Bound by latency: a launch and
+// a round trip to memory per 64 splits, then a chain of dependent instructions.  So the splits are
+// shared out among D/4 threads each (4 adjacent channels a thread, 8 splits at a time at D = 128), whose
+// sums meet in shared memory, and lane i of every wavefront has maximum, sum and weight of split i,
+// which all channels share.  The order of the additions is fixed.  From the launch's first instruction
+// to its last 1.1 us for 32 splits; with a thread per channel that went through the splits one after
+// the other, an exponential each, 2.6, and 1.35 for 16 (4 heads of 471 splits of one long stream:
+// a step of 24.9 us instead of 44.8).
+template <int D>
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
+    const float* __restrict__ partial, float* __restrict__ out, int splits) {
   constexpr int ST = partial_stride(D);
-  const int head = blockIdx.x;
-  const int c = threadIdx.x;
-  const float* pr = partial + (size_t)head * splits * ST;
-  float m = kNegBig, l = 0.f, a = 0.f;
-  for (int s0 = 0; s0 < splits; s0 += BATCH) {
-    float ms[BATCH], ls[BATCH], as[BATCH];
+  constexpr int ROW = D / 4, GROUPS = kCombineThreads / ROW;  // splits at a time
+  typedef __attribute__((ext_vector_type(4), aligned(8))) float f32x4_row;
+  __shared__ float s_sum[GROUPS][D];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int group = tid / ROW, c = tid % ROW * 4;
+  const float* pr = partial + (size_t)blockIdx.x * splits * ST;
+  auto all_lanes = [](float x, auto op) {
+    x = op(x, dpp_f32<0x128>(x));  // row_ror:8, 4, 2, 1: over the 16 lanes of a row
+    x = op(x, dpp_f32<0x124>(x));
+    x = op(x, dpp_f32<0x122>(x));
+    x = op(x, dpp_f32<0x121>(x));
+    return across_k_groups(x, op);
+  };
+  float m = kNegBig, l = 0.f;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < splits; s0 += 64) {
+    const f32x2 ml = *(const f32x2*)(pr + min(s0 + lane, splits - 1) * ST);
+    f32x4 v[64 / GROUPS];
+    static_for<0, 64 / GROUPS>([&](auto j) {
+      v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (s0 + j * GROUPS < splits)
+        v[j] = *(const f32x4_row*)(pr + min(s0 + j * GROUPS + group, splits - 1) * ST + 2 + c);
+    });
+    const bool there = s0 + lane < splits;
+    const float m_new = fmaxf(
+        m, all_lanes(there ? ml.x : kNegBig, [](float x, float y) { return fmaxf(x, y); }));
+    const float r = __builtin_amdgcn_exp2f(m - m_new);
+    const float w = there ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
+    l = fmaf(l, r, all_lanes(w * ml.y, [](float x, float y) { return x + y; }));
+    a *= r;
+    m = m_new;
+    static_for<0, 64 / GROUPS>([&](auto j) {
+      if (s0 + j * GROUPS < splits) {
+        const float wj = __shfl(w, j * GROUPS + group);  // 0 past the last split
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const float* ps = pr + min(s0 + i, splits - 1) * ST;
-      ms[i] = ps[0], ls[i] = ps[1], as[i] = ps[2 + c];
-    }
-    float mb = m;
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) mb = fmaxf(mb, s0 + i < splits ? ms[i] : kNegBig);
-    const float r = __builtin_amdgcn_exp2f(m - mb);
-    l *= r, a *= r, m = mb;
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const float w = s0 + i < splits ? __builtin_amdgcn_exp2f(ms[i] - mb) : 0.f;
-      l = fmaf(w, ls[i], l);
-      a = fmaf(w, as[i], a);
-    }
+        for (int e = 0; e < 4; ++e) a[e] = fmaf(wj, v[j][e], a[e]);
+      }
+    });
   }
-  out[(size_t)head * D + c] = l > 0.f ? a / l : 0.f;
+  *(f32x4*)&s_sum[group][c] = a;
+  __syncthreads();
+  if (tid < D) {
+    float sum = 0.f;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) sum += s_sum[g][tid];
+    out[(size_t)blockIdx.x * D + tid] = l > 0.f ? sum / l : 0.f;
+  }
 }
 
 // Shape of the launch: wavefronts per workgroup, pairs of pages per wavefront, workgroups per
@@ -80,9 +108,26 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
 //   64: 18.7 / 19.0, 128: 32.3 / 28.1; 256 streams of 4 heads, 24 pages 9.8 / 11.5, 64: 21.8 / 20.6,
 //   128: 35.3 / 31.7; of 16 heads, 32 pages 12.2 / 12.8, 64: 20.3 / 18.4).
 //   Otherwise 8 wavefronts with a pair each, which beats 4 with a pair each also where that
-//   leaves CUs idle (8 streams of 90 pages: 13.5 / 14.7).
+//   leaves CUs idle (8 streams of 90 pages: 13.5 / 14.7), or with a page each.  A page is half the
+//   chain of dependent instructions of a pair and half the traffic through a CU, for twice as many
+//   partial results and selections: faster while every CU has at most one of these workgroups, or
+//   where some CUs would have two with pairs and still no more than two with single pages (those
+//   that select; the others come when there is room).  Step in us, pages / pairs:
+//     workgroups with pages, pairs                               D = 128          D = 64
+//     192, 112   16 streams of 90 of 1000 pages                12.6 / 13.6      10.9 / 11.4
+//     256, 128   32 streams of 64 of 500                       12.9 / 13.9
+//     128,  64   28 layers of 4 streams of 256 of 8192          466 / 486
+//     320, 160   20 streams of 128 of 2048                     17.2 / 16.7
+//     384, 192   32 streams of 90 of 1000                      15.8 / 15.4      13.2 / 13.1
+//     512, 256   64 streams of 64 of 500                       16.7 / 16.4
+//     390, 260   130 streams of 24 of 500                      18.3 / 20.2      13.9 / 14.9
+//     484, 264   44 streams of 88 of 1000                      17.6 / 18.9
+//     520, 280   40 streams of 90 of 751 and 7 of a tail       16.7 / 17.9      13.0 / 14.4
+//     516, 258   43 streams of 90 of 1000                      19.9 / 18.3
+//     533, 287   41 streams of 104 of 1000                     21.0 / 19.3      16.2 / 15.2
 struct AttnPlan {
-  int waves, pairs, splits;
+  int waves, nx, pairs, splits;  // nx: pages that a wavefront takes at a time
+  int slots() const { return waves * nx * pairs; }  // page slots per workgroup
 };
 
 // Few streams of 2049..8192 pages (a long context at batch 1) can select inside the attention
@@ -98,20 +143,49 @@ static bool long_select_shape(const stc_shape_t& s, int k_pages) {
 // each other, which is no slower than splits: 26.2 us for 30.2 at 64 pages).
 static int resident_streams(const stc_shape_t& s) { return s.D == 128 ? 256 : 512; }
 
+// K rows and value runs are read once per step.  What a launch cannot know is whether they still lie
+// in the last-level cache (256 MB): behind the other layers of a decoder they do not, where one
+// cache is stepped by itself they do.  us per step with ordinary / streaming loads of them:
+//   keys + bounds, MiB             out of the cache     in it
+//    8 + 15   40 streams of  751    18.5 / 18.5        14.8 / 15.0
+//   20 + 16  128 of  250            22.5 / 22.0        19.8 / 19.0
+//   16 + 32   32 of 2048            22.9 / 22.5        20.8 / 21.0
+//   38 + 31  160 of  400            30.8 / 30.2        25.9 / 26.8
+//   64 + 32  256 of  256            32.4 / 29.4        26.8 / 28.6
+//   32 + 64   64 of 2048            32.8 / 31.9        30.7 / 30.1
+//   75 + 47  320 of  300            44.4 / 42.7        37.2 / 39.8
+//   64 + 64  256 of  512            37.8 / 34.2        32.0 / 32.7
+// Below 80 MiB the two differ by 2 % out of the cache and by 4 % either way in it; above, streaming
+// loads gain 3 to 10 % out of the cache, for which a step of one cache by itself pays up to 7 %.
+// Pages that several query heads of a KV head select (kv_div > 1) count once: they come from the
+// caches after the first.
+static bool streaming_loads(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
+  const int NP = (s.N + kPage - 1) / kPage;
+  const long long streams = (long long)s.B * s.Hkv / kv_div;
+  const long long keys = streams * (k_pages + tail_pages) * kPage * s.D * 2;
+  const long long bounds = k_pages < NP ? streams * NP * s.D * 4 : 0;
+  return keys + bounds >= (80ll << 20);
+}
+
 // kv_div query heads per KV head with page lists of their own (each of them a stream here).
-static AttnPlan attention_plan(const stc_shape_t& s, int k_pages, int kv_div = 1) {
-  const int streams = s.B * s.Hkv;
-  AttnPlan p{k_pages <= 8 ? 4 : 8, 1, 0};
+static AttnPlan attention_plan(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div = 1) {
+  const int streams = s.B * s.Hkv, slots = k_pages + tail_pages;
+  AttnPlan p{slots <= 8 ? 4 : 8, 2, 1, 0};
   const int max_pairs = kv_div > 1 ? kMaxPairsShared : kMaxPairs;
-  if (k_pages > 16 && k_pages <= 16 * max_pairs && streams >= 192 &&
-      streams <= resident_streams(s))
-    p.pairs = (k_pages + 15) / 16;
-  p.splits = (k_pages + p.waves * 2 * p.pairs - 1) / (p.waves * 2 * p.pairs);
+  auto workgroups = [&](int pages, int each) { return (long long)streams * ((pages + each - 1) / each); };
+  if (slots > 16 && slots <= 16 * max_pairs && streams >= 192 && streams <= resident_streams(s))
+    p.pairs = (slots + 15) / 16;
+  else if (slots > 16 && !streaming_loads(s, k_pages, tail_pages, kv_div) &&
+           (workgroups(slots, 8) <= 256 ||
+            (workgroups(slots, 16) > 256 && workgroups(k_pages, 8) <= 512 &&
+             workgroups(slots, 8) <= 768)))
+    p.nx = 1;
+  p.splits = (slots + p.slots() - 1) / p.slots();
   return p;
 }
 
 int attention_splits(const stc_shape_t& s, int k_pages, int kv_div) {
-  return attention_plan(s, k_pages, kv_div).splits;
+  return attention_plan(s, k_pages, 0, kv_div).splits;
 }
 
 // The per-query-head form is the ordinary launch on a shape with one KV head per query head
@@ -140,27 +214,27 @@ struct AttnLaunch {
   hipStream_t st;
 };
 
-template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
+template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI, int NX>
 int attn_go(const AttnLaunch& a) {
   // workgroups of 8 wavefronts at D = 128 need more than the default 64 KiB of LDS
   constexpr int lds_bytes = WAVES * AttnCfg<D>::WAVE_LDS;
   static_assert(SELECT_IPT == 0 || lds_bytes >= (int)sizeof(TopkLds<SELECT_IPT, 64 * WAVES>),
                 "the selection uses the same memory");
   static std::atomic<uint64_t> allowed{0};
-  if (!allow_dynamic_lds((const void*)attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>,
+  if (!allow_dynamic_lds((const void*)attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI, NX>,
                          lds_bytes, allowed))
     return -1;
-  attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI>
+  attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI, NX>
       <<<a.grid, 64 * WAVES, lds_bytes, a.st>>>(
           SELECT_IPT > 0 ? (const void*)a.p.sel_score : (const void*)a.p.page_idx, a.p.q, a.p.K,
           a.p.mask, a.p.tok_off, a.p.NP, a.p.k_pages, a.p.Ncap, a.p.R | (int)a.p.by_xcd << 8, a.p);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int D, int WAVES, int SELECT_IPT, bool STREAM, bool MULTI = false>
+template <int D, int WAVES, int SELECT_IPT, bool STREAM, bool MULTI = false, int NX = 2>
 int attn_tail(const AttnLaunch& a, bool tail) {
-  return tail ? attn_go<D, WAVES, true, SELECT_IPT, STREAM, MULTI>(a)
-              : attn_go<D, WAVES, false, SELECT_IPT, STREAM, MULTI>(a);
+  return tail ? attn_go<D, WAVES, true, SELECT_IPT, STREAM, MULTI, NX>(a)
+              : attn_go<D, WAVES, false, SELECT_IPT, STREAM, MULTI, NX>(a);
 }
 
 template <int D>
@@ -168,6 +242,11 @@ int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, bool sel
                   bool stream_loads) {
   if (plan.waves != 8)  // few pages: nothing to keep out of the caches
     return select ? attn_tail<D, 4, 8, false>(a, tail) : attn_tail<D, 4, 0, false>(a, tail);
+  if (plan.nx == 1) {  // few workgroups, ordinary loads
+    if (select && a.p.NP > 2048) return attn_tail<D, 8, 16, false, false, 1>(a, tail);
+    return select ? attn_tail<D, 8, 4, false, false, 1>(a, tail)
+                  : attn_tail<D, 8, 0, false, false, 1>(a, tail);
+  }
   if (plan.pairs > 1) {
     if (select)
       return stream_loads ? attn_tail<D, 8, 4, true, true>(a, tail)
@@ -195,10 +274,9 @@ bool attention_can_select(const stc_shape_t& s, int k_pages, int tail_pages) {
   if (NP > 2048) return long_select_shape(s, k_pages + tail_pages);
   // the workgroups that select must all be resident at once; those that hold only pages of
   // the tail skip the selection and may come in a second round
-  const AttnPlan p = attention_plan(s, k_pages + tail_pages);
+  const AttnPlan p = attention_plan(s, k_pages, tail_pages);
   const long long streams = (long long)s.B * s.Hkv;
-  const int per_wg = p.waves * 2 * p.pairs;
-  return streams * ((k_pages + per_wg - 1) / per_wg) <= 512 && streams * p.splits <= 768;
+  return streams * ((k_pages + p.slots() - 1) / p.slots()) <= 512 && streams * p.splits <= 768;
 }
 
 // Parameters of an attention launch without a page list's consumers filled in.
@@ -217,30 +295,6 @@ static AttnParams attn_params(const stc_shape_t& s, const stc_shape_t& s0, const
                     s.Hkv / s0.Hkv, page_heads, token_cap(s), sel_score, sel_list, plan.pairs, false};
 }
 
-// K rows and value runs are read once per step.  What a launch cannot know is whether they still lie
-// in the last-level cache (256 MB): behind the other layers of a decoder they do not, where one
-// cache is stepped by itself they do.  us per step with ordinary / streaming loads of them:
-//   keys + bounds, MiB             out of the cache     in it
-//    8 + 15   40 streams of  751    18.5 / 18.5        14.8 / 15.0
-//   20 + 16  128 of  250            22.5 / 22.0        19.8 / 19.0
-//   16 + 32   32 of 2048            22.9 / 22.5        20.8 / 21.0
-//   38 + 31  160 of  400            30.8 / 30.2        25.9 / 26.8
-//   64 + 32  256 of  256            32.4 / 29.4        26.8 / 28.6
-//   32 + 64   64 of 2048            32.8 / 31.9        30.7 / 30.1
-//   75 + 47  320 of  300            44.4 / 42.7        37.2 / 39.8
-//   64 + 64  256 of  512            37.8 / 34.2        32.0 / 32.7
-// Below 80 MiB the two differ by 2 % out of the cache and by 4 % either way in it; above, streaming
-// loads gain 3 to 10 % out of the cache, for which a step of one cache by itself pays up to 7 %.
-// Pages that several query heads of a KV head select (kv_div > 1) count once: they come from the
-// caches after the first.
-static bool streaming_loads(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
-  const int NP = (s.N + kPage - 1) / kPage;
-  const long long streams = (long long)s.B * s.Hkv / kv_div;
-  const long long keys = streams * (k_pages + tail_pages) * kPage * s.D * 2;
-  const long long bounds = k_pages < NP ? streams * NP * s.D * 4 : 0;
-  return keys + bounds >= (80ll << 20);
-}
-
 int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const void* vpacked,
                      const uint16_t* mask, const uint32_t* tok_off, const int32_t* page_idx,
                      int k_pages, const void* K_tail, const void* V_tail, int n_tail, int tail_cap,
@@ -251,7 +305,7 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
   const int streams = s.B * s.Hkv;
   const int tail_pages = (n_tail + kPage - 1) / kPage;
   const int kv_div = s.Hkv / s0.Hkv;
-  const AttnPlan plan = attention_plan(s, k_pages + tail_pages, kv_div);
+  const AttnPlan plan = attention_plan(s, k_pages, tail_pages, kv_div);
   AttnLaunch a{attn_params(s, s0, plan, q, K, vpacked, mask, tok_off, page_idx, k_pages, K_tail,
                            V_tail, n_tail, tail_cap, page_heads, sel_score, sel_list, out, ws),
                dim3(plan.splits, streams), st};
@@ -268,16 +322,10 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
                             : attn_dispatch<64>(a, plan, tail, select, stream_loads);
   if (rc) return -1;
   if (plan.splits > 1) {
-#define STC_COMBINE(DD, BATCH) \
-  attn_combine_kernel<DD, BATCH><<<s.B * s.Hq, DD, 0, st>>>(a.p.partial, out, plan.splits)
-    if (s.D == 128) {
-      if (plan.splits <= 8) STC_COMBINE(128, 8);
-      else STC_COMBINE(128, 16);
-    } else {
-      if (plan.splits <= 8) STC_COMBINE(64, 8);
-      else STC_COMBINE(64, 16);
-    }
-#undef STC_COMBINE
+    if (s.D == 128)
+      attn_combine_kernel<128><<<s.B * s.Hq, kCombineThreads, 0, st>>>(a.p.partial, out, plan.splits);
+    else
+      attn_combine_kernel<64><<<s.B * s.Hq, kCombineThreads, 0, st>>>(a.p.partial, out, plan.splits);
     if (hipGetLastError() != hipSuccess) return -1;
   }
   return 0;
@@ -295,7 +343,7 @@ bool step_is_one_kernel(const stc_shape_t& s, int k_pages, int tail_pages) {
   const int NP = (s.N + kPage - 1) / kPage, streams = s.B * s.Hkv, R = s.Hq / s.Hkv;
   if (k_pages >= NP || R > 8 || streams > resident_streams(s)) return false;
   if (!(NP <= (R <= 4 ? 256 : 192) || (streams >= 192 && NP <= kStepKeys))) return false;
-  return attention_plan(s, k_pages + tail_pages).splits == 1;
+  return attention_plan(s, k_pages, tail_pages).splits == 1;
 }
 
 int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const void* K,
@@ -303,7 +351,7 @@ int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const v
                 const void* K_tail, const void* V_tail, int n_tail, int tail_cap, float* score,
                 int32_t* list, float* out, hipStream_t st) {
   const int tail_pages = (n_tail + kPage - 1) / kPage;
-  const AttnPlan plan = attention_plan(s, k_pages + tail_pages);
+  const AttnPlan plan = attention_plan(s, k_pages, tail_pages);
   const AttnParams p =
       attn_params(s, s, plan, q, K, vpacked, mask, tok_off, nullptr, k_pages, K_tail, V_tail, n_tail,
                   tail_cap, nullptr, nullptr, list, out, nullptr);

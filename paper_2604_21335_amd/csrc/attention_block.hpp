@@ -79,9 +79,9 @@ __device__ __forceinline__ float across_k_groups(float x, Op op) {
   return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
 }
 
-// One wavefront takes one pair of page slots of one stream, or, with MULTI, P.pairs adjacent pairs
-// one after the other (up to kMaxPairs), each a partial result of its own; the WAVES wavefronts of
-// a workgroup then merge their partial results in LDS.
+// One wavefront takes one pair of page slots of one stream (NX = 2), one page slot (NX = 1), or, with
+// MULTI, P.pairs adjacent pairs one after the other (up to kMaxPairs), each a partial result of its
+// own; the WAVES wavefronts of a workgroup then merge their partial results in LDS.
 // Page slots are the selected pages of the compressed cache followed, with TAIL, by the pages
 // of the uncompressed tail; kv_div query-head streams may share one KV head's cache.
 //
@@ -154,12 +154,13 @@ int launch_step_kernel(const AttnParams& p, int D, int streams, const void* boun
 // The work of one workgroup: split `split` of stream `stream`.  `lds` = WAVES * WAVE_LDS bytes
 // of shared memory.  sel_score (SELECT_IPT > 0) = the stream's page scores; they and the memory
 // of the selection, sel_lds, may lie in `lds`, which is written only after the selection.
-template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI>
+template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI, int NX>
 __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream, const int split,
                                            unsigned char* lds, const float* sel_score,
                                            TopkLds<SELECT_IPT, 64 * WAVES>* sel_lds) {
   using C = AttnCfg<D>;
-  const int ppw = MULTI ? 2 * P.pairs : 2;  // pages per wavefront
+  static_assert(NX == 2 || !MULTI, "several pairs, or one page, per wavefront");
+  const int ppw = MULTI ? 2 * P.pairs : NX;  // pages per wavefront
   const uint16_t* __restrict__ q = P.q;
   const uint16_t* __restrict__ K = P.K;
   const unsigned char* __restrict__ vpacked = P.vpacked;
@@ -236,7 +237,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     if (lane < npages && pi0 + lane < k_pages) my_pg = s_pages[wave * ppw + lane];
   }
   if (lane < 4) *(uint32_t*)(wl + C::ZERO + lane * 4) = 0;
-  const int npairs = (npages + 1) / 2;
+  const int npairs = (npages + NX - 1) / NX;
 
   // PV role: the value unit this lane reads for each of its tokens
   const uint32_t unit = (D == 128) ? r16 : (r16 >> 1);
@@ -247,13 +248,13 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   // Masks and offsets of a pair: lanes 0..15 carry the tokens of its first page, 16..31 of its
   // second page.
   struct PairMeta {
-    uint32_t mk, off, run0[2], run1[2];
+    uint32_t mk, off, run0[NX], run1[NX];
     uint32_t moi;  // token index behind off (tail pages derive their offsets from it)
     bool mvalid;
     bool mtail;    // this lane's meta words belong to a tail page
-    int pgs[2];
+    int pgs[NX];
   };
-  u32x4 kreg[2][C::NLD];
+  u32x4 kreg[NX][C::NLD];
 
   // Lanes 0..15 fetch mask and offset of the tokens of the pair's first page, lanes
   // 16..31 of its second page; lanes 32 and 33 fetch the offset just past each page
@@ -265,11 +266,11 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   auto tok_lim = [&](int pg) { return (uint32_t)(is_tail(pg) ? n_tail : N); };
   auto issue_meta = [&](PairMeta& M, int pair) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x) M.pgs[x] = __builtin_amdgcn_readlane(my_pg, 2 * pair + x);
-    const int pg = (lane & 1) ? M.pgs[1] : M.pgs[0];          // lanes 32, 33
-    const int pgt = (lane & 16) ? M.pgs[1] : M.pgs[0];        // token lanes
+    for (int x = 0; x < NX; ++x) M.pgs[x] = __builtin_amdgcn_readlane(my_pg, NX * pair + x);
+    const int pg = (lane & 1) ? M.pgs[NX - 1] : M.pgs[0];     // lanes 32, 33
+    const int pgt = (lane & 16) ? M.pgs[NX - 1] : M.pgs[0];   // token lanes
     const uint32_t t = (pgt < 0 ? 0 : page_no(pgt) * kPage) + r16;
-    const bool tv = lane < 32 && pgt >= 0 && t < tok_lim(pgt);
+    const bool tv = lane < 16 * NX && pgt >= 0 && t < tok_lim(pgt);
     const uint32_t tend =
         pg < 0 ? 0u : min((uint32_t)page_no(pg) * kPage + kPage, tok_lim(pg));
     const uint32_t oi = tv ? t : ((lane == 32 || lane == 33) ? tend : 0u);
@@ -289,14 +290,14 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
       M.off = M.moi * G;
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       M.run0[x] = __builtin_amdgcn_readlane(M.off, 16 * x);  // token 0 of a page is valid
       M.run1[x] = __builtin_amdgcn_readlane(M.off, 32 + x);
     }
   };
   auto issue_k = [&](const PairMeta& M) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       const int pg = M.pgs[x];
       const uint32_t t0 = pg < 0 ? 0 : page_no(pg) * kPage;
       const uint32_t lim = tok_lim(pg);
@@ -321,7 +322,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   // Packed V runs of a pair, flat; lanes past the end of a run read its last unit (of an empty run
   // the store's first), which no token refers to.
 #define STC_ISSUE_V(vreg, M)                                                                   \
-  static_for<0, 2>([&](auto x) {                                                               \
+  static_for<0, NX>([&](auto x) {                                                               \
     const uint32_t rbytes = run_groups(M, x) * gbytes;                                         \
     const unsigned char* vrun = ((M.pgs[x] >= 0 && is_tail(M.pgs[x])) ? vts : vs) +            \
                                 (rbytes ? (size_t)M.run0[x] * gbytes : (size_t)0);             \
@@ -369,16 +370,16 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
   auto qk_softmax = [&](const PairMeta& M, int pair) {
     // K rows of the pair -> LDS tiles (row stride ROW), then back in MFMA operand layout
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
       for (int j = 0; j < C::NLD; ++j)
         *(u32x4*)(wl + (x * C::TILE + ((j * 64 + lane) / C::LPR) * C::ROW +
                         (lane % C::LPR) * 16)) = kreg[x][j];
     wave_lds_sync();
-    float s[2][4];
+    float s[NX][4];
     float mx = kNegBig;
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       f32x4 sv = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < C::KC; ++j) {
@@ -391,7 +392,7 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
       const uint32_t t0 = pg < 0 ? 0 : page_no(pg) * kPage;
       const uint32_t lim = tok_lim(pg);
       // a head that did not select this page gives its tokens no weight
-      const bool mine = (__builtin_amdgcn_readlane(my_heads, 2 * pair + x) >> r16) & 1;
+      const bool mine = (__builtin_amdgcn_readlane(my_heads, NX * pair + x) >> r16) & 1;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool tv = pg >= 0 && mine && (t0 + 4 * kg + i < lim);
@@ -401,10 +402,10 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     }
     mx = across_k_groups(mx, [](float a, float b) { return fmaxf(a, b); });
     const float m_pair = fmaxf(kNegBig, mx);
-    float p[8];
+    float p[4 * NX];
     float psum = 0.f;
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         p[x * 4 + i] = __builtin_amdgcn_exp2f(s[x][i] - m_pair);  // m_pair is finite
@@ -421,9 +422,9 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
       l_part = psum;
     }
     // weights as two bf16 parts; contraction index: (kg, e) e<4 page 0, e>=4 page 1
-    uint32_t h[4], l[4];
+    uint32_t h[4] = {0u, 0u, 0u, 0u}, l[4] = {0u, 0u, 0u, 0u};  // one page: no weight for another
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < 2 * NX; ++r) {
       h[r] = pack_bf16(p[2 * r], p[2 * r + 1]);
       l[r] = pack_bf16(p[2 * r] - bf16_lo(h[r]), p[2 * r + 1] - bf16_hi(h[r]));
     }
@@ -435,20 +436,20 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
 #define STC_PV(vreg, M)                                                                        \
   {                                                                                            \
     wave_lds_sync(); /* the K tiles have been read */                                          \
-    static_for<0, 2>([&](auto x) {                                                             \
+    static_for<0, NX>([&](auto x) {                                                             \
       static_for<0, C::NLD>([&](auto j) {                                                      \
         *(u32x4*)(wl + (x * C::TILE + (j * 64 + lane) * 16)) = vreg[x][j];                     \
       });                                                                                      \
     });                                                                                        \
     if (lane < 32) { /* token lane: kept-group mask and offset relative to the run */         \
-      const uint32_t r0 = (lane & 16) ? M.run0[1] : M.run0[0];                                 \
+      const uint32_t r0 = (lane & 16) ? M.run0[NX - 1] : M.run0[0];                            \
       const uint32_t rel = min(M.off - r0, 0xffffu);                                           \
       *(uint32_t*)(wl + C::META + lane * 4) = (M.mvalid ? M.mk : 0u) | (rel << 16);            \
     }                                                                                          \
     wave_lds_sync();                                                                           \
     /* t[e]: channels r16*CB .. +CB of token e of this lane's k-group (e < 4: page 0) */       \
-    uint32_t t[8][C::CB / 2];                                                                  \
-    _Pragma("unroll") for (int x = 0; x < 2; ++x) {                                            \
+    uint32_t t[4 * NX][C::CB / 2];                                                             \
+    _Pragma("unroll") for (int x = 0; x < NX; ++x) {                                            \
       const uint32_t rg = run_groups(M, x);                                                    \
       const u32x4 mt = *(const u32x4*)(wl + C::META + x * 64 + kg * 16);                       \
       _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                          \
@@ -468,8 +469,8 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     }                                                                                          \
     _Pragma("unroll") for (int cb = 0; cb < C::CB; ++cb) {                                     \
       const uint32_t sel = (cb & 1) ? 0x07060302u : 0x05040100u;                               \
-      uint32_t a[4];                                                                           \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) a[r] =                                     \
+      uint32_t a[4] = {0u, 0u, 0u, 0u};                                                        \
+      _Pragma("unroll") for (int r = 0; r < 2 * NX; ++r) a[r] =                                \
           __builtin_amdgcn_perm(t[2 * r + 1][cb >> 1], t[2 * r][cb >> 1], sel);                \
       const bf16x8 av = as_bf16x8(u32x4{a[0], a[1], a[2], a[3]});                              \
       acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(phi), acc[cb], 0, 0, 0); \

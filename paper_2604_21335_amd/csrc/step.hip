@@ -46,7 +46,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(
       heads);
   __syncthreads();
   for (int i = threadIdx.x; i < P.NP; i += 64 * WAVES) score[(size_t)stream * P.NP + i] = s_score[i];
-  attn_block<D, WAVES, TAIL, kStepKeys / (64 * WAVES), STREAM, true>(
+  attn_block<D, WAVES, TAIL, kStepKeys / (64 * WAVES), STREAM, true, 2>(
       P, stream, 0, lds, s_score, (TopkLds<kStepKeys / 512, 512>*)(lds + step_score_lds<D, RM>()));
 }
 
