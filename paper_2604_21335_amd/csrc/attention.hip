@@ -130,12 +130,14 @@ struct AttnPlan {
   int slots() const { return waves * nx * pairs; }  // page slots per workgroup
 };
 
-// Few streams of 2049..8192 pages (a long context at batch 1) can select inside the attention
-// kernel, 16 keys per thread.
+// Streams of 2049..8192 pages can select inside the attention kernel, 16 keys per thread, while all
+// workgroups are resident at once (two per compute unit).  Step in us, inside / as a launch of its own:
+// 12 streams of 256 of 8192 pages 22.4 / 23.4, 32 of them 41.5 / 44.0; 16 of 300 of 4096 22.1 / 22.6, 32
+// of 128 of 4096 25.4 / 27.4; 64 of 60 of 2100 26.9 / 28.3.
 static bool long_select_shape(const stc_shape_t& s, int k_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
   return NP > 2048 && NP <= 8192 && k_pages > 8 &&
-         (long long)s.B * s.Hkv * ((k_pages + 15) / 16) <= 128;
+         (long long)s.B * s.Hkv * ((k_pages + 15) / 16) <= 512;
 }
 
 // Workgroups that take a whole stream each and are resident at once (the registers of a CU hold
@@ -186,6 +188,10 @@ static AttnPlan attention_plan(const stc_shape_t& s, int k_pages, int tail_pages
 
 int attention_splits(const stc_shape_t& s, int k_pages, int kv_div) {
   return attention_plan(s, k_pages, 0, kv_div).splits;
+}
+int attention_wave_pages(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
+  const AttnPlan p = attention_plan(s, k_pages, tail_pages, kv_div);
+  return p.nx * p.pairs;
 }
 
 // The per-query-head form is the ordinary launch on a shape with one KV head per query head
@@ -255,7 +261,8 @@ int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, bool sel
                         : attn_tail<D, 8, 0, false, true>(a, tail);
   }
   if (select) {  // selection inside the kernel: 2048 (8192) keys over the workgroup's threads
-    if (a.p.NP > 2048) return attn_tail<D, 8, 16, false>(a, tail);  // (at most 128 workgroups)
+    // (streaming loads lose here: 24 streams of 256 of 8192 pages 36.6 us per step, 34.9)
+    if (a.p.NP > 2048) return attn_tail<D, 8, 16, false>(a, tail);
     return stream_loads ? attn_tail<D, 8, 4, true>(a, tail) : attn_tail<D, 8, 4, false>(a, tail);
   }
   return stream_loads ? attn_tail<D, 8, 0, true>(a, tail) : attn_tail<D, 8, 0, false>(a, tail);
@@ -270,7 +277,6 @@ int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, bool sel
 bool attention_can_select(const stc_shape_t& s, int k_pages, int tail_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
   if (k_pages >= NP) return false;
-  // long streams: only where the launch is latency-bound anyway (few workgroups)
   if (NP > 2048) return long_select_shape(s, k_pages + tail_pages);
   // the workgroups that select must all be resident at once; those that hold only pages of
   // the tail skip the selection and may come in a second round

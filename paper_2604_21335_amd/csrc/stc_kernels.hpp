@@ -54,6 +54,8 @@ int launch_select(const stc_shape_t& s, const void* q, const void* bounds, int k
 
 // Workgroups per stream; kv_div > 1: `s` has a KV head per query head, kv_div of which share a cache.
 int attention_splits(const stc_shape_t& s, int k_pages, int kv_div);
+// Pages that a wavefront of that launch takes.
+int attention_wave_pages(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div);
 size_t attention_ws_bytes(const stc_shape_t& s, int k_pages, bool per_head = false);
 int launch_attention(const stc_shape_t& s, const void* q, const void* K, const void* vpacked,
                      const uint16_t* mask, const uint32_t* tok_off, const int32_t* page_idx,
