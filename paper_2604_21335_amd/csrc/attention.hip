@@ -130,14 +130,14 @@ struct AttnPlan {
   int slots() const { return waves * nx * pairs; }  // page slots per workgroup
 };
 
-// Streams of 2049..8192 pages can select inside the attention kernel, 16 keys per thread, while all
-// workgroups are resident at once (two per compute unit).  Step in us, inside / as a launch of its own:
-// 12 streams of 256 of 8192 pages 22.4 / 23.4, 32 of them 41.5 / 44.0; 16 of 300 of 4096 22.1 / 22.6, 32
-// of 128 of 4096 25.4 / 27.4; 64 of 60 of 2100 26.9 / 28.3.
+// Streams of 2049..8192 pages can select inside the attention kernel, 16 keys per thread, while its
+// workgroups are fewer than two per compute unit.  Step in us, inside / as a launch of its own: 12
+// streams of 256 of 8192 pages 22.4 / 23.4, 24 of them 34.9 / 37.9; 16 of 300 of 4096 22.1 / 22.6; 48 of
+// 100 of 3000 28.6 / 29.9.
 static bool long_select_shape(const stc_shape_t& s, int k_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
   return NP > 2048 && NP <= 8192 && k_pages > 8 &&
-         (long long)s.B * s.Hkv * ((k_pages + 15) / 16) <= 512;
+         (long long)s.B * s.Hkv * ((k_pages + 15) / 16) < 512;
 }
 
 // Workgroups that take a whole stream each and are resident at once (the registers of a CU hold
