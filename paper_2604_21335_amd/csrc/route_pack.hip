@@ -14,7 +14,7 @@ constexpr int kChunk = 256;  // tokens per workgroup in the route / pack kernels
 
 __device__ __forceinline__ int block_sum_256(int v, int* lds4) {
   // sum over a 256-thread block; every thread gets the total
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+  v = (int)wave_reduce((uint32_t)v, OpAdd{}, 0u);
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) lds4[wave] = v;
   __syncthreads();
@@ -26,16 +26,12 @@ __device__ __forceinline__ int block_sum_256(int v, int* lds4) {
 // Exclusive prefix sum over a 256-thread block (in thread order).
 __device__ __forceinline__ int block_exscan_256(int v, int* lds4, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const int inc = (int)wave_scan((uint32_t)v, OpAdd{}, 0u);
   if (lane == 63) lds4[wave] = inc;
   __syncthreads();
-  int base = 0;
-  for (int w = 0; w < wave; ++w) base += lds4[w];
-  if (total) *total = lds4[0] + lds4[1] + lds4[2] + lds4[3];
+  const int a = lds4[0], b = lds4[1], c = lds4[2];
+  const int base = (wave > 0 ? a : 0) + (wave > 1 ? b : 0) + (wave > 2 ? c : 0);
+  if (total) *total = a + b + c + lds4[3];
   __syncthreads();
   return base + inc - v;
 }
@@ -64,9 +60,11 @@ __device__ __forceinline__ uint32_t route_token(const RouteInputs& in, int strea
 // that are read once and do not fit the caches go past them (64 streams of 32768 tokens, 67 MB of
 // logits: 9 us less, this launch and the packed copy behind it together).
 template <bool STREAM>
-__global__ __launch_bounds__(kChunk) void route_mask_kernel(const RouteInputs in, uint16_t* mask,
-                                                            uint32_t* __restrict__ chunk_sum,
-                                                            int N, int G, int nchunks, int Ncap) {
+__global__ __launch_bounds__(kChunk) void route_mask_kernel(
+    const float* logits, const uint8_t* kcount, uint16_t* mask, uint32_t* __restrict__ chunk_sum,
+    int N, int G, int nchunks, int Ncap, int share, int mode, int fixed_k,
+    const uint16_t* mask_in) {
+  const RouteInputs in{mode, logits, kcount, fixed_k, mask_in, share};
   __shared__ int red[4];
   const int stream = blockIdx.y;
   const int t = blockIdx.x * kChunk + threadIdx.x;
@@ -629,10 +627,11 @@ __global__ __launch_bounds__(256) void scan_chunks_kernel(uint32_t* chunk_sum, u
 // (streaming stores: nothing here is read again, and lines written completely need no
 // merging in the caches).
 // Bound by memory.  Measured on 64 streams of 32768 tokens, 8 groups, half of them kept
-// (805 MB): 122 us (6.6 TB/s); 158 for the form before, in which every lane stored its piece
-// where it belongs, 256 tokens per workgroup, through the caches.  128 tokens per workgroup
-// 128 us, 32: 132, with the values requested before the masks are known 129, with streaming
-// loads or streaming stores alone 143 and 141.
+// (805 MB): 116 us (6.9 TB/s); 122 while the scan of a workgroup's counts went through shuffles and
+// its arguments were loaded when it started, 158 for the form before that, in which every lane
+// stored its piece where it belongs, 256 tokens per workgroup, through the caches.  (Against 122:
+// 128 tokens per workgroup 128 us, 32: 132, with the values requested before the masks are known
+// 129, with streaming loads or streaming stores alone 143 and 141.)
 // What is in front of a workgroup's tokens, by FORM:
 //   kPackSums     chunk_sum holds the chunks' own sums, and every workgroup adds up those in front
 //                 of its chunk itself
@@ -644,13 +643,13 @@ enum { kPackSums, kPackScanned, kPackRoute };
 constexpr int kPackTokens = 64;
 
 template <int D, int FORM>
-__global__ __launch_bounds__(kChunk) void pack_kernel(const pack_u32x4* __restrict__ V,
-                                                      const RouteInputs in, uint16_t* mask,
-                                                      const uint32_t* __restrict__ chunk_sum,
-                                                      uint32_t* __restrict__ tok_off,
-                                                      pack_u32x4* __restrict__ vpacked,
-                                                      int32_t* dev_status, int N, int G,
-                                                      int nchunks, long long cap, int Ncap) {
+__global__ __launch_bounds__(kChunk) void pack_kernel(
+    const float* logits, const uint8_t* kcount, uint16_t* mask,
+    const pack_u32x4* __restrict__ V, const uint32_t* __restrict__ chunk_sum, int N, int G,
+    int nchunks, int Ncap, int share, int mode, int fixed_k, const uint16_t* mask_in,
+    uint32_t* __restrict__ tok_off, pack_u32x4* __restrict__ vpacked, int32_t* dev_status,
+    long long cap) {
+  const RouteInputs in{mode, logits, kcount, fixed_k, mask_in, share};
   constexpr int PPT = D / 8;                         // 16-byte pieces per token row
   constexpr int PER = kPackTokens * PPT / kChunk;    // pieces per thread
   __shared__ int red[4], red2[4];
@@ -785,7 +784,6 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
   const RouteWs lay = route_ws_layout(s);
   uint32_t* chunk = (uint32_t*)((char*)ws + lay.chunk_sum);
   dim3 grid(nchunks, streams);
-  const RouteInputs in{mode, logits, kcount, fixed_k, mask_in, share};
   bool in_pack = false;  // the packed copy routes the tokens itself
   if (mode == STC_ROUTE_GLOBAL) {
     uint32_t* chunk_eq = (uint32_t*)((char*)ws + lay.chunk_eq);
@@ -857,9 +855,11 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
       const bool stream_loads = mode == STC_ROUTE_TOPK && share == 1 &&
                                 (long long)streams * s.N * s.G * 4 >= (32ll << 20);
       if (stream_loads)
-        route_mask_kernel<true><<<grid, kChunk, 0, st>>>(in, mask, chunk, s.N, s.G, nchunks, Ncap);
+        route_mask_kernel<true><<<grid, kChunk, 0, st>>>(logits, kcount, mask, chunk, s.N, s.G, nchunks,
+                                                    Ncap, share, mode, fixed_k, mask_in);
       else
-        route_mask_kernel<false><<<grid, kChunk, 0, st>>>(in, mask, chunk, s.N, s.G, nchunks, Ncap);
+        route_mask_kernel<false><<<grid, kChunk, 0, st>>>(logits, kcount, mask, chunk, s.N, s.G, nchunks,
+                                                      Ncap, share, mode, fixed_k, mask_in);
     }
   }
   if (hipGetLastError() != hipSuccess) return -1;
@@ -877,10 +877,9 @@ int launch_route_pack(const stc_shape_t& s, int mode, const void* V, const float
   }
   dim3 pgrid((s.N + kPackTokens - 1) / kPackTokens, streams);
 #define STC_PACK(DD, FORM)                                                                    \
-  pack_kernel<DD, FORM><<<pgrid, kChunk, 0, st>>>((const pack_u32x4*)V, in, mask, chunk,      \
-                                                  tok_off, (pack_u32x4*)vpacked, dev_status,  \
-                                                  s.N, s.G, nchunks,                          \
-                                                  (long long)s.v_cap_groups, Ncap)
+  pack_kernel<DD, FORM><<<pgrid, kChunk, 0, st>>>(                                            \
+      logits, kcount, mask, (const pack_u32x4*)V, chunk, s.N, s.G, nchunks, Ncap, share, mode, \
+      fixed_k, mask_in, tok_off, (pack_u32x4*)vpacked, dev_status, (long long)s.v_cap_groups)
 #define STC_PACK_FORMS(DD)                                                                    \
   if (in_pack) STC_PACK(DD, kPackRoute);                                                      \
   else if (fold) STC_PACK(DD, kPackSums);                                                     \
