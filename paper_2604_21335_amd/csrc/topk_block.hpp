@@ -477,12 +477,55 @@ __device__ __forceinline__ void topk_any(const float* __restrict__ sc, int NP, i
   }
 }
 
+// The same for any scores of at most 128 pages (64 with fewer than 8 wavefronts): a page's place is the
+// number of pages in front of it, which every wavefront counts over its share of the pages.  One
+// barrier, where the forms above cross four: 8 streams of 64 pages, 16 kept, 5.9 us per step for 6.3.
+template <int IPT, int THREADS, class Emit>
+__device__ __forceinline__ void topk_few(const float* __restrict__ sc, int NP, int k,
+                                         TopkLds<IPT, THREADS>& S, Emit emit) {
+  constexpr int NW = THREADS / 64, E = NW < 8 ? 1 : 2;  // pages per lane
+  static_assert(NW * E * 64 <= kTopkBins, "counts of all wavefronts");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t key[E];
+  int ahead[E];
+  static_for<0, E>([&](auto e) {
+    key[e] = float_key(sc[min(e * 64 + lane, NP - 1)]);
+    ahead[e] = 0;
+  });
+  const int share = (NP + NW - 1) / NW, j1 = min((wave + 1) * share, NP);
+  for (int j = wave * share; j < j1; ++j) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)(j < 64 ? key[0] : key[E - 1]), j & 63);
+    static_for<0, E>([&](auto e) {
+      ahead[e] += (o > key[e]) | ((o == key[e]) & (j < e * 64 + lane));
+    });
+  }
+  static_for<0, E>([&](auto e) { S.hist[(wave * E + e) * 64 + lane] = ahead[e]; });
+  __syncthreads();
+  int pos = 0;
+  static_for<0, E>([&](auto e) {
+    int place = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) place += S.hist[(w * E + e) * 64 + lane];
+    const bool t = e * 64 + lane < NP && place < k;
+    const uint64_t m = __ballot(t);
+    if (wave == e && t) emit(pos + lanes_below(m), e * 64 + lane);
+    pos += __popcll(m);
+  });
+}
+
 // Top-k pages of a stream by one workgroup of THREADS threads, NP <= THREADS * IPT <= 65535: ties to
 // the lowest page, emit(position in the ascending list, page) for every selected one.  `sc` must not
 // lie in `S`.
 template <int IPT, int THREADS, class Emit>
 __device__ __forceinline__ void topk_block(const float* __restrict__ sc, int NP, int k,
                                            TopkLds<IPT, THREADS>& S, Emit emit) {
+  if constexpr (IPT <= 2) {
+    if (NP <= (THREADS < 512 ? 64 : 128)) {
+      topk_few<IPT, THREADS>(sc, NP, k, S, emit);
+      return;
+    }
+  }
   if (topk_positive<IPT, THREADS>(sc, NP, k, S, emit)) return;
   __syncthreads();
   topk_any<IPT, THREADS>(sc, NP, k, S, emit);

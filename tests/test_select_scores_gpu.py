@@ -42,14 +42,15 @@ def expected(score, k):
 
 @pytest.mark.parametrize("B,Hkv,R,NP,ks", [
     # query heads per KV head, pages: the selecting kernel
-    (1, 2, 9, 3, (1, 2)), (1, 2, 9, 31, (1, 30)), (2, 2, 9, 256, (1, 17, 255)),      # 256 threads: 1 key each
+    (1, 2, 9, 3, (1, 2)), (1, 2, 9, 31, (1, 30)), (2, 2, 9, 64, (1, 17, 63)), (2, 2, 9, 65, (16, 64)), (2, 2, 9, 256, (1, 17, 255)),      # 256 threads: 1 key each
     (2, 2, 9, 257, (9, 100)), (1, 2, 9, 511, (64, 510)),                             # 2 keys
     (2, 1, 9, 513, (1, 40, 112, 113)), (1, 2, 9, 1023, (20, 200, 223, 224, 1000)),   # 4 keys
     (2, 1, 9, 1025, (8, 60, 223, 224)), (2, 2, 9, 2048, (7, 128, 447, 448, 2047)),   # 512 threads: 4 keys
     (1, 2, 9, 2049, (128, 300)), (1, 2, 9, 4096, (200, 511, 600, 896, 897)),         # 8 keys
     (1, 3, 2, 4097, (9, 100, 500)), (1, 2, 7, 8191, (16, 256, 512, 1000)), (1, 2, 1, 8192, (255, 700, 1792, 1793)),
     (1, 2, 2, 8193, (100,)),                                                         # the loop over all keys
-    (3, 2, 1, 2, (1,)), (3, 2, 2, 64, (1, 16, 63)), (2, 2, 1, 255, (16, 17, 254)),   # a whole step, scoring and selection
+    (3, 2, 1, 2, (1,)), (3, 2, 2, 64, (1, 16, 63)), (2, 2, 4, 65, (8, 16)), (2, 2, 1, 127, (16, 40, 126)), (2, 2, 2, 128, (1, 16, 127)),
+    (2, 2, 1, 129, (16, 128)), (2, 2, 1, 255, (16, 17, 254)),   # a whole step, scoring and selection
     (50, 4, 1, 1001, (12, 128)), (50, 4, 4, 700, (100,)), (35, 4, 3, 640, (90, 639)),
 ])
 def test_select_scores(B, Hkv, R, NP, ks):
