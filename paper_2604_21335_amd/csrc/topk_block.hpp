@@ -60,7 +60,7 @@ struct TopkLds {
   alignas(16) int fine[kTopkFine];
   alignas(16) uint32_t wmin[8], wmax[8];
   int tot[8];
-  int cand[64], cand_page[64];
+  int cand[64];
   int gt[64], ge[64];
   int ncand, full;
   int key[THREADS / 64][OWN];
@@ -114,8 +114,9 @@ __device__ __forceinline__ int rank_bin(int4 h4, int rank, int& above, int& cnt)
 //    those that are left of its own, few more than k in all, and only these are counted in finer
 //    bins between that edge and the maximum.
 //  - The keys of the wanted bin are ranked one by one, and positions come from ballots.
-// Made for streams whose k-th largest score is positive and within 8 octaves of the maximum; NaN and
-// infinities are outside.
+// Many keys in the wanted bin get further bins between the smallest and the largest of them, equal ones
+// are taken in page order.  Made for streams whose k-th largest score is positive and within 8
+// octaves of the maximum; NaN and infinities are outside.
 // Time from the scores' arrival to the list, inside the attention launch, against topk_any: 8192 keys of
 // which 256 are kept 5.3 -> 3.6 us, 2048 of which 128 are kept 3.0 -> 2.4 (a step over 28 caches of
 // 131072 tokens 604 -> 543 us, over 64 streams of 2048 pages 30.4 -> 30.0, over 8 streams of 64
@@ -254,15 +255,42 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
 
   // The least key that is taken: the edge, or a key of the wanted bin.
   int least = edge;
-  const int rank = k - above;  // in the wanted bin
-  if (rank < cnt) {
-    if (cnt > 64) return false;
+  int rank = k - above;  // in the wanted bin
+  int equal = 0;         // > 0: that many keys are the least one, and not all of them are taken
+  // Too many to rank one by one: bins between the smallest and the largest of them, unless all are equal.
+  while (rank < cnt && cnt > 64) {
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    auto in_bin = [&](int v) { return (uint32_t)(v - edge) >> shift == 0u; };
     each([&](auto e) {
-      if ((uint32_t)(left[e] - edge) >> shift == 0u) {
-        const int c = atomicAdd(&S.ncand, 1);
-        S.cand[c] = left[e];
-        S.cand_page[c] = page[e];
-      }
+      if (in_bin(left[e])) kmin = min(kmin, (uint32_t)left[e]), kmax = max(kmax, (uint32_t)left[e]);
+    });
+    kmin = wave_reduce(kmin, OpMin{}, 0xffffffffu);
+    kmax = wave_reduce(kmax, OpMax{}, 0u);
+    __syncthreads();  // the bins and the range of the round before have been read
+    if (lane == 0) S.wmax[wave] = kmax, S.wmin[wave] = kmin;
+    if (tid < kTopkFine / 4) ((int4*)S.fine)[tid] = int4{0, 0, 0, 0};
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) kmax = max(kmax, S.wmax[w]), kmin = min(kmin, S.wmin[w]);
+    if (kmin == kmax) {
+      least = (int)kmin, equal = cnt;
+      break;
+    }
+    const int finer = max(0, 24 - __clz((int)(kmax - kmin) | 1));
+    each([&](auto e) {
+      if (in_bin(left[e])) atomicAdd(&S.fine[(left[e] - (int)kmin) >> finer], 1);
+    });
+    __syncthreads();
+    int front = 0;
+    const int o = rank_bin(*(const int4*)&S.fine[kTopkFine - 4 - 4 * lane], rank, front, cnt);
+    rank -= front;
+    shift = finer;
+    edge = (int)kmin + ((kTopkFine - 1 - o) << finer);
+    least = edge;
+  }
+  if (rank < cnt && equal == 0) {
+    each([&](auto e) {
+      if ((uint32_t)(left[e] - edge) >> shift == 0u) S.cand[atomicAdd(&S.ncand, 1)] = left[e];
     });
     __syncthreads();
     const int mine = lane < cnt ? S.cand[lane] : INT32_MIN;
@@ -273,17 +301,26 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
     while ((eq = __ballot(lane < cnt && gt == larger)) == 0) --larger;
     least = __builtin_amdgcn_readlane(
         mine, __builtin_amdgcn_readfirstlane(__ffsll((long long)eq) - 1));
-    if (rank - larger < __popcll(eq)) {  // equal keys: those of the lowest pages are taken
-      const int pg = (eq >> lane) & 1u ? S.cand_page[lane] : INT32_MAX;
-      int lower = 0;
-      for (int i = 0; i < cnt; ++i) lower += __builtin_amdgcn_readlane(pg, i) < pg;
-      const uint64_t last = __ballot(pg != INT32_MAX && lower == rank - larger - 1);
-      const int limit = __builtin_amdgcn_readlane(
-          pg, __builtin_amdgcn_readfirstlane(__ffsll((long long)last) - 1));
-      each([&](auto e) {
-        if (left[e] == least && page[e] > limit) left[e] = INT32_MIN;
-      });
-    }
+    rank -= larger;
+    if (rank < __popcll(eq)) equal = __popcll(eq);
+  }
+  if (equal > 0) {  // of the equal keys the first `rank` are taken; the others are out
+    uint64_t same[NE] = {};
+    int sum = 0;
+    each([&](auto e) {
+      same[e] = __ballot(left[e] == least);
+      sum += __popcll(same[e]);
+    });
+    if (lane == 0) S.gt[wave] = sum;
+    __syncthreads();
+    const uint32_t t = lane < NW ? (uint32_t)S.gt[lane] : 0u;
+    int at = __builtin_amdgcn_readlane((int)(wave_scan(t, OpAdd{}, 0u) - t), wave);
+    if constexpr (ALL) static_for<0, NE>([&](auto e) { at += lanes_below(same[e]); });
+    each([&](auto e) {
+      if (left[e] == least && (ALL ? at++ : at + lanes_below(same[e])) >= rank)
+        left[e] = INT32_MIN;
+      if (!ALL) at += __popcll(same[e]);
+    });
   }
 
   // Positions: a count per wavefront, and the wavefronts in front of it.
