@@ -1,7 +1,7 @@
 """Python binding of libstc (HIP, MI355X): decode attention over a Quest-selected,
 group-packed KV cache.  The functions below have the names of the C entry
-points in include/stc.h and only marshal arguments; every step of the path runs
-in the HIP kernels.  PyTorch is used for device memory and the current stream.
+points in include/stc.h and only marshal arguments, through csrc/binding.cpp; every step of the
+path runs in the HIP kernels.  PyTorch is used for device memory and the current stream.
 
 There is no CPU fallback: if libstc.so cannot be loaded the calls raise.
 """

@@ -120,7 +120,7 @@ __device__ __forceinline__ int rank_bin(int4 h4, int rank, int& above, int& cnt)
 // Time from the scores' arrival to the list, inside the attention launch, against topk_any: 8192 keys of
 // which 256 are kept 5.3 -> 3.6 us, 2048 of which 128 are kept 3.0 -> 2.4 (a step over 28 caches of
 // 131072 tokens 604 -> 543 us, over 64 streams of 2048 pages 30.4 -> 30.0, over 8 streams of 64
-// pages 7.4 -> 7.0).  Scores that it gives up on cost its first phases on top, 0.5 to 1.5 us.
+// pages 7.4 -> 7.0).  Scores that it gives up on cost its first phases on top, 0.3 to 1.5 us.
 template <int IPT, int THREADS, class Emit>
 __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int NP, int k,
                                               TopkLds<IPT, THREADS>& S, Emit emit) {
@@ -348,12 +348,11 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
   return true;
 }
 
-// The same for any scores, with the keys held in registers: thread t owns the IPT adjacent pages t*IPT .. (NP <= THREADS * IPT <= 65535).
-// Each radix
-// pass is a shared-memory histogram of one key digit, which every wavefront then scans for
-// itself (digits in descending order) to find the digit that holds the k-th largest key: no
-// broadcast and no second barrier.  The usual case (one pass, then at most 64 candidates
-// ranked directly) crosses five workgroup barriers.
+// The same for any scores, by radix select: thread t owns the IPT adjacent pages t*IPT .. and holds
+// their keys in registers.  Each radix pass is a shared-memory histogram of one key digit, which
+// every wavefront then scans for itself (digits in descending order) to find the digit that holds
+// the k-th largest key: no broadcast and no second barrier.  The usual case (one pass, then at
+// most 64 candidates ranked directly) crosses five workgroup barriers.
 template <int IPT, int THREADS, class Emit>
 __device__ __forceinline__ void topk_any(const float* __restrict__ sc, int NP, int k,
                                          TopkLds<IPT, THREADS>& S, Emit emit) {
