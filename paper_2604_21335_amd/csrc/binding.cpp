@@ -8,6 +8,7 @@
 namespace {
 
 PyObject* g_error;       // StcError(status, where)
+PyObject* g_shape;       // stc_shape_t
 PyObject* g_device;      // torch._C._cuda_getDevice
 PyObject* g_raw_stream;  // torch._C._cuda_getCurrentRawStream, which takes the device
 PyObject* g_any_stream;  // the package's own way, for builds of torch without these two
@@ -29,15 +30,12 @@ class Args {
 
   const stc_shape_t* shape() {
     PyObject* o = next();
+    const int is = PyObject_IsInstance(o, g_shape);
+    if (is == 0) PyErr_Format(PyExc_TypeError, "%s: shape must be a stc_shape_t", where_);
     Py_buffer b;
-    if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) throw PythonError();
-    const bool fits = b.len == (Py_ssize_t)sizeof(stc_shape_t);
-    if (fits) memcpy(&shape_, b.buf, sizeof shape_);
+    if (is != 1 || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) throw PythonError();
+    memcpy(&shape_, b.buf, sizeof shape_);  // a subclass can only be larger
     PyBuffer_Release(&b);
-    if (!fits) {
-      PyErr_Format(PyExc_TypeError, "%s: shape must be a stc_shape_t", where_);
-      throw PythonError();
-    }
     return &shape_;
   }
 
@@ -74,15 +72,9 @@ class Args {
   void* ws() { return tensor("ws"); }
   size_t bytes() const { return bytes_; }  // of the tensor taken last
 
-  int integer() {
-    PyObject* o = next();
-    PyObject* i = PyLong_CheckExact(o) ? Py_NewRef(o) : PyNumber_Long(o);
-    if (!i) throw PythonError();
-    const unsigned long long v = PyLong_AsUnsignedLongLongMask(i);
-    Py_DECREF(i);
-    if (v == ~0ull && PyErr_Occurred()) throw PythonError();
-    return (int)v;
-  }
+  // What int() takes; index(): whole numbers only.
+  int integer() { return number(PyNumber_Long); }
+  int index() { return number(PyNumber_Index); }
 
   // The current stream of the current device.
   void* stream() {
@@ -103,6 +95,15 @@ class Args {
 
  private:
   PyObject* next() { return args_[at_++]; }
+  int number(PyObject* (*convert)(PyObject*)) {
+    PyObject* o = next();
+    PyObject* i = PyLong_CheckExact(o) ? Py_NewRef(o) : convert(o);
+    if (!i) throw PythonError();
+    const unsigned long long v = PyLong_AsUnsignedLongLongMask(i);
+    Py_DECREF(i);
+    if (v == ~0ull && PyErr_Occurred()) throw PythonError();
+    return (int)v;
+  }
   const char* where_;
   PyObject* const* args_;
   Py_ssize_t at_ = 0;
@@ -145,7 +146,7 @@ STC_PY(build_page_bounds, 3,
   return [=] { return stc_build_page_bounds(&s, K, bounds, st); };)
 
 STC_PY(route_and_pack_values, 12,
-  auto s = *a.shape(); auto mode = a.integer(); auto V = a.bf16("V"); auto logits = a.f32("logits");
+  auto s = *a.shape(); auto mode = a.index(); auto V = a.bf16("V"); auto logits = a.f32("logits");
   auto kcount = a.u8("kcount"); auto fixed_k = a.integer(); auto mask_in = a.u16("mask_in");
   auto mask = a.u16("mask"); auto off = a.u32("tok_off"); auto vpacked = a.bf16("vpacked");
   auto status = a.i32("dev_status"); auto ws = a.ws(); auto nws = a.bytes(); auto st = a.stream();
@@ -232,15 +233,15 @@ STC_PY(append_tail, 7,
   return [=] { return stc_append_tail(&s, k, v, Kt, Vt, n_tail, cap, st); };)
 
 STC_PY(router_logits, 10,
-  auto B = a.integer(); auto Hkv = a.integer(); auto N = a.integer(); auto dm = a.integer();
-  auto G = a.integer(); auto h = a.bf16("h"); auto W = a.bf16("W"); auto bias = a.f32("bias");
+  auto B = a.index(); auto Hkv = a.index(); auto N = a.index(); auto dm = a.index();
+  auto G = a.index(); auto h = a.bf16("h"); auto W = a.bf16("W"); auto bias = a.f32("bias");
   auto per = a.integer(); auto logits = a.f32("logits"); auto st = a.stream();
   return [=] { return stc_router_logits(B, Hkv, N, dm, G, h, W, bias, per, logits, st); };)
 
 STC_PY(compact_tokens, 9,
   auto src = a.bf16("src"); auto idx = a.i32("token_idx"); auto dst = a.bf16("dst");
-  auto B = a.integer(); auto Hkv = a.integer(); auto N = a.integer(); auto keep = a.integer();
-  auto D = a.integer(); auto status = a.i32("dev_status"); auto st = a.stream();
+  auto B = a.index(); auto Hkv = a.index(); auto N = a.index(); auto keep = a.index();
+  auto D = a.index(); auto status = a.i32("dev_status"); auto st = a.stream();
   return [=] { return stc_compact_tokens(src, idx, dst, B, Hkv, N, keep, D, status, st); };)
 
 PyMethodDef methods[] = {
@@ -264,8 +265,9 @@ PyMODINIT_FUNC PyInit__binding() {
   PyObject* pkg = PyImport_ImportModule("paper_2604_21335_amd");
   if (torch_c && pkg) {
     g_error = PyObject_GetAttrString(pkg, "StcError");
+    g_shape = PyObject_GetAttrString(pkg, "stc_shape_t");
     g_any_stream = PyObject_GetAttrString(pkg, "_current_stream");
-    if (g_error && g_any_stream) {
+    if (g_error && g_shape && g_any_stream) {
       g_device = PyObject_GetAttrString(torch_c, "_cuda_getDevice");
       if (g_device) g_raw_stream = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
       PyErr_Clear();
@@ -273,5 +275,5 @@ PyMODINIT_FUNC PyInit__binding() {
   }
   Py_XDECREF(torch_c);
   Py_XDECREF(pkg);
-  return g_error && g_any_stream ? PyModule_Create(&module_def) : nullptr;
+  return g_error && g_shape && g_any_stream ? PyModule_Create(&module_def) : nullptr;
 }
