@@ -130,6 +130,15 @@ struct AttnPlan {
   int slots() const { return waves * nx * pairs; }  // page slots per workgroup
 };
 
+// Keys per thread of the selection inside the launch of a plan, for streams of NP pages; 0 if no form of
+// it holds that many (64 * waves * keys).  Several pairs go with 4 only: 192 to 255 streams of more than
+// 2048 pages with 17 to 32 page slots leave the selection to a launch of its own.
+static int select_keys(const AttnPlan& p, int NP) {
+  if (p.waves != 8) return NP <= 64 * 4 * 8 ? 8 : 0;
+  if (NP <= 64 * 8 * 4) return 4;
+  return p.pairs == 1 && NP <= 64 * 8 * 16 ? 16 : 0;
+}
+
 // Streams of 2049..8192 pages can select inside the attention kernel, 16 keys per thread, while its
 // workgroups are fewer than two per compute unit.  Step in us, inside / as a launch of its own: 12
 // streams of 256 of 8192 pages 22.4 / 23.4, 24 of them 34.9 / 37.9; 16 of 300 of 4096 22.1 / 22.6; 48 of
@@ -244,27 +253,25 @@ int attn_tail(const AttnLaunch& a, bool tail) {
 }
 
 template <int D>
-int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, bool select,
+int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, int keys,
                   bool stream_loads) {
   if (plan.waves != 8)  // few pages: nothing to keep out of the caches
-    return select ? attn_tail<D, 4, 8, false>(a, tail) : attn_tail<D, 4, 0, false>(a, tail);
+    return keys ? attn_tail<D, 4, 8, false>(a, tail) : attn_tail<D, 4, 0, false>(a, tail);
   if (plan.nx == 1) {  // few workgroups, ordinary loads
-    if (select && a.p.NP > 2048) return attn_tail<D, 8, 16, false, false, 1>(a, tail);
-    return select ? attn_tail<D, 8, 4, false, false, 1>(a, tail)
-                  : attn_tail<D, 8, 0, false, false, 1>(a, tail);
+    if (keys == 16) return attn_tail<D, 8, 16, false, false, 1>(a, tail);
+    return keys ? attn_tail<D, 8, 4, false, false, 1>(a, tail)
+                : attn_tail<D, 8, 0, false, false, 1>(a, tail);
   }
   if (plan.pairs > 1) {
-    if (select)
+    if (keys)
       return stream_loads ? attn_tail<D, 8, 4, true, true>(a, tail)
                           : attn_tail<D, 8, 4, false, true>(a, tail);
     return stream_loads ? attn_tail<D, 8, 0, true, true>(a, tail)
                         : attn_tail<D, 8, 0, false, true>(a, tail);
   }
-  if (select) {  // selection inside the kernel: 2048 (8192) keys over the workgroup's threads
-    // (streaming loads lose here: 24 streams of 256 of 8192 pages 36.6 us per step, 34.9)
-    if (a.p.NP > 2048) return attn_tail<D, 8, 16, false>(a, tail);
-    return stream_loads ? attn_tail<D, 8, 4, true>(a, tail) : attn_tail<D, 8, 4, false>(a, tail);
-  }
+  // (streaming loads lose with 16 keys: 24 streams of 256 of 8192 pages 36.6 us per step, 34.9)
+  if (keys == 16) return attn_tail<D, 8, 16, false>(a, tail);
+  if (keys) return stream_loads ? attn_tail<D, 8, 4, true>(a, tail) : attn_tail<D, 8, 4, false>(a, tail);
   return stream_loads ? attn_tail<D, 8, 0, true>(a, tail) : attn_tail<D, 8, 0, false>(a, tail);
 }
 
@@ -276,13 +283,18 @@ int attn_dispatch(const AttnLaunch& a, const AttnPlan& plan, bool tail, bool sel
 // slower beyond (the repeated prologue then delays a second round of workgroups).
 bool attention_can_select(const stc_shape_t& s, int k_pages, int tail_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
-  if (k_pages >= NP) return false;
+  const AttnPlan p = attention_plan(s, k_pages, tail_pages);
+  if (k_pages >= NP || select_keys(p, NP) == 0) return false;
   if (NP > 2048) return long_select_shape(s, k_pages + tail_pages);
   // the workgroups that select must all be resident at once; those that hold only pages of
   // the tail skip the selection and may come in a second round
-  const AttnPlan p = attention_plan(s, k_pages, tail_pages);
   const long long streams = (long long)s.B * s.Hkv;
   return streams * ((k_pages + p.slots() - 1) / p.slots()) <= 512 && streams * p.splits <= 768;
+}
+
+int attention_select_pages(const stc_shape_t& s, int k_pages, int tail_pages) {
+  const AttnPlan p = attention_plan(s, k_pages, tail_pages);
+  return 64 * p.waves * select_keys(p, (s.N + kPage - 1) / kPage);
 }
 
 // Parameters of an attention launch without a page list's consumers filled in.
@@ -315,7 +327,8 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
   AttnLaunch a{attn_params(s, s0, plan, q, K, vpacked, mask, tok_off, page_idx, k_pages, K_tail,
                            V_tail, n_tail, tail_cap, page_heads, sel_score, sel_list, out, ws),
                dim3(plan.splits, streams), st};
-  if (sel_score && (NP > 8192 || per_head || page_heads)) return -1;
+  const int keys = sel_score ? select_keys(plan, NP) : 0;
+  if (sel_score && (keys == 0 || per_head || page_heads)) return -1;
   // with the selection inside, the workgroups of a stream all read the stream's scores: keep
   // them on one XCD (measured on the headline shape: 34.2 against 34.6 us per step)
   if (sel_score && plan.splits > 1 && streams % kXcds == 0) {
@@ -323,9 +336,9 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
     a.grid = dim3(kXcds, plan.splits, streams / kXcds);
   }
   const bool stream_loads = streaming_loads(s, k_pages, tail_pages, kv_div);
-  const bool tail = tail_pages > 0, select = sel_score != nullptr;
-  const int rc = s.D == 128 ? attn_dispatch<128>(a, plan, tail, select, stream_loads)
-                            : attn_dispatch<64>(a, plan, tail, select, stream_loads);
+  const bool tail = tail_pages > 0;
+  const int rc = s.D == 128 ? attn_dispatch<128>(a, plan, tail, keys, stream_loads)
+                            : attn_dispatch<64>(a, plan, tail, keys, stream_loads);
   if (rc) return -1;
   if (plan.splits > 1) {
     if (s.D == 128)

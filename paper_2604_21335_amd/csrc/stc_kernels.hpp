@@ -66,6 +66,8 @@ int launch_attention(const stc_shape_t& s, const void* q, const void* K, const v
 // their stream from these scores themselves and write the list to sel_list.  Only if
 // attention_can_select().
 bool attention_can_select(const stc_shape_t& s, int k_pages, int tail_pages);
+// Most pages per stream that the form which that launch picks can order; 0: none for so many as `s` has.
+int attention_select_pages(const stc_shape_t& s, int k_pages, int tail_pages);
 // The whole step by one workgroup per stream, in one launch.  Only if step_is_one_kernel().
 bool step_is_one_kernel(const stc_shape_t& s, int k_pages, int tail_pages);
 int launch_step(const stc_shape_t& s, const void* q, const void* bounds, const void* K,

@@ -47,3 +47,9 @@ def step(B, Hq, Hkv, D, N, k, n_tail=0):
 def selects_with_scores(B, Hq, Hkv, D, N, k):
     """stc_select_pages as one launch that scores and selects."""
     return _rule("_ZN3stc16score_can_selectERK9stc_shapei", _P, _I)(_shape(B, Hq, Hkv, D, N), k)
+
+
+def select_pages(B, Hq, Hkv, D, N, k, n_tail=0):
+    """Most pages per stream that the attention launch of this step could order itself."""
+    f = _rule("_ZN3stc22attention_select_pagesERK9stc_shapeii", _P, _I, _I, restype=_I)
+    return f(_shape(B, Hq, Hkv, D, N), k, (n_tail + 15) // 16)

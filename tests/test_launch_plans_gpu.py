@@ -106,6 +106,32 @@ def test_step(case):
         t.check(t.c.out, b, h, pages)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,N,G,k,n_tail", [
+    (48, 4, 4, 64, 2049 * 16, 4, 17, 0), (48, 8, 4, 128, 4096 * 16 - 5, 8, 32, 0), (51, 5, 5, 64, 4096 * 16, 4, 32, 0),
+    (51, 5, 5, 128, 2049 * 16, 8, 17, 0), (32, 6, 6, 64, 2500 * 16, 4, 20, 60), (48, 4, 4, 128, 2049 * 16, 8, 30, 17),
+    (51, 5, 5, 64, 4096 * 16, 4, 16, 1)])
+def test_many_long_streams_with_several_pairs(B, Hq, Hkv, D, N, G, k, n_tail):
+    """192 to 255 streams of more pages than a launch of several pairs per wavefront orders: the largest
+    scores are those of the pages from 2048 on, and the step finds them as the two calls do."""
+    assert routes.pairs(B, Hq, Hkv, D, N, k + (n_tail + 15) // 16) == 2
+    assert routes.step(B, Hq, Hkv, D, N, k, n_tail) == "three"
+    t = Case(B, Hq, Hkv, D, N, G, k, n_tail=n_tail)
+    t.K[:, :, 2048 * 16:] *= 2
+    stc.stc_build_page_bounds(t.c.shape, t.K, t.c.bounds)
+    got = {}
+    for one in (False, True):
+        t.c.page_idx.fill_(-7)
+        t.c.out.fill_(float("nan"))
+        t.c.step(t.q, one_call=one)
+        torch.cuda.synchronize()
+        got[one] = (t.c.page_idx.clone(), t.c.out.clone())
+    assert torch.equal(got[False][0], got[True][0]) and torch.equal(got[False][1], got[True][1])
+    for b, h in t.streams():
+        pages = O.select_pages(O.page_scores(t.heads(b, h), O.page_bounds(PT.host_bf16(t.K[b, h]))), k)
+        assert pages[-1] >= 2048 and np.array_equal(t.c.page_idx[b, h].cpu().numpy(), pages)
+        t.check(t.c.out, b, h, pages)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,N,G,pairs", [(48, 4, 4, 64, 100 * 16 - 3, 4, 7), (48, 4, 4, 128, 128 * 16, 8, 8),
                                                   (64, 28, 4, 128, 33 * 16 - 15, 8, 3), (4, 4, 2, 128, 17 * 16, 8, 1)])
 def test_every_page_attended_and_the_list_written(B, Hq, Hkv, D, N, G, pairs):

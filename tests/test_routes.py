@@ -34,3 +34,18 @@ def test_several_pairs_of_pages_per_wavefront(D, streams):
         assert routes.pairs(streams // 4, 4, 4, D, 4096, k, kv_div=4) == (full if k <= 48 else 1)
         assert routes.pairs(191, 1, 1, D, 4096, k) == 1
         assert routes.pairs(513, 1, 1, D, 4096, k) == 1
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("NP", [2047, 2048, 2049, 4096, 8192, 8193])
+def test_a_launch_that_selects_can_order_the_pages_of_its_streams(NP, D):
+    """Whatever the number of streams, kept pages and tail tokens: at most 8192 pages by pages or pairs
+    of pages, at most 2048 by several pairs per wavefront, and what the form itself says."""
+    for streams in range(1, 601):
+        for k in (7, 8, 9, 16, 17, 20, 32, 33, 48, 128, 256):
+            for n_tail in (0, 1, 60, 130):
+                if routes.step(streams, 1, 1, D, NP * 16, k, n_tail) != "in attention":
+                    continue
+                several = routes.pairs(streams, 1, 1, D, NP * 16, k + (n_tail + 15) // 16) > 1
+                assert NP <= (2048 if several else 8192), (streams, k, n_tail)
+                assert NP <= routes.select_pages(streams, 1, 1, D, NP * 16, k, n_tail), (streams, k, n_tail)
