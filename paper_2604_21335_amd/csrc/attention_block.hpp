@@ -300,12 +300,13 @@ __device__ __forceinline__ void attn_block(const AttnParams& P, const int stream
     for (int x = 0; x < NX; ++x) {
       const int pg = M.pgs[x];
       const uint32_t t0 = pg < 0 ? 0 : page_no(pg) * kPage;
-      const uint32_t lim = tok_lim(pg);
+      // absent tokens read the end of the store's last row, those of an absent page the store's first
+      // bytes: their logits are discarded
+      const uint32_t last = pg < 0 ? 0u : tok_lim(pg) * (D * 2) - 16;
       const unsigned char* kb = (pg >= 0 && is_tail(pg)) ? Kts : Ks;  // wave-uniform
 #pragma unroll
       for (int j = 0; j < C::NLD; ++j) {
-        // absent tokens read the end of the store's last row: their logits are discarded
-        const uint32_t ko = min(t0 * (D * 2) + (j * 64 + lane) * 16, lim * (D * 2) - 16);
+        const uint32_t ko = min(t0 * (D * 2) + (j * 64 + lane) * 16, last);
         const u32x4* a = (const u32x4*)(kb + ko);
         kreg[x][j] = STREAM ? __builtin_nontemporal_load(a) : *a;
       }
