@@ -20,7 +20,20 @@ def bits(t):
     (130, 127, 16), (112, 128, 5), (113, 128, 0), (95, 129, 33), (7, 256, 1), (201, 257, 150), (121, 263, 0)])
 @pytest.mark.parametrize("given_masks", [False, True])
 def test_flush_at_tile_edges(D, G, N, n, stay, given_masks):
-    B, Hkv = 2, 3
+    flush_case(2, 3, D, G, N, n, stay, given_masks)
+
+
+@pytest.mark.parametrize("B,Hkv,D,G,N,n,stay", [
+    (43, 6, 64, 8, 33, 1, 0), (43, 6, 128, 8, 97, 31, 1), (65, 4, 128, 16, 1, 32, 3), (37, 7, 64, 1, 15, 33, 0),
+    (43, 6, 128, 2, 95, 49, 20), (65, 4, 64, 4, 130, 64, 33), (65, 4, 128, 8, 31, 63, 0), (96, 8, 64, 8, 121, 97, 5),
+    (96, 8, 64, 8, 113, 128, 40)])
+@pytest.mark.parametrize("given_masks", [False, True])
+def test_flush_of_few_tokens_of_many_streams(B, Hkv, D, G, N, n, stay, given_masks):
+    """More than 256 streams: workgroups that take 32 tokens at a time."""
+    flush_case(B, Hkv, D, G, N, n, stay, given_masks)
+
+
+def flush_case(B, Hkv, D, G, N, n, stay, given_masks):
     g = torch.Generator(device=DEV)
     g.manual_seed(1000 * N + n)
     rand = lambda *s: torch.randn(*s, generator=g, device=DEV)
