@@ -28,42 +28,54 @@ __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(
 
 constexpr int kCombineThreads = 256;
 
-// Merge the split partials of one query head, one workgroup per head.  Bound by latency: a launch and
-// a round trip to memory per 64 splits, then a chain of dependent instructions.  So the splits are
-// shared out among D/4 threads each (4 adjacent channels a thread, 8 splits at a time at D = 128), whose
-// sums meet in shared memory, and lane i of every wavefront has maximum, sum and weight of split i,
-// which all channels share.  The order of the additions is fixed.  From the launch's first instruction
-// to its last 1.1 us for 32 splits; with a thread per channel that went through the splits one after
-// the other, an exponential each, 2.6, and 1.35 for 16 (4 heads of 471 splits of one long stream:
-// a step of 24.9 us instead of 44.8).
-template <int D>
+// Merge the split partials of a query head by WAVES wavefronts.  Bound by latency: a launch and a round
+// trip to memory per BATCH splits, then a chain of dependent instructions.  So the splits are shared out
+// among D/4 threads each (4 adjacent channels a thread), whose sums meet at the end, and lane i of every
+// wavefront has maximum, sum and weight of split i, which all channels share.  The order of the
+// additions is fixed.  With 4 wavefronts 1.1 us for 32 splits from the launch's first instruction to its
+// last; with a thread per channel that went through the splits one after the other, an exponential
+// each, 2.6, and 1.35 for 16 (4 heads of 471 splits of one long stream: a step of 24.9 us instead of
+// 44.8).  Up to 16 splits a wavefront of its own is enough for a head, and many heads then take a
+// quarter of the wavefronts.  Attention with the merge, us, thread per channel / 4 wavefronts / one:
+//   heads x splits   8 x  9              7.7 /  6.6 /  6.5     D = 64      6.6 /  5.9 /  5.6
+//                    8 x 17              7.8 /  6.7 /  7.2                 6.9 /  5.9 /  6.3
+//                  448 x  9             17.1 / 15.4 / 15.3                10.7 /  9.6 /  9.5
+//                  448 x 17             25.5 / 22.6 / 22.9                16.4 / 14.5 / 14.8
+//                 4224 x  4             27.3 / 24.6 / 23.1                16.3 / 15.4 / 15.3
+//                 4224 x 17            101.9 / 92.8 / 92.6                54.7 / 49.5 / 48.2
+//                32768 x  2             85.8 / 86.4 / 73.6                47.4 / 54.0 / 42.7
+template <int D, int WAVES>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
-    const float* __restrict__ partial, float* __restrict__ out, int splits) {
+    const float* __restrict__ partial, float* __restrict__ out, int splits, int heads) {
   constexpr int ST = partial_stride(D);
-  constexpr int ROW = D / 4, GROUPS = kCombineThreads / ROW;  // splits at a time
+  constexpr int ROW = D / 4, GROUPS = 64 * WAVES / ROW;  // splits at a time
+  constexpr int BATCH = WAVES == 1 ? 16 : 64;            // splits requested at once
   typedef __attribute__((ext_vector_type(4), aligned(8))) float f32x4_row;
-  __shared__ float s_sum[GROUPS][D];
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x % (64 * WAVES), lane = tid & 63;
+  const int head = blockIdx.x * (kCombineThreads / 64 / WAVES) +
+                   __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * WAVES));
+  if (head >= heads) return;
   const int group = tid / ROW, c = tid % ROW * 4;
-  const float* pr = partial + (size_t)blockIdx.x * splits * ST;
+  const float* pr = partial + (size_t)head * splits * ST;
   auto all_lanes = [](float x, auto op) {
     x = op(x, dpp_f32<0x128>(x));  // row_ror:8, 4, 2, 1: over the 16 lanes of a row
     x = op(x, dpp_f32<0x124>(x));
     x = op(x, dpp_f32<0x122>(x));
     x = op(x, dpp_f32<0x121>(x));
-    return across_k_groups(x, op);
+    return BATCH > 16 ? across_k_groups(x, op) : x;
   };
   float m = kNegBig, l = 0.f;
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < splits; s0 += 64) {
-    const f32x2 ml = *(const f32x2*)(pr + min(s0 + lane, splits - 1) * ST);
-    f32x4 v[64 / GROUPS];
-    static_for<0, 64 / GROUPS>([&](auto j) {
+  for (int s0 = 0; s0 < splits; s0 += BATCH) {
+    const int mine = s0 + lane % BATCH;
+    const f32x2 ml = *(const f32x2*)(pr + min(mine, splits - 1) * ST);
+    f32x4 v[BATCH / GROUPS];
+    static_for<0, BATCH / GROUPS>([&](auto j) {
       v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (s0 + j * GROUPS < splits)
         v[j] = *(const f32x4_row*)(pr + min(s0 + j * GROUPS + group, splits - 1) * ST + 2 + c);
     });
-    const bool there = s0 + lane < splits;
+    const bool there = mine < splits;
     const float m_new = fmaxf(
         m, all_lanes(there ? ml.x : kNegBig, [](float x, float y) { return fmaxf(x, y); }));
     const float r = __builtin_amdgcn_exp2f(m - m_new);
@@ -71,7 +83,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     l = fmaf(l, r, all_lanes(w * ml.y, [](float x, float y) { return x + y; }));
     a *= r;
     m = m_new;
-    static_for<0, 64 / GROUPS>([&](auto j) {
+    static_for<0, BATCH / GROUPS>([&](auto j) {
       if (s0 + j * GROUPS < splits) {
         const float wj = __shfl(w, j * GROUPS + group);  // 0 past the last split
 #pragma unroll
@@ -79,13 +91,37 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
       }
     });
   }
-  *(f32x4*)&s_sum[group][c] = a;
-  __syncthreads();
-  if (tid < D) {
-    float sum = 0.f;
+  if constexpr (WAVES == 1) {
+    // the groups' sums meet in registers; every group then divides and writes a part of the channels
+    f32x4 sum;
 #pragma unroll
-    for (int g = 0; g < GROUPS; ++g) sum += s_sum[g][tid];
-    out[(size_t)blockIdx.x * D + tid] = l > 0.f ? sum / l : 0.f;
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (GROUPS == 4) {
+        sum[e] = across_k_groups(a[e], [](float x, float y) { return x + y; });
+      } else {
+        const uint32_t u = __float_as_uint(a[e]);
+        const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        sum[e] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      }
+    }
+    float* o = out + (size_t)head * D + c;
+    if constexpr (GROUPS == 4) {
+      const float own = group & 2 ? (group & 1 ? sum[3] : sum[2]) : (group & 1 ? sum[1] : sum[0]);
+      o[group] = l > 0.f ? own / l : 0.f;
+    } else {
+      const f32x2 own = group ? f32x2{sum[2], sum[3]} : f32x2{sum[0], sum[1]};
+      *(f32x2*)(o + 2 * group) = l > 0.f ? f32x2{own.x / l, own.y / l} : f32x2{0.f, 0.f};
+    }
+  } else {
+    __shared__ float s_sum[GROUPS][D];
+    *(f32x4*)&s_sum[group][c] = a;
+    __syncthreads();
+    if (tid < D) {
+      float sum = 0.f;
+#pragma unroll
+      for (int g = 0; g < GROUPS; ++g) sum += s_sum[g][tid];
+      out[(size_t)head * D + tid] = l > 0.f ? sum / l : 0.f;
+    }
   }
 }
 
@@ -341,10 +377,19 @@ int launch_attention(const stc_shape_t& s0, const void* q, const void* K, const 
                             : attn_dispatch<64>(a, plan, tail, keys, stream_loads);
   if (rc) return -1;
   if (plan.splits > 1) {
-    if (s.D == 128)
-      attn_combine_kernel<128><<<s.B * s.Hq, kCombineThreads, 0, st>>>(a.p.partial, out, plan.splits);
-    else
-      attn_combine_kernel<64><<<s.B * s.Hq, kCombineThreads, 0, st>>>(a.p.partial, out, plan.splits);
+    const int heads = s.B * s.Hq;
+    const bool few = plan.splits <= 16;  // one round of requests of a wavefront (table at the kernel)
+#define STC_COMBINE(DD, WAVES)                                                                  \
+  attn_combine_kernel<DD, WAVES><<<(heads * WAVES + 3) / 4, kCombineThreads, 0, st>>>(          \
+      a.p.partial, out, plan.splits, heads)
+    if (s.D == 128) {
+      if (few) STC_COMBINE(128, 1);
+      else STC_COMBINE(128, 4);
+    } else {
+      if (few) STC_COMBINE(64, 1);
+      else STC_COMBINE(64, 4);
+    }
+#undef STC_COMBINE
     if (hipGetLastError() != hipSuccess) return -1;
   }
   return 0;

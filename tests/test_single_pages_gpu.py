@@ -30,6 +30,10 @@ STEPS = [
     (1, 4, 1, 128, 290 * 16, 8, 16, 1, 1), (2, 4, 2, 64, 300 * 16, 4, 20, 200, 1), (1, 7, 1, 128, 400 * 16, 8, 24, 127, 1),
     # 16 keys per thread; the selection as a launch of its own; every page
     (1, 14, 2, 128, 2049 * 16, 8, 130, 0, 1), (1, 4, 2, 64, 8192 * 16, 8, 257, 40, 1), (1, 2, 1, 64, 8193 * 16, 4, 300, 0, 1),
+    # merges of 2, 3, 15, 16 and 17 partial results of 1 to 9 heads
+    (1, 1, 1, 128, 300 * 16, 8, 17, 0, 1), (1, 1, 1, 64, 300 * 16, 8, 20, 0, 1), (3, 3, 3, 64, 260 * 16, 4, 17, 0, 1),
+    (1, 5, 1, 128, 260 * 16, 8, 120, 0, 1), (1, 9, 1, 64, 260 * 16, 8, 128, 0, 1), (1, 3, 1, 128, 260 * 16, 8, 128, 0, 1),
+    (1, 5, 1, 64, 260 * 16, 8, 129, 0, 1), (3, 2, 2, 128, 260 * 16, 8, 136, 0, 1),
     # merges of 33, 64, 65, 129 and 300 partial results
     (1, 5, 1, 64, 2500 * 16, 8, 264, 0, 1), (1, 4, 1, 128, 1500 * 16, 8, 512, 0, 1), (1, 16, 1, 64, 2000 * 16, 8, 513, 0, 1),
     (1, 4, 1, 64, 2200 * 16, 8, 1025, 0, 1), (1, 4, 1, 128, 2401 * 16, 8, 2400, 0, 2),
