@@ -119,8 +119,8 @@ __device__ __forceinline__ int rank_bin(int4 h4, int rank, int& above, int& cnt)
 // octaves of the maximum; NaN and infinities are outside.
 // Time from the scores' arrival to the list, inside the attention launch, against topk_any: 8192 keys of
 // which 256 are kept 5.3 -> 3.6 us, 2048 of which 128 are kept 3.0 -> 2.4 (a step over 28 caches of
-// 131072 tokens 604 -> 543 us, over 64 streams of 2048 pages 30.4 -> 30.0, over 8 streams of 64
-// pages 7.4 -> 7.0).  Scores that it gives up on cost its first phases on top, 0.3 to 1.5 us.
+// 131072 tokens 604 -> 543 us, over 64 streams of 2048 pages 30.4 -> 30.0).  Scores that it gives up
+// on cost its first phases on top, 0.3 to 1.5 us.
 template <int IPT, int THREADS, class Emit>
 __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int NP, int k,
                                               TopkLds<IPT, THREADS>& S, Emit emit) {
@@ -260,7 +260,7 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
   // Too many to rank one by one: bins between the smallest and the largest of them, unless all are equal.
   while (rank < cnt && cnt > 64) {
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    auto in_bin = [&](int v) { return (uint32_t)(v - edge) >> shift == 0u; };
+    auto in_bin = [&](int v) { return ((uint32_t)v - (uint32_t)edge) >> shift == 0u; };
     each([&](auto e) {
       if (in_bin(left[e])) kmin = min(kmin, (uint32_t)left[e]), kmax = max(kmax, (uint32_t)left[e]);
     });
@@ -290,7 +290,7 @@ __device__ __forceinline__ bool topk_positive(const float* __restrict__ sc, int 
   }
   if (rank < cnt && equal == 0) {
     each([&](auto e) {
-      if ((uint32_t)(left[e] - edge) >> shift == 0u) S.cand[atomicAdd(&S.ncand, 1)] = left[e];
+      if (((uint32_t)left[e] - (uint32_t)edge) >> shift == 0u) S.cand[atomicAdd(&S.ncand, 1)] = left[e];
     });
     __syncthreads();
     const int mine = lane < cnt ? S.cand[lane] : INT32_MIN;
