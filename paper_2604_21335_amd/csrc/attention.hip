@@ -231,8 +231,8 @@ static AttnPlan attention_plan(const stc_shape_t& s, int k_pages, int tail_pages
   return p;
 }
 
-int attention_splits(const stc_shape_t& s, int k_pages, int kv_div) {
-  return attention_plan(s, k_pages, 0, kv_div).splits;
+int attention_splits(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
+  return attention_plan(s, k_pages, tail_pages, kv_div).splits;
 }
 int attention_wave_pages(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div) {
   const AttnPlan p = attention_plan(s, k_pages, tail_pages, kv_div);

@@ -52,8 +52,9 @@ int launch_score_select(const stc_shape_t& s, const void* q, const void* bounds,
 int launch_select(const stc_shape_t& s, const void* q, const void* bounds, int k_pages,
                   int32_t* page_idx, float* score, bool per_head, hipStream_t st);
 
-// Workgroups per stream; kv_div > 1: `s` has a KV head per query head, kv_div of which share a cache.
-int attention_splits(const stc_shape_t& s, int k_pages, int kv_div);
+// Questions to the launch plan, asked by tests only.  Workgroups per stream; kv_div > 1: `s` has a KV
+// head per query head, kv_div of which share a cache.
+int attention_splits(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div);
 // Pages that a wavefront of that launch takes.
 int attention_wave_pages(const stc_shape_t& s, int k_pages, int tail_pages, int kv_div);
 size_t attention_ws_bytes(const stc_shape_t& s, int k_pages, bool per_head = false);

@@ -24,12 +24,13 @@ def router_form(B, N, d_model, G):
     return _rule("_ZN3stc11router_formEiiii", _I, _I, _I, _I, restype=_I)(B, N, d_model, G)
 
 
-def pairs(B, Hq, Hkv, D, N, slots, kv_div=1):
-    """Pairs of pages per wavefront of the attention over `slots` page slots (selected and tail).  A
-    launch with page lists per query head has Hkv = Hq and kv_div query heads per KV head."""
-    s = _shape(B, Hq, Hkv, D, N)
-    splits = _rule("_ZN3stc16attention_splitsERK9stc_shapeii", _P, _I, _I, restype=_I)(s, slots, kv_div)
-    full = (slots + 15) // 16
+def pairs(B, Hq, Hkv, D, N, k, kv_div=1, n_tail=0):
+    """Pairs of pages per wavefront of the attention over k listed pages and a tail.  A launch with page
+    lists per query head has Hkv = Hq and kv_div query heads per KV head."""
+    s, tp = _shape(B, Hq, Hkv, D, N), (n_tail + 15) // 16
+    f = _rule("_ZN3stc16attention_splitsERK9stc_shapeiii", _P, _I, _I, _I, restype=_I)
+    splits = f(s, k, tp, kv_div)
+    full = (k + tp + 15) // 16
     return full if splits == 1 else 1
 
 

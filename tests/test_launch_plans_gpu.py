@@ -86,7 +86,7 @@ def test_step(case):
     *shape, n_tail, launches, pairs = case
     B, Hq, Hkv, D, N, G, k = shape
     assert routes.step(B, Hq, Hkv, D, N, k, n_tail) == launches
-    assert routes.pairs(B, Hq, Hkv, D, N, k + (n_tail + 15) // 16) == pairs
+    assert routes.pairs(B, Hq, Hkv, D, N, k, n_tail=n_tail) == pairs
     t = Case(*shape, n_tail=n_tail)
     got = {}
     for one in (False, True):
@@ -113,7 +113,7 @@ def test_step(case):
 def test_many_long_streams_with_several_pairs(B, Hq, Hkv, D, N, G, k, n_tail):
     """192 to 255 streams of more pages than a launch of several pairs per wavefront orders: the largest
     scores are those of the pages from 2048 on, and the step finds them as the two calls do."""
-    assert routes.pairs(B, Hq, Hkv, D, N, k + (n_tail + 15) // 16) == 2
+    assert routes.pairs(B, Hq, Hkv, D, N, k, n_tail=n_tail) == 2
     assert routes.step(B, Hq, Hkv, D, N, k, n_tail) == "three"
     t = Case(B, Hq, Hkv, D, N, G, k, n_tail=n_tail)
     t.K[:, :, 2048 * 16:] *= 2

@@ -46,6 +46,6 @@ def test_a_launch_that_selects_can_order_the_pages_of_its_streams(NP, D):
             for n_tail in (0, 1, 60, 130):
                 if routes.step(streams, 1, 1, D, NP * 16, k, n_tail) != "in attention":
                     continue
-                several = routes.pairs(streams, 1, 1, D, NP * 16, k + (n_tail + 15) // 16) > 1
+                several = routes.pairs(streams, 1, 1, D, NP * 16, k, n_tail=n_tail) > 1
                 assert NP <= (2048 if several else 8192), (streams, k, n_tail)
                 assert NP <= routes.select_pages(streams, 1, 1, D, NP * 16, k, n_tail), (streams, k, n_tail)
