@@ -268,9 +268,10 @@ struct AttnLaunch {
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI, int NX>
 int attn_go(const AttnLaunch& a) {
   // workgroups of 8 wavefronts at D = 128 need more than the default 64 KiB of LDS
-  constexpr int lds_bytes = WAVES * AttnCfg<D>::WAVE_LDS;
-  static_assert(SELECT_IPT == 0 || lds_bytes >= (int)sizeof(TopkLds<SELECT_IPT, 64 * WAVES>),
-                "the selection uses the same memory");
+  // (the selection uses the same memory)
+  constexpr int attn_lds = WAVES * AttnCfg<D>::WAVE_LDS;
+  constexpr int topk_lds = SELECT_IPT > 0 ? (int)sizeof(TopkLds<SELECT_IPT, 64 * WAVES>) : 0;
+  constexpr int lds_bytes = attn_lds > topk_lds ? attn_lds : topk_lds;
   static std::atomic<uint64_t> allowed{0};
   if (!allow_dynamic_lds((const void*)attn_mfma_kernel<D, WAVES, TAIL, SELECT_IPT, STREAM, MULTI, NX>,
                          lds_bytes, allowed))

@@ -26,7 +26,11 @@ def kinds(streams, NP, k, g):
            "mostly zero": torch.where(u(streams, NP, 1) < 0.03, 5 + z.abs(), torch.zeros_like(z)),
            # as many pages above the equal ones that only some of them are taken
            "ties at the end": torch.where(u(streams, NP, 1) < 0.5 * k / NP, 50 + z, torch.full_like(z, 20.0)),
-           "tiny": 1e-37 * (1 + u(streams, NP, 2))}
+           "tiny": 1e-37 * (1 + u(streams, NP, 2)), "close together": 64 + z.clamp(-3, 3) * 0.5,
+           # fewer positive scores than are kept; enough of them, but not among the maxima of adjacent pages
+           "half positive": torch.where(pages[None, :, None] < k / 2, 5 + z.abs(), -5 - z.abs()),
+           "positive at the end": torch.where(pages[None, :, None] >= NP - k - 3, 5 + z.abs(), -5 - z.abs()),
+           "one far below": torch.where(pages[None, :, None] == 1, torch.full_like(z, 1e-30), 40 + 5 * z)}
     nan = 40 + 5 * z
     nan[:, NP // 2] = float("inf")        # times the zeros of the other channels
     out["not finite"] = nan
