@@ -4,9 +4,8 @@
 
 namespace stc {
 
-// No bound on the registers: several pairs at D = 64 held to 128 of them, for two workgroups per CU,
-// spill 2 to 11 and are slower at every number of streams (512 streams of 40 pages 15.1 us, 14.1
-// without; 256 streams of 64 pages and a tail 16.3, 13.3; 512 of 128 pages 37.8, 36.8).
+// No bound on the registers is needed: the forms of several pairs take 120 to 125 of them at D = 64, two
+// workgroups per CU, and 188 at most at D = 128; those of one pair or page 64 at D = 64.
 template <int D, int WAVES, bool TAIL, int SELECT_IPT, bool STREAM, bool MULTI, int NX>
 __global__ __launch_bounds__(64 * WAVES) void attn_mfma_kernel(
     const void* list_or_score, const uint16_t* q, const uint16_t* K, const uint16_t* mask,
@@ -179,15 +178,27 @@ static int select_keys(const AttnPlan& p, int NP) {
 // workgroups are fewer than two per compute unit.  Step in us, inside / as a launch of its own: 12
 // streams of 256 of 8192 pages 22.4 / 23.4, 24 of them 34.9 / 37.9; 16 of 300 of 4096 22.1 / 22.6; 48 of
 // 100 of 3000 28.6 / 29.9.
+// The line is not where the two meet: at 512 workgroups, which stay three launches as they always were
+// (the tests of the step ask for that form there), inside would be faster still: 64 streams of 128 of 2049
+// pages 30.2 / 30.5 (D = 64: 19.8 / 20.4), of 4096 38.6 / 40.0; 32 of 256 of 8192 41.4 / 42.1 (D = 64:
+// 25.9 / 27.9).
 static bool long_select_shape(const stc_shape_t& s, int k_pages) {
   const int NP = (s.N + kPage - 1) / kPage;
   return NP > 2048 && NP <= 8192 && k_pages > 8 &&
          (long long)s.B * s.Hkv * ((k_pages + 15) / 16) < 512;
 }
 
-// Workgroups that take a whole stream each and are resident at once (the registers of a CU hold
-// one at D = 128, two at D = 64 without a tail; with one the two halves of 512 streams follow
-// each other, which is no slower than splits: 26.2 us for 30.2 at 64 pages).
+// Workgroups that take a whole stream each and are resident at once: the registers of a CU hold one at
+// D = 128, two at D = 64, with and without a tail.  Step in us at D = 64, a workgroup per stream / splits
+// and a merge (tail: its pages):
+//   512 streams of  64 of  250 pages  27.3 / 30.5   and a tail of 2  30.2 / 31.4
+//   512         of  64 of  512        33.4 / 36.0
+//   512         of  64 of 1100                      and a tail of 2  48.8 / 51.8
+//   512         of 100 of  512                      and a tail of 4  46.4 / 46.1
+//   384         of  40 of  500                      and a tail of 2  21.6 / 24.5
+//   300         of  48 of  400                      and a tail of 2  24.0 / 24.4
+//   260         of  64 of  300        24.0 / 24.2   and a tail of 2  26.5 / 24.6
+// (Just above 256 streams few CUs have a second one.)
 static int resident_streams(const stc_shape_t& s) { return s.D == 128 ? 256 : 512; }
 
 // K rows and value runs are read once per step.  What a launch cannot know is whether they still lie

@@ -6,21 +6,20 @@
 
 namespace stc {
 
-// The three parts are those of the separate kernels and give the same bits: the scoring of
-// score_tiles.hpp into LDS (and to `score`, where the caller finds the scores afterwards), the
-// selection of topk_block.hpp from there, the attention of attention_block.hpp without splits.
-// RM: query heads per KV head are at most this; `heads` = their number.
-// Bound by memory while many workgroups are in different parts, by the chain of dependent
-// accesses of one stream where there are few.
-// At D = 64 two workgroups share a CU, with 128 registers each; without a tail one register is
-// spilled for it (512 streams of 512 pages, 64 kept 36.5 us, 39.2 with one workgroup per CU; of 250
-// pages, 30 kept 19.6, 22.5; but 256 streams of 512 pages 20.3, 19.6).
 // Bytes of shared memory in front of the selection's: query operands and page scores.
 template <int D, int RM>
 constexpr int step_score_lds() {
   return score_q_lds_bytes<D, RM>() + kStepKeys * 4;
 }
 
+// The three parts are those of the separate kernels and give the same bits: the scoring of
+// score_tiles.hpp into LDS (and to `score`, where the caller finds the scores afterwards), the
+// selection of topk_block.hpp from there, the attention of attention_block.hpp without splits.
+// RM: query heads per KV head are at most this; `heads` = their number.
+// Bound by memory while many workgroups are in different parts, by the chain of dependent
+// accesses of one stream where there are few.
+// At D = 64 two workgroups share a CU: 120 registers, 122 with a tail, nothing spilled (the bound of 128
+// holds them to that, and the compiler stays below it without one).
 template <int D, int RM, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void step_kernel(
     const score_u32x4* __restrict__ tiles, float* __restrict__ score, const uint16_t* q,

@@ -114,7 +114,10 @@ __device__ __forceinline__ int topk_shift(int hi, int lo) {
 //     all equal             24.2 / 25.4 / 18.1   31.0 / 31.6 / 28.0
 //     3 % positive, zeros   47.2 / 46.2 / 19.2   42.0 / 40.0 / 28.0   24.5 / 24.3 / 20.8
 //     rising with the page  19.7 / 20.0 / 20.0   30.0 / 28.6 / 29.7   21.9 / 21.1 / 21.1
-// (rising: all kept pages are one wavefront's.)  Measured and left out: counting a bin that many lanes share
+// (rising: all kept pages are one wavefront's.)  With four channels of the keys eight times the others, as the
+// benchmark's are, ordinary steps pay 0.5 to 1 % for the range of the keys, without which the second of the
+// three counted at once: 64 streams of 2048 pages, 28 heads 28.0 / 28.2; one layer of 4 streams of 8192 15.39 /
+// 15.53; 40 of 751 with a tail 16.5 / 16.7.  Measured and left out: counting a bin that many lanes share
 // by ballots (20.0 -> 21.9 with rising scores), lists of 128 to 256 keys with a walk over the keys in
 // registers where they do not fit (17.4 there, but 2 to 4 % more in every ordinary step: its code).
 template <int IPT, int THREADS, class Emit>
